@@ -22,7 +22,7 @@
  * beta [B, H].
  *
  * Ownership: the caller allocates and frees every buffer (including the workspaces of
- * sfda_chunk_fwd_segmented and sfda_chunk_bwd) and owns the stream; the library allocates
+ * the factored and segmented forwards and of sfda_chunk_bwd) and owns the stream; the library allocates
  * no device memory and keeps no state between calls (calls are reentrant; calls
  * that write the same buffers on different streams race, as any two kernels would).
  *
@@ -174,6 +174,43 @@ sfda_status_t sfda_chunk_fwd_decoupled(const void* q, const void* k, const void*
                                        sfda_stream_t stream);
 
 /*
+ * sfda_chunk_fwd_factored, sfda_chunk_fwd_decoupled_factored -- sfda_chunk_fwd and
+ * sfda_chunk_fwd_decoupled in two launches per piece of the sequence: one forms what every
+ * 16-token block does to the state (the products T (conj(K) G), conj(Q) G - A T (conj(K) G) and
+ * the like of the chunk relations of Thm 4.2, 4.4, 4.5; all blocks at once), the other scans the
+ * blocks with only the state-dependent products left.  Results agree with the one-launch
+ * forwards to rounding and do not depend on the pieces.
+ *   Arguments, errors and numerical range as the one-launch entry points (a block outside the
+ *   range gives NaN outputs for the whole block and everything after it), plus:
+ *   workspace : device memory of at least sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m,
+ *               n, in_dtype, decoupled) bytes (SFDA_ERR_SHAPE if smaller, SFDA_ERR_NULL if
+ *               NULL), 16-byte aligned, not overlapping any other argument (SFDA_ERR_ALIAS); no
+ *               initial contents needed.  Holds the operands of up to 256 MiB worth of blocks at
+ *               a time (at least one 64-token step of every head) and, in more than one piece, the
+ *               state (0 for sizes or a dtype out of range).
+ *   S_T == S0 (in place) is allowed.  T == 0 needs no workspace.
+ */
+size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n,
+                                               sfda_dtype_t in_dtype, int decoupled);
+
+sfda_status_t sfda_chunk_fwd_factored(const void* q, const void* k, const void* v,
+                                      const void* alpha, const void* theta, const void* beta,
+                                      const float* S0, void* o, float* S_T,
+                                      int B, int H, int T, int m, int n, int C,
+                                      sfda_dtype_t in_dtype, sfda_dtype_t out_dtype,
+                                      void* workspace, size_t workspace_bytes,
+                                      sfda_stream_t stream);
+
+sfda_status_t sfda_chunk_fwd_decoupled_factored(const void* q, const void* k, const void* r,
+                                                const void* v, const void* alpha,
+                                                const void* theta, const void* eta,
+                                                const void* beta, const float* S0, void* o,
+                                                float* S_T, int B, int H, int T, int m, int n,
+                                                int C, sfda_dtype_t in_dtype,
+                                                sfda_dtype_t out_dtype, void* workspace,
+                                                size_t workspace_bytes, sfda_stream_t stream);
+
+/*
  * sfda_chunk_fwd_segmented -- sfda_chunk_fwd with each head's sequence cut into G
  * segments of T / G tokens that are scanned in parallel (for few heads over long
  * sequences, where one workgroup per head leaves most of the GPU idle).  It uses the
@@ -181,23 +218,22 @@ sfda_status_t sfda_chunk_fwd_decoupled(const void* q, const void* k, const void*
  * the stretch's transitions, B its write from the zero state) composed along the segments
  * (Lemma A.2, the boundary-state scan of Thm 6.1 at segment granularity): chunk passes give
  * every segment's P_g (final state from S0 = I with v = 0) and B_g (final state from
- * S0 = 0), and a fold gives S_in[g + 1] = P_g S_in[g] + B_g and S_T = S_in[G].  With
- * float32 inputs the same two passes also give the readouts X_t = P_t^* q_t and the
- * zero-state outputs o0_t, and a join writes o_t = o0_t + S_in^* X_t (the same law token by
- * token; a bfloat16 o is then rounded twice); with bfloat16 inputs a third pass writes o
- * from the exact incoming states.  With float32 inputs and n <= 64 the two passes run as
- * one scan per segment (one copy of the chunk factors, twice the columns).  Up to two
- * (float32) or three (bfloat16) times the scan work of sfda_chunk_fwd, spread over G times
- * as many workgroups; results agree with it to rounding.
+ * S0 = 0), a fold gives S_in[g + 1] = P_g S_in[g] + B_g and S_T = S_in[G], and a third pass
+ * writes o from the exact incoming states: three times the scan work of sfda_chunk_fwd, spread
+ * over G times as many workgroups; results agree with it to rounding.  With float32 inputs
+ * the call runs the factored forward (sfda_chunk_fwd_factored, bitwise its result) in the same
+ * workspace instead, a piece of the sequence at a time, which spreads each head's work
+ * without repeating it; where the workspace does not hold one 64-token step of that, it runs
+ * sfda_chunk_fwd.
  *   Arguments and errors as sfda_chunk_fwd, plus:
  *   G >= 1 with T a multiple of G * C (SFDA_ERR_SHAPE otherwise; T == 0 is as
  *   sfda_chunk_fwd).
  *   workspace : device memory of at least sfda_chunk_fwd_segmented_workspace_bytes(B, H,
  *               T, m, n, G, in_dtype) bytes (SFDA_ERR_SHAPE if smaller, SFDA_ERR_NULL if
  *               NULL), 16-byte aligned, not overlapping any other argument
- *               (SFDA_ERR_ALIAS); no initial contents needed.  Holds, per segment, P_g
- *               (m x m), B_g and the incoming state (m x n), and with float32 inputs per
- *               token X_t (m), complex float32 (0 for sizes or a dtype out of range).
+ *               (SFDA_ERR_ALIAS); no initial contents needed.  Its size is that of, per
+ *               segment, P_g (m x m), B_g and the incoming state (m x n), and with float32
+ *               inputs m more per token, complex float32 (0 for sizes or a dtype out of range).
  *   S_T == S0 (in place) is allowed.
  */
 size_t sfda_chunk_fwd_segmented_workspace_bytes(int B, int H, int T, int m, int n, int G,
@@ -209,9 +245,9 @@ size_t sfda_chunk_fwd_segmented_workspace_bytes(int B, int H, int T, int m, int 
  * for which the segments' workgroups (B * H * G * ceil(n / 64)) still fit the compute units
  * once each, T is a multiple of G * C and every segment keeps at least 256 tokens; 1 (use
  * sfda_chunk_fwd) when that G is below 4 for float32 inputs or below 8 for bfloat16 ones.
- * The segmented scan does two (float32) or three (bfloat16) times the scan work of
- * sfda_chunk_fwd spread over G times the workgroups, so it pays only when few heads would
- * leave most compute units idle.  Sizes or a dtype out of range, or no device, give 1.
+ * With bfloat16 inputs the segmented scan does three times the scan work of sfda_chunk_fwd spread
+ * over G times the workgroups, so it pays only when few heads would leave most compute units
+ * idle.  Sizes or a dtype out of range, or no device, give 1.
  * Launches nothing and allocates nothing.
  */
 int sfda_chunk_fwd_auto_segments(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype);

@@ -82,6 +82,13 @@ int auto_slice(long BH, int n)
     return slice;
 }
 
+// the factored scans run one workgroup per head and 8 value columns
+bool factored_fits(long BH, int n) { return (BH + 7) * ((n + 7) / 8) <= 0x7FFFFFFFL; }
+// most bytes of operand records that the suggested workspace holds at a time (the sequence then
+// runs in pieces; the records of one piece also stay within reach of the 256 MiB last-level
+// cache)
+constexpr size_t FACTORED_CAP = size_t(256) << 20;
+
 }  // namespace
 
 extern "C" {
@@ -218,13 +225,16 @@ sfda_status_t sfda_chunk_fwd_gated(const void* q, const void* k_raw, const void*
                           stream, slice, nullptr, 0, false, &gp);
 }
 
-sfda_status_t sfda_chunk_fwd_decoupled(const void* q, const void* k, const void* r, const void* v,
+// the checks of the write-decoupled forward and its launch descriptor (run: false when there is
+// nothing to launch)
+static sfda_status_t decoupled_prepare(const void* q, const void* k, const void* r, const void* v,
                                        const void* alpha, const void* theta, const void* eta,
                                        const void* beta, const float* S0, void* o, float* S_T,
                                        int B, int H, int T, int m, int n, int C,
                                        sfda_dtype_t in_dtype, sfda_dtype_t out_dtype,
-                                       sfda_stream_t stream)
+                                       sfda_stream_t stream, sfda::ChunkLaunch& L, bool& run)
 {
+    run = false;
     const int slice = auto_slice(static_cast<long>(B) * H, n);
     // the shared checks, with the erase strengths in beta's place
     const sfda_status_t st0 = chunk_fwd_impl(q, k, v, alpha, theta, eta, S0, o, S_T, B, H, T, m, n,
@@ -241,15 +251,102 @@ sfda_status_t sfda_chunk_fwd_decoupled(const void* q, const void* k, const void*
         return SFDA_ERR_ALIAS;
     if (S_T && T > 0 && (overlap(range_of(S_T, BH * m * n * 2 * 4), rr) || overlap(range_of(S_T, BH * m * n * 2 * 4), rb)))
         return SFDA_ERR_ALIAS;
-    sfda::ChunkLaunch L;
     L.q = q; L.k = k; L.v = v; L.alpha = alpha; L.theta = theta; L.beta = eta;
     L.r = r; L.wbeta = beta;
     L.S0 = S0; L.o = o; L.S_T = S_T;
     L.B = B; L.H = H; L.T = T; L.m = m; L.n = n; L.C = C; L.slice = slice;
     L.in_bf16 = in_dtype == SFDA_BF16;
     L.out_bf16 = out_dtype == SFDA_BF16;
+    run = true;
+    return SFDA_OK;
+}
+
+sfda_status_t sfda_chunk_fwd_decoupled(const void* q, const void* k, const void* r, const void* v,
+                                       const void* alpha, const void* theta, const void* eta,
+                                       const void* beta, const float* S0, void* o, float* S_T,
+                                       int B, int H, int T, int m, int n, int C,
+                                       sfda_dtype_t in_dtype, sfda_dtype_t out_dtype,
+                                       sfda_stream_t stream)
+{
+    sfda::ChunkLaunch L;
+    bool run;
+    const sfda_status_t st0 = decoupled_prepare(q, k, r, v, alpha, theta, eta, beta, S0, o, S_T, B, H, T, m, n, C,
+                                                in_dtype, out_dtype, stream, L, run);
+    if (st0 != SFDA_OK || !run) return st0;
     const hipError_t e = sfda::launch_chunk_decoupled(L, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
+}
+
+size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n, sfda_dtype_t in_dtype,
+                                               int decoupled)
+{
+    if (B <= 0 || H <= 0 || T <= 0 || m < 1 || m > 64 || n < 1 || !state_fits(m, n) || !chunk_rows_fit(n) ||
+        !dtype_ok(in_dtype))
+        return 0;
+    const long BH = static_cast<long>(B) * H;
+    if (!factored_fits(BH, n)) return 0;
+    return sfda::factored_bytes(BH, T, m, n, in_dtype == SFDA_BF16, decoupled != 0, FACTORED_CAP);
+}
+
+// the checks of both factored entry points past sfda_chunk_fwd's, then the launches
+static sfda_status_t factored_impl(const sfda::ChunkLaunch& L, sfda_dtype_t in_dtype, sfda_dtype_t out_dtype,
+                                   void* workspace, size_t workspace_bytes, sfda_stream_t stream)
+{
+    const long BH = static_cast<long>(L.B) * L.H;
+    if (!factored_fits(BH, L.n)) return SFDA_ERR_SHAPE;
+    const size_t need = sfda_chunk_fwd_factored_workspace_bytes(L.B, L.H, L.T, L.m, L.n, in_dtype, L.r != nullptr);
+    if (!workspace) return SFDA_ERR_NULL;
+    if (!aligned16(workspace)) return SFDA_ERR_ALIGN;
+    if (workspace_bytes < need) return SFDA_ERR_SHAPE;
+    const long ei = esize(in_dtype), eo = esize(out_dtype), BHT = BH * L.T, mn = static_cast<long>(L.m) * L.n;
+    const Range rw = range_of(workspace, static_cast<long>(need));
+    const Range all[] = {range_of(L.q, BHT * L.m * 2 * ei), range_of(L.k, BHT * L.m * 2 * ei),
+                         range_of(L.v, BHT * L.n * 2 * ei), range_of(L.alpha, BHT * L.m * ei),
+                         range_of(L.theta, BHT * L.m * ei), range_of(L.beta, BHT * ei),
+                         range_of(L.o, BHT * L.n * 2 * eo), range_of(L.S0, BH * mn * 8),
+                         range_of(L.S_T, BH * mn * 8), range_of(L.r, BHT * L.m * 2 * ei), range_of(L.wbeta, BHT * ei)};
+    for (const Range& r : all)
+        if (r.lo && overlap(rw, r)) return SFDA_ERR_ALIAS;
+    return sfda::launch_factored(L, workspace, need, device_cus(), static_cast<hipStream_t>(stream)) == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
+}
+
+sfda_status_t sfda_chunk_fwd_factored(const void* q, const void* k, const void* v, const void* alpha,
+                                      const void* theta, const void* beta, const float* S0, void* o,
+                                      float* S_T, int B, int H, int T, int m, int n, int C,
+                                      sfda_dtype_t in_dtype, sfda_dtype_t out_dtype, void* workspace,
+                                      size_t workspace_bytes, sfda_stream_t stream)
+{
+    const int slice = auto_slice(static_cast<long>(B) * H, n);
+    const bool empty = T == 0 || B == 0 || H == 0;      // nothing to factor (T == 0 copies the state)
+    const sfda_status_t st0 = chunk_fwd_impl(q, k, v, alpha, theta, beta, S0, o, S_T, B, H, T, m, n, C, in_dtype,
+                                             out_dtype, stream, slice, nullptr, 0, /*check_only=*/!empty);
+    if (st0 != SFDA_OK || empty) return st0;
+    sfda::ChunkLaunch L;
+    L.q = q; L.k = k; L.v = v; L.alpha = alpha; L.theta = theta; L.beta = beta;
+    L.S0 = S0; L.o = o; L.S_T = S_T;
+    L.B = B; L.H = H; L.T = T; L.m = m; L.n = n; L.C = C; L.slice = slice;
+    L.in_bf16 = in_dtype == SFDA_BF16;
+    L.out_bf16 = out_dtype == SFDA_BF16;
+    return factored_impl(L, in_dtype, out_dtype, workspace, workspace_bytes, stream);
+}
+
+sfda_status_t sfda_chunk_fwd_decoupled_factored(const void* q, const void* k, const void* r, const void* v,
+                                                const void* alpha, const void* theta, const void* eta,
+                                                const void* beta, const float* S0, void* o, float* S_T,
+                                                int B, int H, int T, int m, int n, int C,
+                                                sfda_dtype_t in_dtype, sfda_dtype_t out_dtype,
+                                                void* workspace, size_t workspace_bytes, sfda_stream_t stream)
+{
+    sfda::ChunkLaunch L;
+    bool run;
+    const sfda_status_t st0 = decoupled_prepare(q, k, r, v, alpha, theta, eta, beta, S0, o, S_T, B, H, T, m, n, C,
+                                                in_dtype, out_dtype, stream, L, run);
+    if (st0 != SFDA_OK || !run) return st0;
+    if (T == 0) {                                       // copies the state
+        const hipError_t e = sfda::launch_chunk_decoupled(L, static_cast<hipStream_t>(stream));
+        return e == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
+    }
+    return factored_impl(L, in_dtype, out_dtype, workspace, workspace_bytes, stream);
 }
 
 size_t sfda_chunk_fwd_segmented_workspace_bytes(int B, int H, int T, int m, int n, int G,
@@ -328,52 +425,40 @@ static sfda_status_t segmented_impl(const void* q, const void* k, const void* v,
         if (overlap(rw, r)) return SFDA_ERR_ALIAS;
 
     const hipStream_t st = static_cast<hipStream_t>(stream);
+    sfda::ChunkLaunch L;
+    L.q = q; L.k = k; L.v = v; L.alpha = alpha; L.theta = theta; L.beta = beta;
+    L.m = m; L.n = n; L.C = C;
+    L.in_bf16 = in_dtype == SFDA_BF16;
+    L.out_bf16 = out_dtype == SFDA_BF16;
+    if (in_dtype == SFDA_F32) {
+        // the factored forward needs no segments: the workspace holds its operand records, one
+        // piece of the sequence at a time.  Where not even one step's records fit (a few
+        // hundred tokens, few columns) one scan per head takes less time than two launches.
+        L.B = B; L.H = H; L.T = T; L.S0 = S0; L.S_T = S_T; L.o = o;
+        L.slice = auto_slice(BH, n);
+        const bool fits = factored_fits(BH, n) && sfda::factored_bytes(BH, T, m, n, false, false, 0) <= need;
+        const hipError_t e = fits ? sfda::launch_factored(L, workspace, need, device_cus(), st) : sfda::launch_chunk(L, st);
+        return e == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
+    }
     const long segs = BH * G;
     float* P = static_cast<float*>(workspace);                      // [segs][m][m]
     float* Bs = P + segs * m * m * 2;                               // [segs][m][n]
     float* Sin = Bs + segs * static_cast<long>(m) * n * 2;          // [segs][m][n]
-    float* X = Sin + segs * static_cast<long>(m) * n * 2;           // [segs][T / G][m], float32 inputs
     // [B, H, T, .] with T = G * Ts is [B*H*G, Ts, .]: each segment runs as a head
-    const int Ts = T / G;
-    // float32 inputs: the outputs come from the zero-state pass and a join (o0 + S_in^* X),
-    // cheaper than a third pass of the latency-bound float32 scan; bfloat16 inputs: a third
-    // pass of the pipelined kernel from the incoming states (cheaper than writing X in
-    // float32 and the join)
-    const bool join = in_dtype == SFDA_F32 && o != nullptr;
-    sfda::ChunkLaunch L;
-    L.q = q; L.k = k; L.alpha = alpha; L.theta = theta; L.beta = beta;
-    L.B = static_cast<int>(segs); L.H = 1; L.T = Ts; L.m = m; L.C = C;
-    L.in_bf16 = in_dtype == SFDA_BF16;
-    if (join && n <= 64) {
-        // P_g and B_g in one scan per segment (one copy of the chunk factors): the transfer
-        // columns from I_m with X_t = P_t^* q_t, the value columns from zero with o0 into o
-        L.v = v; L.S0 = nullptr; L.S_T = Bs; L.o = o; L.out_bf16 = out_dtype == SFDA_BF16;
-        L.n = n; L.slice = slice_n; L.xo = X; L.pend = P;
-        if (sfda::launch_chunk_segment(L, st) != hipSuccess) return SFDA_ERR_HIP;
-    } else {
-        // P_g (and with the join X_t = P_t^* q_t, the m-column float32 output): S0 = I,
-        // v = 0, in place on the identity
-        if (sfda::launch_identity(P, segs, m, st) != hipSuccess) return SFDA_ERR_HIP;
-        L.v = nullptr; L.S0 = P; L.S_T = P; L.o = join ? X : nullptr; L.out_bf16 = false;
-        L.n = m; L.slice = ((m + 7) / 8) * 8;
-        if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
-        // B_g (and with the join the zero-state outputs o0, into o)
-        L.v = v; L.S0 = nullptr; L.S_T = Bs; L.o = join ? o : nullptr; L.out_bf16 = out_dtype == SFDA_BF16;
-        L.n = n; L.slice = slice_n;
-        if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
-    }
-    // incoming states and S_T
+    L.B = static_cast<int>(segs); L.H = 1; L.T = T / G;
+    // P_g: S0 = I, v = 0, in place on the identity
+    if (sfda::launch_identity(P, segs, m, st) != hipSuccess) return SFDA_ERR_HIP;
+    L.v = nullptr; L.S0 = P; L.S_T = P; L.o = nullptr;
+    L.n = m; L.slice = ((m + 7) / 8) * 8;
+    if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
+    // B_g
+    L.v = v; L.S0 = nullptr; L.S_T = Bs;
+    L.n = n; L.slice = slice_n;
+    if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
+    // incoming states and S_T, then the outputs from the exact incoming states
     if (sfda::launch_fold(P, Bs, Sin, S0, S_T, BH, G, m, n, st) != hipSuccess) return SFDA_ERR_HIP;
-    if (join) {
-        // o = o0 + S_in^* X (the affine law of each segment, token by token)
-        if (sfda::launch_join(X, Sin, o, out_dtype == SFDA_BF16, segs, Ts, m, n, st) != hipSuccess)
-            return SFDA_ERR_HIP;
-    } else {
-        // outputs from the exact incoming states
-        L.S0 = Sin; L.S_T = nullptr; L.o = o;
-        if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
-    }
-    return SFDA_OK;
+    L.S0 = Sin; L.S_T = nullptr; L.o = o;
+    return sfda::launch_chunk(L, st) == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
 }
 
 sfda_status_t sfda_chunk_fwd_segmented(const void* q, const void* k, const void* v,

@@ -25,6 +25,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 namespace sfda {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -155,6 +157,39 @@ __device__ __forceinline__ void mma<PREC_BF16>(f32x4& acc, const Frag8& a, const
 }
 
 __device__ __forceinline__ f32x4 zero4() { f32x4 z = {0.f, 0.f, 0.f, 0.f}; return z; }
+
+// ---------------------------------------------------------------- 16 x 16 inverses
+// N = (I - X)^{-1} for X strictly lower triangular (X = -(D_beta L') on a diagonal block),
+// i.e. N = I + X N, by forward substitution over the pivots s = 0 .. 14.  Lane (i, cg) --
+// i = lane % 16, cg = lane / 16 -- holds row i of X and row i, columns cg, cg + 4, cg + 8,
+// cg + 12 of N (slot k holds column 4k + cg); the pivot row N(s, .) is lane s of the lane's
+// own 16-lane row (a DPP row broadcast).  N is lower triangular, so the pivot row is zero
+// past column s and slot k takes part only in the steps s >= 4k.
+template <int K>
+__device__ __forceinline__ float row_bcast(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + K, 0xF, 0xF, false));
+}
+// SLOTS: the slots k this lane's wave carries (bit k); two waves can share one inverse, one
+// taking slots {0, 3}, the other {1, 2} (18 of the 36 slot steps each)
+template <int S, int SLOTS>
+__device__ __forceinline__ void subst_step(float (&nr)[4], float (&ni)[4], const float2 (&xrow)[16])
+{
+    const float xr = xrow[S].x, xi = xrow[S].y;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (4 * k > S || !((SLOTS >> k) & 1)) continue;
+        const float pr = row_bcast<S>(nr[k]), pi = row_bcast<S>(ni[k]);
+        nr[k] = __builtin_fmaf(xr, pr, __builtin_fmaf(-xi, pi, nr[k]));
+        ni[k] = __builtin_fmaf(xr, pi, __builtin_fmaf(xi, pr, ni[k]));
+    }
+}
+template <int SLOTS = 0xF, int... S>
+__device__ __forceinline__ void subst_steps(float (&nr)[4], float (&ni)[4], const float2 (&xrow)[16],
+                                            std::integer_sequence<int, S...>)
+{
+    (subst_step<S, SLOTS>(nr, ni, xrow), ...);
+}
+constexpr int SLOTS_A = 0x9, SLOTS_B = 0x6;     // the two halves of a shared inverse
 
 // ----------------------------------------------------------------- workgroup placement
 

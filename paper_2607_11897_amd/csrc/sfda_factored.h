@@ -1,0 +1,60 @@
+// The factored chunk evaluation: what a 16-token block does to the state depends on the
+// block's q, k, alpha, theta and beta only through a few small operands.  With S the state
+// entering the block (in the frame of its 64-token step, below), the block relations of
+// sfda_chunk_bf16.hip
+//   Delta = N D_beta (conj(V) - (conj(K) G) S),   N = (I + D_beta L)^{-1}
+//   O^*   = (conj(Q) G) S + A Delta,   S_out = |D| S + (K Q)^T Delta
+// read, with T = N D_beta (Thm 4.2's D_beta M), W = T (conj(K) G) and Z = conj(Q) G - A W,
+//   Delta = X conj(V) - W S,   O^* = Y conj(V) + Z S,   S_out = |D| S + (K Q)^T Delta,
+// with X = T and Y = A T.  The write-decoupled variant (erase rows k with eta, write rows r with
+// beta; L_r, A_r its k-r and q-r Gram blocks, T = N D_eta) has the same form with
+// X = -T L_r D_beta, Y = A_r D_beta + A X and one more term, (R Q)^T D_beta conj(V), in S_out.
+//
+// So the work splits in two: a preparing kernel forms every block's operands at once (one
+// workgroup per head and 64-token step, one wave per block), and a scan over the blocks that
+// only holds the products with the state.  Where the state-dependent chain of a chunk used to
+// wait for the chunk's loads, Gram products and inverse, it now waits for two products.
+//
+// Operand record of a 16-token block (in the caller's workspace, per head and step): left
+// operands of the matrix cores as the scans' lanes read them.  A fragment covers 16 rows x 16
+// complex K indices: lane (c, g) = (lane % 16, lane / 16) holds row c, K indices 4g .. 4g + 3;
+// one 16-byte word per lane as bf16 pairs (1 KiB), or two 16-byte halves per lane as fp32
+// (half 0 of every lane, then half 1: 2 KiB).  Channel blocks kb = 0 .. nkb - 1, nkb =
+// ceil(m / 16):
+//   -W  [nkb]  rows tokens,   K channels of kb         Z  [nkb]  the same
+//   K Q [nkb]  rows channels of kb, K tokens            (R Q) D_beta [nkb]  (decoupled)
+//   X, Y       rows tokens, K tokens
+//   |D| [64] fp32; e^{i phi} of the step's whole phase [64] complex fp32 (block 3's is used)
+// Phases are relative to the step's first token; the scans rotate the state by the step's
+// phase after its last block.  Decay magnitudes are relative to the block, as in the bf16
+// kernel, and a block whose decay falls below 2^-126 has NaN operands.
+#pragma once
+
+#include "sfda_device.h"
+#include "sfda_launch.h"
+
+namespace sfda {
+namespace fac {
+
+constexpr int CP = 64;               // tokens per step (one workgroup of the preparing kernel)
+constexpr int NB = CP / 16;          // blocks per step
+
+// bytes of one block's record and of its parts
+struct RecLayout {
+    int nkb, frag, z, kq, rq, x, y, dm, rot, block;
+    __host__ __device__ RecLayout(int m, bool bf16, bool dec) {
+        nkb = (m + 15) / 16;
+        frag = bf16 ? 1024 : 2048;
+        z = nkb * frag;
+        kq = 2 * z;
+        rq = 3 * z;
+        x = (dec ? 4 : 3) * z;
+        y = x + frag;
+        dm = y + frag;
+        rot = dm + 256;
+        block = rot + 512;
+    }
+};
+
+}  // namespace fac
+}  // namespace sfda

@@ -1,0 +1,1153 @@
+// The factored chunk evaluation (sfda_factored.h has the relations and the operand records):
+// the preparing kernel and the scans.
+#include <type_traits>
+
+#include "sfda_chunk_common.h"
+#include "sfda_factored.h"
+
+namespace sfda {
+namespace fac {
+
+typedef uint32_t u32;
+typedef u32 u32x2 __attribute__((ext_vector_type(2)));
+typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// LDS written and read by one wave: its LDS instructions run in order, so only the compiler has
+// to keep the order
+__device__ __forceinline__ void wave_order() { asm volatile("" ::: "memory"); }
+
+// two floats -> (lo, hi) bf16 pair, round to nearest even
+__device__ __forceinline__ u32 pack_bf16(float lo, float hi) {
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(u32, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ float bf_lo(u32 w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf_hi(u32 w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+// wave-uniform size kept in a scalar register (a size in a vector register turns every access
+// into a loop over the wave's descriptors)
+__device__ __forceinline__ rsrc_t rsrc(const void* base, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, __builtin_amdgcn_readfirstlane(bytes),
+                                             0x00020000);
+}
+__device__ __forceinline__ u32x4 ld128(rsrc_t r, u32 off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
+
+// ------------------------------------------------------------------ complex matrix operands
+// A complex 16 x 16 result is two accumulator tiles (real and imaginary part; lane (c, g) holds
+// rows 4g + r of column c).  A fragment holds 4 consecutive K entries of one row (left operand)
+// or of one column (right operand) as (re, im) pairs; a right operand enters one product per
+// output part, as (Re, -Im) and as (Im, Re).
+struct CAcc { f32x4 re, im; };
+__device__ __forceinline__ void czero(CAcc& z) { z.re = zero4(); z.im = zero4(); }
+
+template <int P> struct Frag;
+template <> struct Frag<PREC_BF16> { u32x4 w; };
+template <> struct Frag<PREC_F32> { float2 x[4]; };
+template <int P> struct Right;
+template <> struct Right<PREC_BF16> { u32x4 re, im; };
+template <> struct Right<PREC_F32> { float re[4], im[4], nim[4]; };
+
+template <int P> __device__ __forceinline__ Frag<P> frag4(const float2 (&x)[4]) {
+    Frag<P> f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (P == PREC_BF16) f.w[r] = pack_bf16(x[r].x, x[r].y);
+        else f.x[r] = x[r];
+    }
+    return f;
+}
+// s = -1 negates
+template <int P> __device__ __forceinline__ Frag<P> frag_acc(const CAcc& z, float s = 1.f) {
+    float2 x[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = make_float2(s * z.re[r], s * z.im[r]);
+    return frag4<P>(x);
+}
+template <int P> __device__ __forceinline__ float2 frag_get(const Frag<P>& f, int r) {
+    if constexpr (P == PREC_BF16) return make_float2(bf_lo(f.w[r]), bf_hi(f.w[r]));
+    else return f.x[r];
+}
+template <int P> __device__ __forceinline__ Right<P> right(const Frag<P>& f) {
+    Right<P> b;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (P == PREC_BF16) {
+            b.re[r] = f.w[r] ^ 0x80000000u;
+            b.im[r] = __builtin_amdgcn_alignbit(f.w[r], f.w[r], 16);
+        } else {
+            b.re[r] = f.x[r].x;
+            b.im[r] = f.x[r].y;
+            b.nim[r] = -f.x[r].y;
+        }
+    }
+    return b;
+}
+// right operand from a split accumulator
+template <int P> __device__ __forceinline__ Right<P> right_acc(const CAcc& y) {
+    Right<P> b;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (P == PREC_BF16) {
+            b.re[r] = pack_bf16(y.re[r], -y.im[r]);
+            b.im[r] = pack_bf16(y.im[r], y.re[r]);
+        } else {
+            b.re[r] = y.re[r];
+            b.im[r] = y.im[r];
+            b.nim[r] = -y.im[r];
+        }
+    }
+    return b;
+}
+// z += X Y over 16 complex K indices
+template <int P> __device__ __forceinline__ void cmma(CAcc& z, const Frag<P>& a, const Right<P>& b) {
+    if constexpr (P == PREC_BF16) {
+        z.re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.w), __builtin_bit_cast(bf16x8, b.re), z.re, 0, 0, 0);
+        z.im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.w), __builtin_bit_cast(bf16x8, b.im), z.im, 0, 0, 0);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            z.re = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[r].x, b.re[r], z.re, 0, 0, 0);
+            z.im = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[r].x, b.im[r], z.im, 0, 0, 0);
+            z.re = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[r].y, b.nim[r], z.re, 0, 0, 0);
+            z.im = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[r].y, b.re[r], z.im, 0, 0, 0);
+        }
+    }
+}
+
+// ------------------------------------------------------------------ preparing kernel
+// One wave per 16-token block: everything after the phase totals stays inside the wave, so the
+// workgroup meets one barrier.  LDS per wave is two 16 x 64 operand areas that the operands pass
+// through one after another (held together they would leave one workgroup per compute unit):
+// their rows are padded by 16 bytes, so a row fragment (16 rows x one 16-byte chunk) and a
+// column fragment (4 rows x 16 consecutive entries) both read distinct banks.
+struct PrepArgs {
+    const void *q, *k, *alpha, *theta, *beta, *r, *wbeta;
+    char* fac;
+    int T, m, step0, nsteps;             // steps of this piece
+    RecLayout lay;
+};
+
+template <int P> struct Op {             // operand areas of one wave
+    static constexpr int ES = P == PREC_BF16 ? 4 : 8;
+    static constexpr int PITCH = MP * ES + 16;
+    static constexpr int AREA = 16 * PITCH;
+};
+
+template <int P> __device__ __forceinline__ Frag<P> lds_row(const char* a, int row, int kb, int g) {
+    Frag<P> f;
+    const char* p = a + row * Op<P>::PITCH + (kb * 16 + 4 * g) * Op<P>::ES;
+    if constexpr (P == PREC_BF16) {
+        f.w = *reinterpret_cast<const u32x4*>(p);
+    } else {
+        const float4 lo = *reinterpret_cast<const float4*>(p), hi = *reinterpret_cast<const float4*>(p + 16);
+        f.x[0] = make_float2(lo.x, lo.y); f.x[1] = make_float2(lo.z, lo.w);
+        f.x[2] = make_float2(hi.x, hi.y); f.x[3] = make_float2(hi.z, hi.w);
+    }
+    return f;
+}
+template <int P> __device__ __forceinline__ Frag<P> lds_col(const char* a, int col, int g) {
+    Frag<P> f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const char* p = a + (4 * g + r) * Op<P>::PITCH + col * Op<P>::ES;
+        if constexpr (P == PREC_BF16) f.w[r] = *reinterpret_cast<const u32*>(p);
+        else f.x[r] = *reinterpret_cast<const float2*>(p);
+    }
+    return f;
+}
+// 4 consecutive entries, at lane word `at` (in entries) of a row-padded area or of a fragment
+template <int P> __device__ __forceinline__ void put4(char* p, const float2 (&x)[4]) {
+    if constexpr (P == PREC_BF16) {
+        u32x4 w;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = pack_bf16(x[r].x, x[r].y);
+        *reinterpret_cast<u32x4*>(p) = w;
+    } else {
+        *reinterpret_cast<float4*>(p) = make_float4(x[0].x, x[0].y, x[1].x, x[1].y);
+        *reinterpret_cast<float4*>(p + 16) = make_float4(x[2].x, x[2].y, x[3].x, x[3].y);
+    }
+}
+// a lane's entries of a fragment in the records' order
+template <int P> __device__ __forceinline__ void put_frag(char* f, int lane, const Frag<P>& x) {
+    if constexpr (P == PREC_BF16) {
+        *reinterpret_cast<u32x4*>(f + lane * 16) = x.w;
+    } else {
+        *reinterpret_cast<float4*>(f + lane * 16) = make_float4(x.x[0].x, x.x[0].y, x.x[1].x, x.x[1].y);
+        *reinterpret_cast<float4*>(f + 1024 + lane * 16) = make_float4(x.x[2].x, x.x[2].y, x.x[3].x, x.x[3].y);
+    }
+}
+
+template <typename TIN, bool WIDE>
+__device__ __forceinline__ void load4r(rsrc_t rs, u32 e, int left, float (&x)[4])
+{
+    if constexpr (WIDE && sizeof(TIN) == 2) {
+        const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, left > 0 ? e * 2 : OOR, 0, 0);
+        x[0] = bf_lo(w.x); x[1] = bf_hi(w.x); x[2] = bf_lo(w.y); x[3] = bf_hi(w.y);
+    } else if constexpr (WIDE) {
+        const u32x4 w = ld128(rs, left > 0 ? e * 4 : OOR);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = __uint_as_float(w[k]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = ld_real<TIN>(rs, k < left ? (e + k) * static_cast<u32>(sizeof(TIN)) : OOR);
+    }
+}
+template <typename TIN, bool WIDE>
+__device__ __forceinline__ void load4c(rsrc_t rs, u32 e, int left, float2 (&x)[4])
+{
+    if constexpr (WIDE && sizeof(TIN) == 2) {
+        const u32x4 w = ld128(rs, left > 0 ? e * 4 : OOR);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = make_float2(bf_lo(w[k]), bf_hi(w[k]));
+    } else if constexpr (WIDE) {
+        const u32x4 a = ld128(rs, left > 0 ? e * 8 : OOR), b = ld128(rs, left > 0 ? e * 8 + 16 : OOR);
+        x[0] = make_float2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        x[1] = make_float2(__uint_as_float(a[2]), __uint_as_float(a[3]));
+        x[2] = make_float2(__uint_as_float(b[0]), __uint_as_float(b[1]));
+        x[3] = make_float2(__uint_as_float(b[2]), __uint_as_float(b[3]));
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = ld_cplx<TIN>(rs, k < left ? (e + k) * 2 * static_cast<u32>(sizeof(TIN)) : OOR);
+    }
+}
+
+template <int S, typename X> __device__ __forceinline__ X quad_lane(X x) {   // DPP quad permutation
+    return __builtin_bit_cast(X, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), S, 0xF, 0xF, false));
+}
+
+template <int P> struct PrepSmem {
+    struct Wave { char r0[Op<P>::AREA], r1[Op<P>::AREA]; float beta[16], wb[16]; };
+    Wave w[NB];
+    u32 tph[NB][MP];                     // theta / 2 pi summed over each block, in 2^-32 revolutions
+    static_assert(Op<P>::AREA >= 16 * 18 * 8, "the inverse's scratch fits an operand area");
+};
+
+template <int P, typename TIN, bool DEC>
+__device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigned wg)
+{
+    constexpr int ES = Op<P>::ES, PITCH = Op<P>::PITCH;
+    auto& sw = sm.w;
+    auto& tph = sm.tph;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int pw = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const long bh = wg / static_cast<unsigned>(A.nsteps);
+    const int st = static_cast<int>(wg - bh * A.nsteps);
+    const int T = A.T, m = A.m;
+    const int t0 = (A.step0 + st) * CP + pw * 16;      // the block's first token
+    const int tsg = lane & 3, cg = lane >> 2;          // tokens 4 tsg .. + 3, channels 4 cg .. + 3
+    const int pc0 = cg * 4;
+    auto& w = sw[pw];
+#ifdef SFDA_LDS_POISON
+    lds_poison(&sm, sizeof(sm), tid, 256);
+    __syncthreads();
+#endif
+
+    // ---- loads: every one in flight together; past T or past m they read as zero
+    float av[4][4], th[4][4];
+    float2 kq[4][4], qq[4][4], rq[4][4];
+    {
+        const int rows = min(max(T - t0, 0), 16);
+        const long e0 = (bh * T + t0) * static_cast<long>(m);
+        const int rb = rows * m * static_cast<int>(sizeof(TIN));
+        const TIN *gq = static_cast<const TIN*>(A.q), *gk = static_cast<const TIN*>(A.k);
+        const TIN *ga = static_cast<const TIN*>(A.alpha), *gt = static_cast<const TIN*>(A.theta);
+        const rsrc_t ra = rsrc(ga + e0, rb), rt = rsrc(gt + e0, rb);
+        const rsrc_t rqq = rsrc(gq + 2 * e0, 2 * rb), rk = rsrc(gk + 2 * e0, 2 * rb);
+        const rsrc_t rr = DEC ? rsrc(static_cast<const TIN*>(A.r) + 2 * e0, 2 * rb) : rk;
+        auto load = [&](auto wide_c) __attribute__((always_inline)) {
+            constexpr bool W = decltype(wide_c)::value;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const u32 e = static_cast<u32>((tsg * 4 + u) * m + pc0);
+                load4r<TIN, W>(ra, e, m - pc0, av[u]);
+                load4r<TIN, W>(rt, e, m - pc0, th[u]);
+                load4c<TIN, W>(rk, e, m - pc0, kq[u]);
+                load4c<TIN, W>(rqq, e, m - pc0, qq[u]);
+                if constexpr (DEC) load4c<TIN, W>(rr, e, m - pc0, rq[u]);
+            }
+        };
+        if ((m & 3) == 0) load(std::true_type{});
+        else load(std::false_type{});
+        if (lane < 16) {
+            const rsrc_t rbt = rsrc(static_cast<const TIN*>(A.beta) + bh * T + t0, rows * static_cast<int>(sizeof(TIN)));
+            w.beta[lane] = ld_real<TIN>(rbt, lane * static_cast<u32>(sizeof(TIN)));
+            if constexpr (DEC) {
+                const rsrc_t rw = rsrc(static_cast<const TIN*>(A.wbeta) + bh * T + t0, rows * static_cast<int>(sizeof(TIN)));
+                w.wb[lane] = ld_real<TIN>(rw, lane * static_cast<u32>(sizeof(TIN)));
+            }
+        }
+    }
+
+    // ---- scans of the block per channel: prefix products P, suffix products Q, phase sums.
+    // Phases are kept in units of 2^-32 revolutions: the sums are exact and wrap by themselves
+    // (summed as fp32 revolutions they put float32 results at 9.6e-7 instead of 6e-7 of the
+    // 64-bit ones)
+    float Pf[4][4], Qb[4][4], dtot[4], invd[4];              // [token u][channel k]
+    u32 ph[4][4];
+    {
+        const bool s0 = tsg == 0, s01 = tsg < 2, s3 = tsg == 3, s23 = tsg >= 2;
+        u32 tpk[4];
+        bool low = false;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float a[4], finite = 0.f;                     // finite: NaN once a theta is not
+            u32 lp[4], rp = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool ok = t0 + tsg * 4 + u < T && pc0 + k < m;
+                a[u] = ok ? av[u][k] : 1.f;               // the identity token's alpha
+                finite = __builtin_fmaf(th[u][k], 0.f, finite);
+                rp += static_cast<u32>(__builtin_amdgcn_fractf(th[u][k] * 0.15915494309189535f) * 4294967296.f);
+                lp[u] = rp;
+            }
+            const float m0 = a[0], m1 = m0 * a[1], m2 = m1 * a[2], m3 = m2 * a[3];
+            const float x2 = a[3], x1 = a[2] * a[3], x0 = a[1] * x1;
+            float im = m3, is = m3;
+            u32 ip = rp;
+            float y = quad_lane<0x90>(im);                                 // [0, 0, 1, 2]
+            u32 yp = quad_lane<0x90>(ip);
+            im *= s0 ? 1.f : y;
+            ip += s0 ? 0u : yp;
+            y = quad_lane<0x40>(im); yp = quad_lane<0x40>(ip);             // [0, 0, 0, 1]
+            im *= s01 ? 1.f : y;
+            ip += s01 ? 0u : yp;
+            float ys = quad_lane<0xF9>(is);                                // [1, 2, 3, 3]
+            is *= s3 ? 1.f : ys;
+            ys = quad_lane<0xFE>(is);                                      // [2, 3, 3, 3]
+            is *= s23 ? 1.f : ys;
+            const float pm = quad_lane<0x90>(im), ps = quad_lane<0xF9>(is), D = quad_lane<0xFF>(im);   // [3, 3, 3, 3]
+            const u32 pp = quad_lane<0x90>(ip);
+            const float em = s0 ? 1.f : pm, es = s3 ? 1.f : ps;
+            const u32 ep = s0 ? 0u : pp;
+            tpk[k] = quad_lane<0xFF>(ip);
+            Pf[0][k] = em * m0; Pf[1][k] = em * m1; Pf[2][k] = em * m2; Pf[3][k] = em * m3;
+            Qb[0][k] = es * x0; Qb[1][k] = es * x1; Qb[2][k] = es * x2; Qb[3][k] = es;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) ph[u][k] = ep + lp[u];
+            dtot[k] = D;
+            low = low || !(D >= 1.17549435e-38f) || finite != finite;      // below the normal range (or NaN)
+        }
+        const bool bad = __builtin_amdgcn_ballot_w64(low) != 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (bad) dtot[k] = __builtin_nanf("");
+            invd[k] = 1.f / dtot[k];
+        }
+        if (s0) *reinterpret_cast<u32x4*>(&tph[pw][pc0]) = u32x4{tpk[0], tpk[1], tpk[2], tpk[3]};
+    }
+    __syncthreads();
+    char* const rec = A.fac + ((bh * A.nsteps + st) * static_cast<long>(NB) + pw) * A.lay.block;
+    const int nkb = A.lay.nkb;
+    constexpr float REV = 1.f / 4294967296.f;
+    u32 off[4] = {0, 0, 0, 0};
+    {
+        u32 tot[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const u32x4 t = *reinterpret_cast<const u32x4*>(&tph[b][pc0]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (b < pw) off[k] += t[k];
+                tot[k] += t[k];
+            }
+        }
+        if (tsg == 0) {
+            float2 z[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float p = static_cast<float>(tot[k]) * REV;
+                z[k] = make_float2(__builtin_amdgcn_cosf(p), __builtin_amdgcn_sinf(p));
+            }
+            *reinterpret_cast<float4*>(rec + A.lay.dm + pc0 * 4) = make_float4(dtot[0], dtot[1], dtot[2], dtot[3]);
+            put4<PREC_F32>(rec + A.lay.rot + pc0 * 8, z);
+        }
+    }
+    // conj(q) e^{i phi}, conj(k) e^{i phi} (and conj(r) e^{i phi}); x e^{-i phi} is the conjugate
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float Ph = static_cast<float>(off[k] + ph[u][k]) * REV;
+            const float sn = __builtin_amdgcn_sinf(Ph), cs = __builtin_amdgcn_cosf(Ph);
+            auto turn = [&](float2 x) { return make_float2(__builtin_fmaf(x.x, cs, x.y * sn), __builtin_fmaf(x.x, sn, -x.y * cs)); };
+            qq[u][k] = turn(qq[u][k]);
+            kq[u][k] = turn(kq[u][k]);
+            if constexpr (DEC) rq[u][k] = turn(rq[u][k]);
+        }
+
+    // ---- K Q (and R Q D_beta) to the record, through the wave's area so that the stores are
+    // whole lines
+    auto out_cols = [&](const float2 (&x)[4][4], int at, const float* wt) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float2 y[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float s = Qb[u][k];
+                if constexpr (DEC) if (wt) s *= wt[tsg * 4 + u];
+                y[u] = make_float2(x[u][k].x * s, -x[u][k].y * s);
+            }
+            const int l2 = (cg & 3) * 4 + k + 16 * tsg;       // the fragment's lane
+            put_frag<P>(w.r1 + (cg >> 2) * A.lay.frag, l2, frag4<P>(y));
+        }
+        wave_order();
+        for (int i = 0; i < nkb * A.lay.frag; i += 1024)
+            *reinterpret_cast<u32x4*>(rec + at + i + lane * 16) = *reinterpret_cast<const u32x4*>(w.r1 + i + lane * 16);
+        wave_order();
+    };
+    out_cols(kq, A.lay.kq, nullptr);
+    if constexpr (DEC) out_cols(rq, A.lay.rq, w.wb);
+
+    // ---- row operands: conj(Q) G, conj(K) G (kept in area 0), K / G
+    auto out_rows = [&](char* area, const float2 (&x)[4][4], auto scale, float sy) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            float2 y[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float s = scale(u, k);
+                y[k] = make_float2(x[u][k].x * s, sy * x[u][k].y * s);
+            }
+            put4<P>(area + (tsg * 4 + u) * PITCH + pc0 * ES, y);
+        }
+        wave_order();
+    };
+    Frag<P> qf[4], kf[4];
+    out_rows(w.r1, qq, [&](int u, int k) { return Pf[u][k]; }, 1.f);
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) qf[kb] = lds_row<P>(w.r1, c, kb, g);
+    wave_order();
+    out_rows(w.r0, kq, [&](int u, int k) { return Pf[u][k]; }, 1.f);
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) kf[kb] = lds_row<P>(w.r0, c, kb, g);
+    out_rows(w.r1, kq, [&](int u, int k) { return Qb[u][k] * invd[k]; }, -1.f);
+
+    // ---- Grams: L (rows t, columns j) and A^T (rows j, columns t), so that A comes out as the
+    // right operand it is used as
+    CAcc zl, za, zlr, zar;
+    czero(zl); czero(za); czero(zlr); czero(zar);
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+        if (kb >= nkb) break;
+        const Frag<P> d = lds_row<P>(w.r1, c, kb, g);
+        cmma<P>(zl, kf[kb], right<P>(d));
+        cmma<P>(za, d, right<P>(qf[kb]));
+    }
+    wave_order();
+    if constexpr (DEC) {
+        out_rows(w.r1, rq, [&](int u, int k) { return Qb[u][k] * invd[k]; }, -1.f);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            if (kb >= nkb) break;
+            const Frag<P> d = lds_row<P>(w.r1, c, kb, g);
+            cmma<P>(zlr, kf[kb], right<P>(d));
+            cmma<P>(zar, d, right<P>(qf[kb]));
+        }
+        wave_order();
+    }
+
+    // ---- T = (I + D_beta L)^{-1} D_beta, row c on the lanes (c, .)
+    float2* const xs = reinterpret_cast<float2*>(w.r1);     // [16][18]
+    {
+        const float4 bt = *reinterpret_cast<const float4*>(&w.beta[4 * g]);
+        const float btr[4] = {bt.x, bt.y, bt.z, bt.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool lo = c < 4 * g + r;
+            xs[(4 * g + r) * 18 + c] = make_float2(lo ? -btr[r] * zl.re[r] : 0.f, lo ? -btr[r] * zl.im[r] : 0.f);
+        }
+        wave_order();
+        float2 xrow[16];
+#pragma unroll
+        for (int s2 = 0; s2 < 16; s2 += 2) {
+            const float4 x2 = *reinterpret_cast<const float4*>(&xs[c * 18 + s2]);
+            xrow[s2] = make_float2(x2.x, x2.y);
+            xrow[s2 + 1] = make_float2(x2.z, x2.w);
+        }
+        float nr[4], ni[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { nr[k] = c == 4 * k + g ? 1.f : 0.f; ni[k] = 0.f; }
+        subst_steps(nr, ni, xrow, std::make_integer_sequence<int, 15>{});
+        wave_order();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float b = w.beta[4 * k + g];
+            xs[c * 18 + 4 * k + g] = make_float2(nr[k] * b, ni[k] * b);
+        }
+        wave_order();
+    }
+    Frag<P> tf, af;                    // T[c][4g + r]; A[c][4g + r]
+    {
+        float2 x[4], y[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            x[r] = xs[c * 18 + 4 * g + r];
+            const bool keep = 4 * g + r <= c;
+            y[r] = make_float2(keep ? za.re[r] : 0.f, keep ? za.im[r] : 0.f);
+        }
+        tf = frag4<P>(x);
+        af = frag4<P>(y);
+    }
+    const Right<P> tr = right<P>(tf), ar = right<P>(af);
+
+    // ---- X and Y
+    {
+        CAcc y;
+        if constexpr (!DEC) {
+            float2 x[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = xs[(4 * g + r) * 18 + c];        // T^T, row c
+            put_frag<P>(rec + A.lay.x, lane, tf);
+            czero(y);
+            cmma<P>(y, frag4<P>(x), ar);                                        // Y^T = T^T A^T
+        } else {
+            float2 x[4];
+            const float bj = w.wb[c];
+            const float4 b4 = *reinterpret_cast<const float4*>(&w.wb[4 * g]);
+            const float br[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool lo = c < 4 * g + r, keep = 4 * g + r <= c;
+                x[r] = make_float2(lo ? zlr.re[r] * bj : 0.f, lo ? zlr.im[r] * bj : 0.f);   // (L_r D_beta)[4g + r][c]
+                y.re[r] = keep ? zar.re[r] * br[r] : 0.f;                       // (A_r D_beta)^T
+                y.im[r] = keep ? zar.im[r] * br[r] : 0.f;
+            }
+            const Frag<P> lb = frag4<P>(x);
+            CAcc xa, xt;
+            czero(xa); czero(xt);
+            cmma<P>(xa, tf, right<P>(lb));                                      // T L_r D_beta
+            cmma<P>(xt, lb, tr);                                                // its transpose
+            put_frag<P>(rec + A.lay.x, lane, frag_acc<P>(xt, -1.f));
+            cmma<P>(y, frag_acc<P>(xa, -1.f), ar);                              // + X^T A^T
+        }
+        put_frag<P>(rec + A.lay.y, lane, frag_acc<P>(y));
+    }
+
+    // ---- -W and Z, channel block by channel block
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+        if (kb >= nkb) break;
+        const Frag<P> kt = lds_col<P>(w.r0, kb * 16 + c, g);                    // (conj(K) G)[4g + r][kb * 16 + c]
+        CAcc a, b, z;
+        czero(a); czero(b);
+        cmma<P>(a, tf, right<P>(kt));                                           // W (rows tokens)
+        cmma<P>(b, kt, tr);                                                     // W^T
+        put_frag<P>(rec + kb * A.lay.frag, lane, frag_acc<P>(b, -1.f));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float2 x = frag_get<P>(qf[kb], r);
+            z.re[r] = x.x;
+            z.im[r] = x.y;
+        }
+        cmma<P>(z, frag_acc<P>(a, -1.f), ar);                                   // Z^T = (conj(Q) G)^T - W^T A^T
+        put_frag<P>(rec + A.lay.z + kb * A.lay.frag, lane, frag_acc<P>(z));
+    }
+}
+
+template <int P, typename TIN, bool DEC>
+__global__ __launch_bounds__(256, 2) void prep_kernel(PrepArgs A)
+{
+    __shared__ __align__(16) PrepSmem<P> sm;
+    prep<P, TIN, DEC>(sm, A, blockIdx.x);
+}
+
+// ------------------------------------------------------------------ forward scans
+struct ScanArgs {
+    const char* fac;
+    const void* v;
+    void* o;
+    const float* Sin;      // entering state (may be null: zero); Sout may be the same buffer
+    float* Sout;           // may be null
+    long heads;
+    int T, m, n, n_slices;
+    int step0, nsteps;
+    RecLayout lay;
+};
+
+// Workgroup w of a scan: the slices of a head read the same records, so they go to one XCD (the
+// dispatcher hands workgroups to the 8 XCDs round-robin by index): indices 8 S j + 8 s + x for
+// head 8 j + x, the grid padded to whole groups of 8 heads.  Below 8 heads the plain order
+// spreads the slices over the XCDs.
+__device__ __forceinline__ bool scan_place(unsigned w, int S, long heads, long& bh, int& sl) {
+    if (heads >= 8) {
+        const unsigned x = w & 7u, q = w >> 3, j = q / static_cast<unsigned>(S);
+        sl = static_cast<int>(q - j * static_cast<unsigned>(S));
+        bh = 8L * j + x;
+    } else {
+        bh = w / static_cast<unsigned>(S);
+        sl = static_cast<int>(w - bh * S);
+    }
+    return bh < heads;
+}
+static long scan_grid(long heads, int S) { return (heads >= 8 ? (heads + 7) / 8 * 8 : heads) * S; }
+
+template <typename TOUT> __device__ __forceinline__ void st_real(rsrc_t r, u32 off, int s, float x) {
+    if constexpr (sizeof(TOUT) == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, off, s, 0);
+    else __builtin_amdgcn_raw_buffer_store_b16(static_cast<uint16_t>(pack_bf16(x, 0.f)), r, off, s, 0);
+}
+template <typename TV> __device__ __forceinline__ float2 ld_cplx(rsrc_t r, u32 off, int s) {
+    if constexpr (sizeof(TV) == 4) {
+        return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, s, 0));
+    } else {
+        const u32 w = __builtin_amdgcn_raw_buffer_load_b32(r, off, s, 0);
+        return make_float2(bf_lo(w), bf_hi(w));
+    }
+}
+
+// What the scans share: the piece's tokens, and one step's resources.  A block's offset in them is
+// scalar, and a step past the end is an empty range (loads read zero, stores drop).  Every step
+// has four blocks: those past the end of the sequence hold identity tokens (no change of the
+// state, no output), so the scans have no ragged tail.
+struct Span {
+    int tb, te, nsteps;
+    long base_tn, base_mn;
+    const char* fac;
+    __device__ __forceinline__ Span(const ScanArgs& A, long bh) {
+        tb = A.step0 * CP;
+        te = min(A.T, tb + A.nsteps * CP);
+        nsteps = (te - tb + CP - 1) / CP;
+        base_tn = (bh * A.T + tb) * static_cast<long>(A.n);
+        base_mn = bh * static_cast<long>(A.m) * A.n;
+        fac = A.fac + bh * A.nsteps * static_cast<long>(NB) * A.lay.block;
+    }
+    __device__ __forceinline__ int bytes(const ScanArgs& A, int st) const { return st < nsteps ? NB * A.lay.block : 0; }
+    __device__ __forceinline__ int rows(int st) const { return max(min(te - tb - st * CP, CP), 0); }
+    __device__ __forceinline__ const char* rec(const ScanArgs& A, int st) const { return fac + static_cast<long>(st) * (NB * A.lay.block); }
+    __device__ __forceinline__ long elem(const ScanArgs& A, int st) const { return 2 * (base_tn + static_cast<long>(st) * CP * A.n); }
+};
+__device__ __forceinline__ f32x4 ldv4(rsrc_t r, u32 off, int s) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, s, 0));
+}
+__device__ __forceinline__ float2 ldv2(rsrc_t r, u32 off, int s) {
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, s, 0));
+}
+// keeps the loads before it in this order for every block, so that the wait counts stay exact
+#define LOAD_ORDER() __builtin_amdgcn_sched_barrier(0)
+
+// fp32 operands.  Workgroup: 8 value columns on four waves; wave w holds channel block w of them
+// (16 x 8 complex, interleaved columns: lane (c, g) part c & 1 of column c / 2), so a block's
+// chain is 10 matrix instructions for its share of Delta, one exchange of the shares through LDS,
+// and 8 for the update -- with the state on one wave it would be four times that, and with 16
+// columns per workgroup half as many compute units would work.  The products of the output wait
+// behind the exchange (they fill its 330 cycles); their shares are summed after the next block's
+// barrier.  An fp32 matrix instruction takes 32 cycles and the SIMD issues no vector instruction
+// beside it, so the chain is the sum of the two, about 1400 of the 2060 cycles a block takes;
+// separate waves for the outputs changed nothing (113 us against 111 us for B4 H8 T2048).  Each
+// wave reads only its own channel block of the records, four blocks ahead, straight into
+// registers; waves past the channels read an empty range, so their state stays zero without a
+// branch.
+constexpr int FCOLS = 8;
+struct ScanF32Smem { f32x4 red[2][2][4][64]; };        // [parity][Delta, O][wave][lane]
+template <typename TV, typename TOUT, bool DEC>
+__device__ __forceinline__ void scan_f32(ScanF32Smem& sm, const ScanArgs& A, unsigned wg)
+{
+    auto& red = sm.red;
+    long bh;
+    int sl;
+    if (!scan_place(wg, A.n_slices, A.heads, bh, sl)) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, g = lane >> 4, qp = lane & 1;
+    const int n = A.n, m = A.m;
+    const int j = sl * FCOLS + (c >> 1);
+    const bool live = wave < A.lay.nkb;                // this wave's channels exist
+    const Span sp(A, bh);
+    const TV* const gv = static_cast<const TV*>(A.v);
+    TOUT* const go = static_cast<TOUT*>(A.o);
+
+    f32x4 S;
+    {
+        const rsrc_t rs = rsrc(A.Sin ? A.Sin + 2 * sp.base_mn : A.Sin, A.Sin && live ? m * n * 8 : 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = wave * 16 + 4 * g + r;
+            S[r] = ld_f32(rs, j < n ? static_cast<u32>(((i * n + j) * 2 + qp) * 4) : OOR);
+        }
+    }
+
+    struct Pre { f32x4 w0, w1, z0, z1, k0, k1, r0, r1, d; float2 x, y, v, u0, u1, u2, u3; };
+    Pre pre[NB];
+    const int so = wave * A.lay.frag;
+    const u32 l16 = lane * 16;
+    const u32 lx = (wave >> 1) * 1024 + lane * 16 + (wave & 1) * 8;           // K index 4g + wave of X, Y
+    const int row_v = n * 2 * static_cast<int>(sizeof(TV)), row_o = n * 2 * static_cast<int>(sizeof(TOUT));
+    auto voff = [&](int r) { return j < n ? static_cast<u32>((4 * g + r) * n + j) * 2 * static_cast<u32>(sizeof(TV)) : OOR; };
+    const u32 lv = voff(wave);
+    struct Step { rsrc_t own, all, v, o; };
+    auto step_of = [&](int st) __attribute__((always_inline)) {
+        const int bytes = sp.bytes(A, st), rows = sp.rows(st);
+        const char* rec = sp.rec(A, st);
+        const long e = sp.elem(A, st);
+        return Step{rsrc(rec, live ? bytes : 0), rsrc(rec, bytes), rsrc(gv + e, rows * row_v), rsrc(go + e, go ? rows * row_o : 0)};
+    };
+    // a block's operands in three parts, each requested again as soon as its products have
+    // issued: eleven loads in a row hold up the wave behind the load unit (120 us against 111)
+    auto fetch_w = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+        const int at = b * A.lay.block;
+        p.w0 = ldv4(q.own, l16, at + so);
+        p.w1 = ldv4(q.own, l16 + 1024, at + so);
+        p.x = ldv2(q.all, lx, at + A.lay.x);
+        LOAD_ORDER();
+    };
+    auto fetch_z = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+        const int at = b * A.lay.block;
+        p.z0 = ldv4(q.own, l16, at + so + A.lay.z);
+        p.z1 = ldv4(q.own, l16 + 1024, at + so + A.lay.z);
+        p.y = ldv2(q.all, lx, at + A.lay.y);
+        LOAD_ORDER();
+    };
+    auto fetch_k = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+        const int at = b * A.lay.block;
+        p.k0 = ldv4(q.own, l16, at + so + A.lay.kq);
+        p.k1 = ldv4(q.own, l16 + 1024, at + so + A.lay.kq);
+        p.d = ldv4(q.own, g * 16, at + A.lay.dm + wave * 64);
+        if constexpr (DEC) {
+            p.r0 = ldv4(q.own, l16, at + so + A.lay.rq);
+            p.r1 = ldv4(q.own, l16 + 1024, at + so + A.lay.rq);
+            p.u0 = ld_cplx<TV>(q.v, voff(0), b * 16 * row_v);
+            p.u1 = ld_cplx<TV>(q.v, voff(1), b * 16 * row_v);
+            p.u2 = ld_cplx<TV>(q.v, voff(2), b * 16 * row_v);
+            p.u3 = ld_cplx<TV>(q.v, voff(3), b * 16 * row_v);
+        }
+        p.v = ld_cplx<TV>(q.v, lv, b * 16 * row_v);
+        LOAD_ORDER();
+    };
+    auto mma1 = [&](f32x4& acc, float a, float b) __attribute__((always_inline)) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+    };
+    auto mma8 = [&](f32x4& acc, f32x4 a, f32x4 b, const Frag8& y) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) mma1(acc, s < 4 ? a[s & 3] : b[s & 3], y.v[s]);
+    };
+    const u32 eo = j < n ? static_cast<u32>(((4 * g + wave) * n + j) * 2 + qp) * static_cast<u32>(sizeof(TOUT)) : OOR;
+    // o of block b of a step, whose shares lie in red[b & 1][1]: wave w sums and stores the rows
+    // 4g + w
+    auto store_o = [&](rsrc_t ro, int b) __attribute__((always_inline)) {
+        float o = 0.f;
+#pragma unroll
+        for (int w2 = 0; w2 < 4; ++w2) o += reinterpret_cast<const float*>(&red[b & 1][1][w2][lane])[wave];
+        st_real<TOUT>(ro, eo, b * 16 * row_o, qp ? -o : o);
+    };
+    // block b of a step; prev, next: the resources that hold the block before it and the one four
+    // further
+    auto block = [&](int b, Pre& p, const Step& prev, const Step& next) __attribute__((always_inline)) {
+        const Frag8 sb = bfrag_from_acc(S, qp);
+        f32x4 pw = zero4(), pz = zero4();
+        const float v0 = qp ? -p.v.y : p.v.x, v1 = qp ? p.v.x : p.v.y;       // conj(v) = (x, -y)
+        mma1(pw, p.x.x, v0);
+        mma1(pw, p.x.y, v1);
+        mma8(pw, p.w0, p.w1, sb);
+        fetch_w(next, b, p);
+        red[b & 1][0][wave][lane] = pw;
+        __syncthreads();
+        f32x4 d[4];
+#pragma unroll
+        for (int w2 = 0; w2 < 4; ++w2) d[w2] = red[b & 1][0][w2][lane];
+        mma1(pz, p.y.x, v0);
+        mma1(pz, p.y.y, v1);
+        mma8(pz, p.z0, p.z1, sb);
+        fetch_z(next, b, p);
+        store_o(prev.o, (b + NB - 1) % NB);
+        S *= p.d;
+        mma8(S, p.k0, p.k1, bfrag_from_acc((d[0] + d[1]) + (d[2] + d[3]), qp));
+        if constexpr (DEC) {
+            Frag8 vb;
+            bpair(vb, 0, p.u0.x, -p.u0.y, qp);
+            bpair(vb, 1, p.u1.x, -p.u1.y, qp);
+            bpair(vb, 2, p.u2.x, -p.u2.y, qp);
+            bpair(vb, 3, p.u3.x, -p.u3.y, qp);
+            mma8(S, p.r0, p.r1, vb);
+        }
+        red[b & 1][1][wave][lane] = pz;
+        fetch_k(next, b, p);
+    };
+    // back from the step's frame
+    auto turn = [&](f32x4 r0, f32x4 r1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float cs = r < 2 ? r0[2 * r] : r1[2 * r - 4], sn = r < 2 ? r0[2 * r + 1] : r1[2 * r - 3];
+            const float own = S[r], oth = partner(own);
+            S[r] = qp ? __builtin_fmaf(cs, own, sn * oth) : __builtin_fmaf(cs, own, -sn * oth);
+        }
+    };
+    Step cur = step_of(0), prev = cur;
+    prev.o = rsrc(go, 0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        fetch_w(cur, b, pre[b]);
+        fetch_z(cur, b, pre[b]);
+        fetch_k(cur, b, pre[b]);
+    }
+    for (int st = 0; st < sp.nsteps; ++st) {
+        const Step next = step_of(st + 1);
+        const f32x4 r0 = ldv4(cur.own, g * 32, A.lay.rot + wave * 128), r1 = ldv4(cur.own, g * 32 + 16, A.lay.rot + wave * 128);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) block(b, pre[b], b ? cur : prev, next);
+        turn(r0, r1);
+        prev = cur;
+        cur = next;
+    }
+    __syncthreads();
+    store_o(prev.o, NB - 1);
+    if (A.Sout != nullptr && live && j < n) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = wave * 16 + 4 * g + r;
+            if (i < m) A.Sout[2 * (sp.base_mn + static_cast<long>(i) * n + j) + qp] = S[r];
+        }
+    }
+}
+template <typename TV, typename TOUT, bool DEC>
+__global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs A)
+{
+    __shared__ ScanF32Smem sm;
+    scan_f32<TV, TOUT, DEC>(sm, A, blockIdx.x);
+}
+
+// The scan of one piece beside the preparation of the next, in one launch (the first nscan
+// workgroups scan).  For a scan that leaves half of the compute units or more idle: a few heads
+// over a long sequence.  The two roles' LDS together keeps one workgroup per compute unit, so that
+// a scan shares its matrix cores with nobody.
+template <typename TIN, typename TOUT>
+__global__ __launch_bounds__(256, 1) void scan_prep_f32_kernel(ScanArgs S, PrepArgs N, unsigned nscan)
+{
+    __shared__ __align__(16) struct { ScanF32Smem scan; PrepSmem<PREC_F32> prep; } sm;
+    if (blockIdx.x < nscan) scan_f32<TIN, TOUT, false>(sm.scan, S, blockIdx.x);
+    else prep<PREC_F32, TIN, false>(sm.prep, N, blockIdx.x - nscan);
+}
+
+// bf16 operands.  Workgroup: 32 value columns.  The state's chain and the outputs on different
+// waves, two on each SIMD: in one wave everything adds up -- matrix instructions (17 cycles),
+// vector instructions (6.5 each), the 330 cycles of an exchange through LDS -- while another
+// wave's vector instructions issue beside a bf16 matrix instruction (dec. forward B8 H16 T4096: scan
+// 244 us, 256-266 us with the outputs on the state's waves).  The state waves put the operand
+// words of the entering state, which they form anyway, into LDS before the block's one barrier;
+// an output wave takes every second block whole.  State wave (cw, h) holds 16 of them (cw) with
+// channel blocks 2h, 2h + 1: half the channels per wave halves a wave's instructions, at the price
+// of one exchange of the halves of Delta.  Output wave (cw, p) takes the blocks of parity p.
+// What a wave has no use for (channels past m; X on the second half, whose share of Delta has
+// none) it reads from an empty range, without a branch.
+constexpr int BCOLS = 32;
+template <typename TOUT, bool DEC>
+__global__ __launch_bounds__(512, 1) void scan_bf16_kernel(ScanArgs A)
+{
+    constexpr int P = PREC_BF16;
+    __shared__ f32x4 red[2][4][2][64];                 // [parity][state wave][re, im][lane]: shares of Delta
+    __shared__ u32x4 ent[2][2][4][2][64];              // [parity][cw][channel block][re, im words][lane]: entering state
+    long bh;
+    int sl;
+    if (!scan_place(blockIdx.x, A.n_slices, A.heads, bh, sl)) return;
+    const int lane = threadIdx.x & 63;
+    const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3;
+    const int c = lane & 15, g = lane >> 4, h = wave & 1, cw = wave >> 1;
+    const int n = A.n, m = A.m;
+    const int j = sl * BCOLS + cw * 16 + c;
+    const Span sp(A, bh);
+    const uint16_t* const gv = static_cast<const uint16_t*>(A.v);
+    TOUT* const go = static_cast<TOUT*>(A.o);
+    const u32 l16 = lane * 16;
+    const int row_v = n * 4, row_o = n * 2 * static_cast<int>(sizeof(TOUT));
+    u32 voff[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) voff[r] = j < n ? static_cast<u32>((4 * g + r) * n + j) * 4u : OOR;
+    auto ldf = [&](rsrc_t r, u32 off, int s) __attribute__((always_inline)) {
+        Frag<P> f;
+        f.w = __builtin_amdgcn_raw_buffer_load_b128(r, off, s, 0);
+        return f;
+    };
+    auto conj_v = [&](const u32 (&v)[4]) __attribute__((always_inline)) {
+        Frag<P> f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f.w[r] = v[r] ^ 0x80000000u;
+        return right<P>(f);
+    };
+
+    if (wave8 < 4) {
+        // ================================================ state waves
+        const bool live0 = 2 * h < A.lay.nkb, live1 = 2 * h + 1 < A.lay.nkb;
+        CAcc S[2];
+        {
+            const rsrc_t rs = rsrc(A.Sin ? A.Sin + 2 * sp.base_mn : A.Sin, A.Sin ? m * n * 8 : 0);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = (2 * h + kb) * 16 + 4 * g + r;
+                    const float2 x = ld_c64(rs, j < n && i < m ? static_cast<u32>(i * n + j) * 8u : OOR);
+                    S[kb].re[r] = x.x;
+                    S[kb].im[r] = x.y;
+                }
+        }
+        struct Pre { Frag<P> w[2], k[2], r[2], x; f32x4 d[2]; u32 v[4]; };
+        Pre pre[NB];
+        const int so = 2 * h * 1024;
+        struct Step { rsrc_t own[2], x, v; };
+        auto step_of = [&](int st) __attribute__((always_inline)) {
+            const int bytes = sp.bytes(A, st);
+            const char* rec = sp.rec(A, st);
+            return Step{{rsrc(rec, live0 ? bytes : 0), rsrc(rec, live1 ? bytes : 0)}, rsrc(rec, h ? 0 : bytes),
+                        rsrc(gv + sp.elem(A, st), sp.rows(st) * row_v)};
+        };
+        auto fetch_w = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+            const int at = b * A.lay.block;
+            p.x = ldf(q.x, l16, at + A.lay.x);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) p.w[kb] = ldf(q.own[kb], l16 + kb * 1024, at + so);
+            LOAD_ORDER();
+        };
+        auto fetch_k = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+            const int at = b * A.lay.block;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p.v[r] = __builtin_amdgcn_raw_buffer_load_b32(q.v, voff[r], b * 16 * row_v, 0);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                p.d[kb] = ldv4(q.own[kb], g * 16 + kb * 64, at + A.lay.dm + h * 128);
+                if constexpr (DEC) p.r[kb] = ldf(q.own[kb], l16 + kb * 1024, at + so + A.lay.rq);
+                p.k[kb] = ldf(q.own[kb], l16 + kb * 1024, at + so + A.lay.kq);
+            }
+            LOAD_ORDER();
+        };
+        // block b of a step; next: the resources that hold the block four further
+        auto block = [&](int b, Pre& p, const Step& next) __attribute__((always_inline)) {
+            const Right<P> vb = conj_v(p.v);
+            CAcc d;
+            czero(d);
+            cmma<P>(d, p.x, vb);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                const Right<P> sb = right_acc<P>(S[kb]);
+                ent[b & 1][cw][2 * h + kb][0][lane] = sb.re;
+                ent[b & 1][cw][2 * h + kb][1][lane] = sb.im;
+                cmma<P>(d, p.w[kb], sb);
+            }
+            red[b & 1][wave][0][lane] = d.re;
+            red[b & 1][wave][1][lane] = d.im;
+            fetch_w(next, b, p);
+            __syncthreads();
+            const f32x4 ore = red[b & 1][wave ^ 1][0][lane], oim = red[b & 1][wave ^ 1][1][lane];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                S[kb].re *= p.d[kb];
+                S[kb].im *= p.d[kb];
+                if constexpr (DEC) cmma<P>(S[kb], p.r[kb], vb);
+            }
+            d.re += ore;
+            d.im += oim;
+            const Right<P> db = right_acc<P>(d);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) cmma<P>(S[kb], p.k[kb], db);
+            fetch_k(next, b, p);
+        };
+        // back from the step's frame
+        struct Rot { f32x4 x[2][2]; };
+        auto load_rot = [&](const Step& q) __attribute__((always_inline)) {
+            Rot z;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) z.x[kb][u] = ldv4(q.own[kb], g * 32 + kb * 128 + u * 16, A.lay.rot + h * 256);
+            return z;
+        };
+        auto turn = [&](const Rot& z) __attribute__((always_inline)) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float cs = z.x[kb][r >> 1][2 * (r & 1)], sn = z.x[kb][r >> 1][2 * (r & 1) + 1];
+                    const float x = S[kb].re[r], y = S[kb].im[r];
+                    S[kb].re[r] = __builtin_fmaf(cs, x, -sn * y);
+                    S[kb].im[r] = __builtin_fmaf(cs, y, sn * x);
+                }
+        };
+        Step cur = step_of(0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            fetch_w(cur, b, pre[b]);
+            fetch_k(cur, b, pre[b]);
+        }
+        for (int st = 0; st < sp.nsteps; ++st) {
+            const Step next = step_of(st + 1);
+            const Rot z = load_rot(cur);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) block(b, pre[b], next);
+            turn(z);
+            cur = next;
+        }
+        if (A.Sout != nullptr) {
+            const rsrc_t rs = rsrc(A.Sout + 2 * sp.base_mn, m * n * 8);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = (2 * h + kb) * 16 + 4 * g + r;
+                    const u32x2 x = {__float_as_uint(S[kb].re[r]), __float_as_uint(S[kb].im[r])};
+                    __builtin_amdgcn_raw_buffer_store_b64(x, rs, j < n && i < m ? static_cast<u32>(i * n + j) * 8u : OOR, 0, 0);
+                }
+        }
+    } else {
+        // ================================================ output waves: blocks 2 i + h
+        const int nkb = A.lay.nkb;
+        u32 ooff[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ooff[r] = j < n ? static_cast<u32>((4 * g + r) * n + j) * 2u * static_cast<u32>(sizeof(TOUT)) : OOR;
+        struct Pre { Frag<P> z[4], y; u32 v[4]; };
+        Pre pre[2];                                    // blocks h and 2 + h of a step
+        auto fetch = [&](int st, int b, Pre& p) __attribute__((always_inline)) {
+            const rsrc_t q = rsrc(sp.rec(A, st), sp.bytes(A, st));
+            const rsrc_t qv = rsrc(gv + sp.elem(A, st), sp.rows(st) * row_v);
+            const int at = b * A.lay.block;
+            p.y = ldf(q, l16, at + A.lay.y);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p.v[r] = __builtin_amdgcn_raw_buffer_load_b32(qv, voff[r], b * 16 * row_v, 0);
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) p.z[kb] = ldf(q, l16, at + A.lay.z + kb * 1024);   // (past nkb not used)
+            LOAD_ORDER();
+        };
+        fetch(0, h, pre[0]);
+        fetch(0, 2 + h, pre[1]);
+        for (int st = 0; st < sp.nsteps; ++st) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                __syncthreads();
+                if ((b & 1) != h) continue;
+                Pre& p = pre[b >> 1];
+                CAcc o;
+                czero(o);
+                cmma<P>(o, p.y, conj_v(p.v));
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb) {
+                    if (kb >= nkb) break;
+                    cmma<P>(o, p.z[kb], Right<P>{ent[b & 1][cw][kb][0][lane], ent[b & 1][cw][kb][1][lane]});
+                }
+                const rsrc_t ro = rsrc(go + sp.elem(A, st), go ? sp.rows(st) * row_o : 0);
+                fetch(st + 1, b, p);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {                // o = conj(O^*)
+                    if constexpr (sizeof(TOUT) == 2)
+                        __builtin_amdgcn_raw_buffer_store_b32(pack_bf16(o.re[r], -o.im[r]), ro, ooff[r], b * 16 * row_o, 0);
+                    else
+                        __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(o.re[r]), __float_as_uint(-o.im[r])}, ro, ooff[r],
+                                                              b * 16 * row_o, 0);
+                }
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------ launches
+
+template <int P, typename TIN, bool DEC>
+static hipError_t prep_t(const ChunkLaunch& L, const PrepArgs& a, hipStream_t st)
+{
+    const long heads = static_cast<long>(L.B) * L.H;
+    hipLaunchKernelGGL((prep_kernel<P, TIN, DEC>), dim3(static_cast<unsigned>(heads * a.nsteps)), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+template <bool DEC>
+static hipError_t scan_t(const ChunkLaunch& L, bool bf, const ScanArgs& a, hipStream_t st)
+{
+    const dim3 grid(static_cast<unsigned>(scan_grid(a.heads, a.n_slices)));
+    if (bf) {
+        if (L.out_bf16) hipLaunchKernelGGL((scan_bf16_kernel<uint16_t, DEC>), grid, dim3(512), 0, st, a);
+        else hipLaunchKernelGGL((scan_bf16_kernel<float, DEC>), grid, dim3(512), 0, st, a);
+    } else if (L.in_bf16) {
+        if (L.out_bf16) hipLaunchKernelGGL((scan_f32_kernel<uint16_t, uint16_t, DEC>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((scan_f32_kernel<uint16_t, float, DEC>), grid, dim3(256), 0, st, a);
+    } else {
+        if (L.out_bf16) hipLaunchKernelGGL((scan_f32_kernel<float, uint16_t, DEC>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((scan_f32_kernel<float, float, DEC>), grid, dim3(256), 0, st, a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace fac
+
+// Records of one 64-token step of every head, and the state carried between pieces
+static long fac_step_bytes(long heads, int m, bool bf, bool dec)
+{
+    return heads * fac::NB * fac::RecLayout(m, bf, dec).block;
+}
+
+size_t factored_bytes(long heads, int T, int m, int n, bool in_bf16, bool dec, size_t cap)
+{
+    const long steps = (static_cast<long>(T) + fac::CP - 1) / fac::CP;
+    const long one = fac_step_bytes(heads, m, bf16_operands(in_bf16, m), dec);
+    long piece = one > 0 ? static_cast<long>(cap) / one : steps;
+    piece = piece < 1 ? 1 : piece > steps ? steps : piece;
+    return static_cast<size_t>(piece) * one + (piece < steps ? static_cast<size_t>(heads) * m * n * 8 : 0);
+}
+
+hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus, hipStream_t st)
+{
+    using namespace fac;
+    const bool dec = L.r != nullptr, bf = bf16_operands(L.in_bf16, L.m);
+    const long heads = static_cast<long>(L.B) * L.H;
+    const int steps = (L.T + CP - 1) / CP;
+    const long one = fac_step_bytes(heads, L.m, bf, dec);
+    const long carry_bytes = heads * L.m * static_cast<long>(L.n) * 8;
+    const bool whole = static_cast<size_t>(steps) * one <= bytes;
+    long piece = whole ? steps : (static_cast<long>(bytes) - carry_bytes) / one;
+    if (piece < 1) return hipErrorInvalidValue;
+    const long most = 0x7FFFFFFFL / heads;              // workgroups of a launch
+    if (piece > most) piece = most;
+    // the state between pieces: S_T where the caller wants it, else the end of the workspace
+    float* carry = L.S_T ? L.S_T : reinterpret_cast<float*>(static_cast<char*>(ws) + bytes - carry_bytes);
+
+    ScanArgs sa{static_cast<const char*>(ws), L.v, L.o, L.S0, nullptr, heads, L.T, L.m, L.n, 0, 0, 0, RecLayout(L.m, bf, dec)};
+    const int cols = bf ? BCOLS : FCOLS;
+    sa.n_slices = (L.n + cols - 1) / cols;
+    PrepArgs pa{L.q, L.k, L.alpha, L.theta, L.beta, L.r, L.wbeta, static_cast<char*>(ws), L.T, L.m, 0, 0, sa.lay};
+    auto prepare = [&](const PrepArgs& p) {
+        if (dec)
+            return bf ? prep_t<PREC_BF16, uint16_t, true>(L, p, st)
+                      : L.in_bf16 ? prep_t<PREC_F32, uint16_t, true>(L, p, st) : prep_t<PREC_F32, float, true>(L, p, st);
+        return bf ? prep_t<PREC_BF16, uint16_t, false>(L, p, st)
+                  : L.in_bf16 ? prep_t<PREC_F32, uint16_t, false>(L, p, st) : prep_t<PREC_F32, float, false>(L, p, st);
+    };
+    // float32 scans on at most half of the compute units: each piece's scan with the next one's
+    // preparation beside it, the records in two halves of the workspace (H16 T65536: 3.86 ms
+    // one after the other)
+    const long nscan = scan_grid(heads, sa.n_slices);
+    bool beside = false;
+    if (!dec && !L.in_bf16 && 2 * nscan <= cus && steps >= 8) {
+        const long half = whole ? (steps + 3) / 4 : piece / 2;
+        if (half >= 1 && static_cast<size_t>(2 * half * one + carry_bytes) <= bytes) {
+            beside = true;
+            piece = half;
+        }
+    }
+    for (int s = 0, half = 0; s < steps; s += static_cast<int>(piece), half ^= beside) {
+        const int here = steps - s < piece ? steps - s : static_cast<int>(piece);
+        const int after = steps - s - here < piece ? steps - s - here : static_cast<int>(piece);
+        char* const at = static_cast<char*>(ws) + half * piece * one;
+        pa.step0 = sa.step0 = s;
+        pa.nsteps = sa.nsteps = here;
+        pa.fac = at;
+        sa.fac = at;
+        sa.Sout = s + here < steps ? carry : L.S_T;
+        hipError_t e = hipSuccess;
+        if (!beside || s == 0) e = prepare(pa);
+        if (e != hipSuccess) return e;
+        if (beside && after > 0) {
+            pa.step0 = s + here;
+            pa.nsteps = after;
+            pa.fac = static_cast<char*>(ws) + (half ^ 1) * piece * one;
+            const dim3 grid(static_cast<unsigned>(nscan + heads * after));
+            if (L.out_bf16) hipLaunchKernelGGL((scan_prep_f32_kernel<float, uint16_t>), grid, dim3(256), 0, st, sa, pa, static_cast<unsigned>(nscan));
+            else hipLaunchKernelGGL((scan_prep_f32_kernel<float, float>), grid, dim3(256), 0, st, sa, pa, static_cast<unsigned>(nscan));
+            e = hipGetLastError();
+        } else {
+            e = dec ? scan_t<true>(L, bf, sa, st) : scan_t<false>(L, bf, sa, st);
+        }
+        if (e != hipSuccess) return e;
+        sa.Sin = carry;
+    }
+    return hipSuccess;
+}
+
+}  // namespace sfda

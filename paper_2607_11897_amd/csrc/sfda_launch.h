@@ -39,11 +39,6 @@ struct ChunkLaunch {
     // strengths wbeta; beta holds the erase strengths
     const void* r = nullptr;
     const void* wbeta = nullptr;
-    // segment forward (launch_chunk_segment): beside the value columns (from S0 = 0 when
-    // S0 is null) the m columns of the homogeneous transfer from I_m, with outputs
-    // X_t = P_t^* q_t [heads][T][m] and the last transfer [heads][m][m] (complex fp32)
-    float* xo = nullptr;
-    float* pend = nullptr;
 };
 
 // per-chunk gradient pass of the backward (one workgroup per head and chunk)
@@ -73,18 +68,20 @@ hipError_t launch_step(const StepLaunch& L, hipStream_t st);
 hipError_t launch_chunk(const ChunkLaunch& L, hipStream_t st);
 hipError_t launch_chunk_bf16(const ChunkLaunch& L, hipStream_t st);   // bf16 inputs
 hipError_t launch_chunk_decoupled(const ChunkLaunch& L, hipStream_t st);   // C = 16 or 32
-hipError_t launch_chunk_segment(const ChunkLaunch& L, hipStream_t st);
+// the factored forward (sfda_factored.h; write-decoupled when L.r is set): operand records of
+// as many 64-token steps at a time as `bytes` of workspace hold, then a scan over them.
+// factored_bytes: the workspace that holds `cap` bytes of records (at least one step's, at
+// most the whole sequence's), with the state carried between pieces
+size_t factored_bytes(long heads, int T, int m, int n, bool in_bf16, bool dec, size_t cap);
+hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus, hipStream_t st);   // cus: compute units
 // backward: the forward scan recording states and Delta (F; none when F.T == 0) and the
 // reverse adjoint scan (A) in one launch, then the per-chunk gradient pass
 hipError_t launch_bwd_scans(const ChunkLaunch& F, const ChunkLaunch& A, hipStream_t st);
 hipError_t launch_chunk_grad(const GradLaunch& L, hipStream_t st);
 // per 16-token block: the triangular solve's residual and ||D_beta L'||_F ([B, H, ceil(T / 16)])
 hipError_t launch_solve_monitor(const ChunkLaunch& L, float* residual, float* lnorm, hipStream_t st);
-// segment-parallel scan: identity fill, the fold of the segments' affine maps and the join of
-// the outputs (o += S_in^* X)
+// segment-parallel scan: identity fill and the fold of the segments' affine maps
 hipError_t launch_identity(float* P, long count, int m, hipStream_t st);
-hipError_t launch_join(const float* X, const float* Sin, void* o, bool out_bf16, long segs,
-                       int Ts, int m, int n, hipStream_t st);
 hipError_t launch_fold(const float* P, const float* Bs, float* Sin, const float* S0, float* S_T,
                        long heads, int G, int m, int n, hipStream_t st);
 

@@ -22,7 +22,8 @@ STATUS = {0: "SFDA_OK", 1: "SFDA_ERR_NULL", 2: "SFDA_ERR_SHAPE", 3: "SFDA_ERR_CH
           8: "SFDA_ERR_SCRATCH"}
 NOALLOC_SCRATCH_BYTES = 32 * 1024 * 1024      # SFDA_NOALLOC_SCRATCH_BYTES
 EXPORTS = ("sfda_chunk_fwd", "sfda_chunk_fwd_sliced", "sfda_chunk_fwd_gated", "sfda_chunk_fwd_decoupled",
-           "sfda_chunk_fwd_segmented", "sfda_chunk_fwd_segmented_noalloc",
+           "sfda_chunk_fwd_factored", "sfda_chunk_fwd_decoupled_factored",
+           "sfda_chunk_fwd_factored_workspace_bytes", "sfda_chunk_fwd_segmented", "sfda_chunk_fwd_segmented_noalloc",
            "sfda_chunk_fwd_segmented_workspace_bytes", "sfda_chunk_fwd_auto_segments",
            "sfda_chunk_bwd", "sfda_chunk_bwd_workspace_bytes", "sfda_chunk_solve_monitor",
            "sfda_step", "sfda_status_string", "sfda_abi_version")
@@ -70,6 +71,12 @@ def load_library(path: str = LIB_PATH):
     lib.sfda_chunk_fwd_gated.restype = i
     lib.sfda_chunk_fwd_decoupled.argtypes = [vp] * 11 + [i] * 6 + [i, i, vp]
     lib.sfda_chunk_fwd_decoupled.restype = i
+    lib.sfda_chunk_fwd_factored.argtypes = [vp] * 9 + [i] * 6 + [i, i, vp, ctypes.c_size_t, vp]
+    lib.sfda_chunk_fwd_factored.restype = i
+    lib.sfda_chunk_fwd_decoupled_factored.argtypes = [vp] * 11 + [i] * 6 + [i, i, vp, ctypes.c_size_t, vp]
+    lib.sfda_chunk_fwd_decoupled_factored.restype = i
+    lib.sfda_chunk_fwd_factored_workspace_bytes.argtypes = [i] * 7
+    lib.sfda_chunk_fwd_factored_workspace_bytes.restype = ctypes.c_size_t
     lib.sfda_chunk_fwd_segmented.argtypes = [vp] * 9 + [i] * 7 + [i, i, vp, ctypes.c_size_t, vp]
     lib.sfda_chunk_fwd_segmented.restype = i
     lib.sfda_chunk_fwd_segmented_noalloc.argtypes = [vp] * 9 + [i] * 7 + [i, i, vp]
@@ -155,6 +162,16 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+def _workspace(nbytes: int, device, stream):
+    """A workspace from torch's allocator, owned by the stream it is used on (so that its memory
+    is given to later work of that stream only)."""
+    import torch
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
 def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=None,
               out_dtype=None, want_state: bool = True, slice: Optional[int] = None,
               segments="auto", workspace=None, stream=None) -> Tuple:
@@ -164,9 +181,11 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
     slice: value columns per workgroup (sfda_chunk_fwd_sliced); segments: G parallel
     segments per head (sfda_chunk_fwd_segmented; `workspace` a uint8 device tensor of at
     least segmented_workspace_bytes(...) bytes, allocated here when not given), None for one
-    scan per head (sfda_chunk_fwd), or "auto" (the default, without a slice): the count
-    sfda_chunk_fwd_auto_segments suggests, segments when the heads alone would leave most
-    compute units idle (the workspace then comes from torch's allocator)."""
+    scan per head (sfda_chunk_fwd), or "auto" (the default).  "auto" runs float32 inputs through
+    sfda_chunk_fwd_factored (whatever the slice: no column's arithmetic depends on it) and
+    bfloat16 ones, without a slice, with the count sfda_chunk_fwd_auto_segments suggests:
+    segments when the heads alone would leave most compute units idle.  Workspaces not given
+    come from torch's allocator."""
     import torch
     lib = load_library()
     B, H, T, m, _ = _dims(q, v, 5)
@@ -192,6 +211,17 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
         if segments != "auto":
             raise ValueError(f"segments must be an int, None or 'auto', not {segments!r}")
         segments = None
+        nfac = 0
+        # (a slice the library refuses goes to sfda_chunk_fwd_sliced, which says so; a workspace
+        # the caller sized for segments keeps them)
+        if in_code == SFDA_F32 and workspace is None and (slice is None or (8 <= slice <= 64 and slice % 8 == 0)):
+            nfac = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 0)
+        if nfac:
+            ws = _workspace(nfac, q.device, stream)
+            st = lib.sfda_chunk_fwd_factored(*args, in_code, _dtype_code(o), _ptr(ws), nfac, _stream(stream))
+            if st != 0:
+                raise SfdaError(st, "sfda_chunk_fwd_factored")
+            return o, S_T
         if slice is None and q.is_cuda:
             with torch.cuda.device(q.device):
                 G = int(lib.sfda_chunk_fwd_auto_segments(B, H, T, m, n, C, in_code))
@@ -199,7 +229,7 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
     if segments is not None:
         nws = lib.sfda_chunk_fwd_segmented_workspace_bytes(B, H, T, m, n, segments, in_code)
         if workspace is None:
-            workspace = torch.empty(max(nws, 1), dtype=torch.uint8, device=q.device)
+            workspace = _workspace(max(nws, 1), q.device, stream)
         st = lib.sfda_chunk_fwd_segmented(*args, segments, in_code, _dtype_code(o), _ptr(workspace),
                                           workspace.numel() * workspace.element_size(), _stream(stream))
         if st != 0:
@@ -281,9 +311,9 @@ def chunk_fwd_gated(q, k_raw, v, a, b, c, S0=None, C: int = 64, *, alpha_min: fl
 
 def chunk_fwd_decoupled(q, k, r, v, alpha, theta, eta, beta, S0=None, C: int = 32, *, o=None,
                         S_T=None, out_dtype=None, want_state: bool = True, stream=None) -> Tuple:
-    """Write-decoupled forward (sfda_chunk_fwd_decoupled): erase along k with strengths eta
-    [B,H,T], write along r [B,H,T,m,2] with strengths beta [B,H,T]; C 16 or 32.  Shapes and
-    results otherwise as chunk_fwd."""
+    """Write-decoupled forward (sfda_chunk_fwd_decoupled_factored, its workspace from torch's
+    allocator): erase along k with strengths eta [B,H,T], write along r [B,H,T,m,2] with
+    strengths beta [B,H,T].  Shapes and results otherwise as chunk_fwd."""
     import torch
     lib = load_library()
     B, H, T, m, _ = _dims(q, v, 5)
@@ -303,9 +333,14 @@ def chunk_fwd_decoupled(q, k, r, v, alpha, theta, eta, beta, S0=None, C: int = 3
                 v=(v, (B, H, T, n, 2)), alpha=(alpha, (B, H, T, m)), theta=(theta, (B, H, T, m)),
                 eta=(eta, (B, H, T)), beta=(beta, (B, H, T)), S0=(S0, (B, H, m, n, 2)),
                 o=(o, (B, H, T, n, 2)), S_T=(S_T, (B, H, m, n, 2))))
-    st = lib.sfda_chunk_fwd_decoupled(_ptr(q), _ptr(k), _ptr(r), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(eta),
-                                      _ptr(beta), _ptr(S0), _ptr(o), _ptr(S_T), B, H, T, m, n, C, in_code,
-                                      _dtype_code(o), _stream(stream))
+    args = [_ptr(q), _ptr(k), _ptr(r), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(eta), _ptr(beta), _ptr(S0),
+            _ptr(o), _ptr(S_T), B, H, T, m, n, C, in_code, _dtype_code(o)]
+    nws = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 1)
+    if nws:
+        ws = _workspace(nws, q.device, stream)
+        st = lib.sfda_chunk_fwd_decoupled_factored(*args, _ptr(ws), nws, _stream(stream))
+    else:
+        st = lib.sfda_chunk_fwd_decoupled(*args, _stream(stream))
     if st != 0:
         raise SfdaError(st, "sfda_chunk_fwd_decoupled")
     return o, S_T

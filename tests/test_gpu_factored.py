@@ -1,0 +1,118 @@
+"""The factored forwards (sfda_chunk_fwd_factored, sfda_chunk_fwd_decoupled_factored) at the edges
+of their tiles and steps, against the complex128 oracle: tokens around the 16-token block and the
+64-token step, key channels around the 16-channel block, value columns around the scans' 8 and
+32 columns; in several pieces, and with a piece's scan beside the next one's preparation
+(few heads, many steps), bitwise the same as in one piece.
+
+Bars as for sfda_chunk_fwd: max |x - ref| / max |ref| <= 1e-4 (float32 inputs), <= 2e-2 (bfloat16)."""
+from __future__ import annotations
+
+import ctypes
+
+import numpy as np
+import pytest
+
+from gpu_util import I, ensure_built, rel_err, run_oracle, to_complex, upload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return ensure_built()
+
+
+def say(*a):
+    print("[case]", *a, flush=True)
+
+
+def factored(lib, x, bytes_=None):
+    """sfda_chunk_fwd_factored through the C entry (every dtype), its workspace poisoned."""
+    import torch
+    from paper_2607_11897_amd import sfda
+    d = upload(x)
+    B, H, T, m, n = x.shape
+    code = sfda.SFDA_F32 if x.dtype == "f32" else sfda.SFDA_BF16
+    need = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, code, 0)
+    assert need > 0
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")     # NaN, whatever the type
+    o = torch.full((B, H, T, n, 2), float("nan"), device="cuda", dtype=d["q"].dtype)
+    S = torch.full((B, H, m, n, 2), float("nan"), device="cuda")
+    p = lambda t: None if t is None else ctypes.c_void_p(t.data_ptr())
+    st = lib.sfda_chunk_fwd_factored(p(d["q"]), p(d["k"]), p(d["v"]), p(d["alpha"]), p(d["theta"]), p(d["beta"]),
+                                     p(d["S0"]), p(o), p(S), B, H, T, m, n, 64, code, code, p(ws), need,
+                                     ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0
+    torch.cuda.synchronize()
+    return to_complex(o), to_complex(S)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,T,m,n", [
+    (1, 1, 1, 64, 64), (1, 2, 16, 16, 8), (2, 5, 17, 17, 9), (1, 3, 63, 33, 33), (1, 8, 64, 48, 32),
+    (3, 3, 65, 64, 65), (1, 9, 129, 5, 7), (1, 2, 200, 47, 1), (1, 1, 130, 3, 40), (2, 1, 96, 62, 96),
+])
+def test_factored_edges(lib, B, H, T, m, n, dtype):
+    x = I.make_chunk_inputs(I.Workload("edge", B, H, T, m, n, 64, dtype, I.LAWS_MAIN, 900 + T + m, 1e-4))
+    say("factored", (B, H, T, m, n), dtype)
+    o, S = factored(lib, x)
+    o_ref, S_ref = run_oracle(x)
+    tol = 1e-4 if dtype == "f32" else 2e-2
+    eo, es = rel_err(o, o_ref), rel_err(S, S_ref)
+    say("err(o)", eo, "err(S_T)", es)
+    assert eo <= tol and es <= tol
+
+
+@pytest.mark.parametrize("B,H,T,m,n,G", [
+    (1, 3, 768, 40, 24, 1),       # 2 * 3 * 3 workgroups at most: pieces with the next one prepared beside
+    (1, 64, 640, 64, 64, 1),      # 512 workgroups: pieces one after the other
+])
+def test_factored_pieces_bitwise(lib, B, H, T, m, n, G):
+    """sfda_chunk_fwd_segmented's workspace holds the records of a part of the sequence only: the
+    result is bitwise that of the workspace that holds them all."""
+    import torch
+    from paper_2607_11897_amd import sfda
+    x = I.make_chunk_inputs(I.Workload("pieces", B, H, T, m, n, 64, "f32", I.LAWS_LONG, 950, 1e-4))
+    d = upload(x)
+    args = (d["q"], d["k"], d["v"], d["alpha"], d["theta"], d["beta"], d["S0"])
+    small = sfda.segmented_workspace_bytes(B, H, T, m, n, G)
+    assert small < lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, 0, 0)
+    say("pieces", (B, H, T, m, n))
+    o1, S1 = sfda.chunk_fwd(*args, C=64)
+    o2, S2 = sfda.chunk_fwd(*args, C=64, segments=G)
+    o3, _ = sfda.chunk_fwd(*args, C=64, segments=G, want_state=False)     # the state carried in the workspace
+    torch.cuda.synchronize()
+    assert torch.equal(o1, o2) and torch.equal(S1, S2) and torch.equal(o1, o3)
+    x0 = x.head(0, H - 1)
+    o_ref, S_ref = run_oracle(x0)
+    assert rel_err(to_complex(o1)[:1, H - 1:], o_ref) <= 1e-4 and rel_err(to_complex(S1)[:1, H - 1:], S_ref) <= 1e-4
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,m,n", [(1, 16, 8), (33, 17, 33), (64, 64, 64), (131, 50, 7)])
+def test_decoupled_edges(T, m, n, dtype):
+    from test_gpu_decoupled import oracle_dec, run_dec
+    x = I.make_decoupled_inputs(1, 9, T, m, n, dtype, seed=970 + T)
+    say("decoupled", (T, m, n), dtype)
+    o, S = run_dec(x, 16)
+    o_ref, S_ref = oracle_dec(x)
+    tol = 1e-4 if dtype == "f32" else 2e-2
+    assert rel_err(o, o_ref) <= tol and rel_err(S, S_ref) <= tol
+
+
+@pytest.mark.parametrize("field,bad", [("theta", float("nan")), ("theta", float("inf")), ("alpha", 1e-39)])
+def test_bad_gate_gives_nan_from_its_block_on(lib, field, bad):
+    """A phase that is not finite, or a decay below the block range: NaN from that 16-token block
+    on and in S_T, the blocks before it untouched."""
+    x = I.make_chunk_inputs(I.Workload("bad", 1, 2, 100, 20, 12, 64, "f32", I.LAWS_MAIN, 990, 1e-4))
+    o_ref, _ = run_oracle(x)
+    a = getattr(x, field).copy()
+    a[0, 1, 53, 7] = bad                                  # block 3 of head 1
+    import dataclasses
+    o, S = factored(lib, dataclasses.replace(x, **{field: a}))
+    say("bad", field, bad)
+    assert np.all(np.isnan(o[0, 1, 48:])) and np.all(np.isnan(S[0, 1]))
+    assert rel_err(o[0, 1, :48], o_ref[0, 1, :48]) <= 1e-4 and rel_err(o[0, 0], o_ref[0, 0]) <= 1e-4
+    assert np.all(np.isfinite(S[0, 0]))
