@@ -82,8 +82,12 @@ int auto_slice(long BH, int n)
     return slice;
 }
 
-// the factored scans run one workgroup per head and 8 value columns
-bool factored_fits(long BH, int n) { return (BH + 7) * ((n + 7) / 8) <= 0x7FFFFFFFL; }
+// the factored scans run one workgroup per head and 8 value columns, and address a 64-token
+// step's rows of v, o and dL/do (at most 8 bytes per element) with 32-bit byte offsets
+bool factored_fits(long BH, int n)
+{
+    return (BH + 7) * ((n + 7) / 8) <= 0x7FFFFFFFL && static_cast<long>(64) * n * 8 < 0x80000000L;
+}
 // most bytes of operand records that the suggested workspace holds at a time (the sequence then
 // runs in pieces; the records of one piece also stay within reach of the 256 MiB last-level
 // cache)

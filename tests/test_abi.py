@@ -313,3 +313,13 @@ def test_solve_monitor_argument_errors(lib):
     assert monitor(lib, res=P[1]) == 6            # over k
     assert monitor(lib, ln=P[6]) == 6             # over residual
     assert monitor(lib, B=0, k=None) == 0 and monitor(lib, T=0, k=None) == 0
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_factored_row_offsets(lib, dtype):
+    """A 64-token step's rows must lie within 32-bit byte offsets: past that the factored forwards
+    have no workspace (and refuse the call), and the binding runs the scan in place."""
+    n = 1 << 22
+    assert lib.sfda_chunk_fwd_factored_workspace_bytes(1, 1, 64, 1, n - 1, dtype, 0) > 0
+    assert lib.sfda_chunk_fwd_factored_workspace_bytes(1, 1, 64, 1, n, dtype, 0) == 0
+    assert lib.sfda_chunk_fwd_factored_workspace_bytes(1, 1, 64, 1, n, dtype, 1) == 0
