@@ -288,10 +288,10 @@ sfda_status_t sfda_chunk_fwd_segmented(const void* q, const void* k, const void*
  * (the backward of the chunkwise forward, recomputing the chunk factors of Thm 4.2 /
  * Cor. 4.3 instead of storing them).  Given dO = dL/do and dS_T = dL/dS_T it returns the
  * gradients with respect to every input; the gradient of a complex variable z is
- * dL/dRe(z) + i dL/dIm(z).  Three launches on the stream: a forward scan recording the
- * state entering each chunk and the chunk's solve result, a reverse scan carrying dL/dS
- * through the chunks (the adjoint of the boundary-state map of Thm 6.1; it writes dv and
- * dS0), and one workgroup per (head, chunk) forming dq, dk, dalpha, dtheta and dbeta.
+ * dL/dRe(z) + i dL/dIm(z).  On the stream: a forward scan recording the state entering each
+ * chunk and the chunk's solve result, a reverse scan carrying dL/dS through the chunks (the
+ * adjoint of the boundary-state map of Thm 6.1; it writes dv and dS0), both in one launch, and
+ * one workgroup per (head, chunk) forming dq, dk, dalpha, dtheta and dbeta.
  *   q, k, v, alpha, theta, beta, S0 : as sfda_chunk_fwd (in_dtype; S0 NULL = zero state).
  *   dO   : [B,H,T,n] complex (device, out_dtype); dS_T : [B,H,m,n] complex float32 or NULL
  *          (zero).
@@ -312,6 +312,15 @@ sfda_status_t sfda_chunk_fwd_segmented(const void* q, const void* k, const void*
  *   alpha must be nonzero wherever T > 0 (dalpha divides by it).
  */
 size_t sfda_chunk_bwd_workspace_bytes(int B, int H, int T, int m, int n, int C);
+
+/*
+ * sfda_chunk_bwd_factored_workspace_bytes -- the workspace at which sfda_chunk_bwd prepares its
+ * scans' operands for all blocks in parallel (as sfda_chunk_fwd_factored does; faster, the same
+ * gradients up to rounding): at least sfda_chunk_bwd_workspace_bytes; 0 where there is none
+ * (sizes sfda_chunk_bwd refuses, and T == 0).
+ */
+size_t sfda_chunk_bwd_factored_workspace_bytes(int B, int H, int T, int m, int n, int C,
+                                               sfda_dtype_t in_dtype);
 
 sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const void* alpha,
                              const void* theta, const void* beta, const float* S0,

@@ -487,9 +487,6 @@ sfda_status_t sfda_chunk_fwd_segmented_noalloc(const void* q, const void* k, con
                           out_dtype, nullptr, 0, stream, true);
 }
 
-// the backward's chunk length: C = 64 and 128 run at 32 (the gradient pass stages a block
-// of value columns beside the chunk's operands in LDS; every C gives the same gradients up
-// to rounding)
 // The backward runs 16-token chunks whatever C is (the gradients do not depend on the
 // chunk length, to rounding): 1 / g of a 16-token chunk stays finite while the chunk's
 // decay is at least 2^-126, the forward's range, and measured on MI355X it is as fast as
@@ -507,6 +504,15 @@ size_t sfda_chunk_bwd_workspace_bytes(int B, int H, int T, int m, int n, int C)
     return chunks * (2 * static_cast<size_t>(m) * n + 2 * static_cast<size_t>(C) * n) * 8;
 }
 
+size_t sfda_chunk_bwd_factored_workspace_bytes(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype)
+{
+    const size_t need = sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C);
+    const long BH = static_cast<long>(B) * H;
+    // (twice the forward's scans in one launch)
+    if (need == 0 || !dtype_ok(in_dtype) || !factored_fits(2 * BH + 8, n)) return 0;
+    return (need + 255) / 256 * 256 + sfda::bwd_factors_bytes(BH, T, m, in_dtype == SFDA_BF16);
+}
+
 sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const void* alpha,
                              const void* theta, const void* beta, const float* S0,
                              const void* dO, const float* dS_T, void* dq, void* dk, void* dv,
@@ -520,6 +526,7 @@ sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const 
     if (!chunk_ok(C)) return SFDA_ERR_CHUNK;
     if (!chunk_rows_fit(n)) return SFDA_ERR_SHAPE;
     const size_t need = sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C);
+    const int requested_C = C;
     C = bwd_chunk(C);
     const long BH = static_cast<long>(B) * H;
     const int slice = n <= 64 ? ((n + 7) / 8) * 8 : 64;
@@ -554,6 +561,15 @@ sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const 
         for (int b = a + 1; b < 8; ++b)
             if (overlap(outs[a], outs[b])) return SFDA_ERR_ALIAS;
     }
+    // the factored scans, where the workspace has room for the operand records (a caller's
+    // tensors past the needed bytes, inside workspace_bytes, are none of its own: scans in place)
+    const size_t facs = sfda_chunk_bwd_factored_workspace_bytes(B, H, T, m, n, requested_C, in_dtype);
+    bool factored = facs > 0 && workspace_bytes >= facs;
+    const Range whole = range_of(workspace, static_cast<long>(facs));
+    if (factored) {
+        for (const Range& r : ins) factored = factored && !overlap(whole, r);
+        for (int a = 0; a < 7; ++a) factored = factored && !overlap(whole, outs[a]);
+    }
 
     const hipStream_t st = static_cast<hipStream_t>(stream);
     float* S_rec = static_cast<float*>(workspace);
@@ -571,7 +587,9 @@ sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const 
     sfda::ChunkLaunch F = L;
     F.S0 = S0; F.S_T = nullptr; F.ck_state = S_rec; F.ck_rows = D_rows;
     L.S0 = dS_T; L.S_T = dS0; L.ck_state = G_rec; L.ck_rows = F_rows; L.dO = dO; L.dv = dv;
-    if (sfda::launch_bwd_scans(F, L, st) != hipSuccess) return SFDA_ERR_HIP;
+    const hipError_t scans = factored ? sfda::launch_bwd_factored(F, L, static_cast<char*>(workspace) + (need + 255) / 256 * 256, st)
+                                      : sfda::launch_bwd_scans(F, L, st);
+    if (scans != hipSuccess) return SFDA_ERR_HIP;
     if (!need_inputs) return SFDA_OK;
     sfda::GradLaunch Gl;
     Gl.q = q; Gl.k = k; Gl.v = v; Gl.alpha = alpha; Gl.theta = theta; Gl.beta = beta; Gl.dO = dO;

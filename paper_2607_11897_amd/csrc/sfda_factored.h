@@ -39,6 +39,9 @@ namespace fac {
 constexpr int CP = 64;               // tokens per step (one workgroup of the preparing kernel)
 constexpr int NB = CP / 16;          // blocks per step
 
+// what the records serve: the forward, the write-decoupled forward, the backward's scans
+enum Kind { FWD = 0, DEC = 1, BWD = 2 };
+
 // bytes of one block's record and of its parts
 struct RecLayout {
     int nkb, frag, z, kq, rq, x, y, dm, rot, block;
@@ -53,6 +56,31 @@ struct RecLayout {
         dm = y + frag;
         rot = dm + 256;
         block = rot + 512;
+    }
+};
+
+// The backward's records.  The frame is the block's own: phases relative to the block's first
+// token, and K Q turned to its end, so that S_out = g S + (K Q)^T Delta with g = |D| e^{i phi} of
+// the block (complex), and the adjoint of the block (G = dL/dS_out, G_R = conj(dL/do)) is
+//   X' = conj(K Q) G,   dL/dS = conj(g) G - W^* X' + Z^* G_R,
+//   G_F = N^* (X' + A^* G_R)     (the adjoint of the solve's right-hand side, before D_beta)
+// Fragments, in the order of the forward's record: -W [kb] and T (rows tokens), K Q [kb] (rows
+// channels) for the states; conj(K Q) [kb] (rows tokens), -W^* [kb] and Z^* [kb] (rows channels),
+// N^* and (A N)^* (rows tokens) for the adjoint; g [64] complex fp32.
+struct BwdLayout {
+    int nkb, frag, kq, kr, ws, zs, x, ns, an, gc, block;
+    __host__ __device__ BwdLayout(int m, bool bf16) {
+        nkb = (m + 15) / 16;
+        frag = bf16 ? 1024 : 2048;
+        kq = nkb * frag;
+        kr = 2 * kq;
+        ws = 3 * kq;
+        zs = 4 * kq;
+        x = 5 * kq;
+        ns = x + frag;
+        an = ns + frag;
+        gc = an + frag;
+        block = gc + 512;
     }
 };
 

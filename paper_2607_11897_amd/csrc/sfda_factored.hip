@@ -65,6 +65,11 @@ template <int P> __device__ __forceinline__ Frag<P> frag_acc(const CAcc& z, floa
     for (int r = 0; r < 4; ++r) x[r] = make_float2(s * z.re[r], s * z.im[r]);
     return frag4<P>(x);
 }
+// what the rounding of x to a fragment leaves over
+__device__ __forceinline__ float2 rest(float2 x) {
+    const uint32_t w = pack_bf16(x.x, x.y);
+    return make_float2(x.x - bf_lo(w), x.y - bf_hi(w));
+}
 template <int P> __device__ __forceinline__ float2 frag_get(const Frag<P>& f, int r) {
     if constexpr (P == PREC_BF16) return make_float2(bf_lo(f.w[r]), bf_hi(f.w[r]));
     else return f.x[r];
@@ -127,6 +132,7 @@ struct PrepArgs {
     char* fac;
     int T, m, step0, nsteps;             // steps of this piece
     RecLayout lay;
+    BwdLayout bwd;                       // the records' layout for the backward
 };
 
 template <int P> struct Op {             // operand areas of one wave
@@ -224,10 +230,11 @@ template <int P> struct PrepSmem {
     static_assert(Op<P>::AREA >= 16 * 18 * 8, "the inverse's scratch fits an operand area");
 };
 
-template <int P, typename TIN, bool DEC>
+template <int P, typename TIN, int KIND>
 __device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigned wg)
 {
     constexpr int ES = Op<P>::ES, PITCH = Op<P>::PITCH;
+    constexpr bool DEC = KIND == Kind::DEC, BWD = KIND == Kind::BWD;
     auto& sw = sm.w;
     auto& tph = sm.tph;
 
@@ -340,10 +347,11 @@ __device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigne
         if (s0) *reinterpret_cast<u32x4*>(&tph[pw][pc0]) = u32x4{tpk[0], tpk[1], tpk[2], tpk[3]};
     }
     __syncthreads();
-    char* const rec = A.fac + ((bh * A.nsteps + st) * static_cast<long>(NB) + pw) * A.lay.block;
-    const int nkb = A.lay.nkb;
+    char* const rec = A.fac + ((bh * A.nsteps + st) * static_cast<long>(NB) + pw) * (BWD ? A.bwd.block : A.lay.block);
+    const int nkb = A.lay.nkb, frag = A.lay.frag;
     constexpr float REV = 1.f / 4294967296.f;
     u32 off[4] = {0, 0, 0, 0};
+    float2 turn_end[4];                   // e^{i phi} at the end of the frame (step, or block: BWD)
     {
         u32 tot[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -351,17 +359,22 @@ __device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigne
             const u32x4 t = *reinterpret_cast<const u32x4*>(&tph[b][pc0]);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (b < pw) off[k] += t[k];
-                tot[k] += t[k];
+                if (!BWD && b < pw) off[k] += t[k];
+                if (!BWD || b == pw) tot[k] += t[k];
             }
         }
-        if (tsg == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float p = static_cast<float>(tot[k]) * REV;
+            turn_end[k] = make_float2(__builtin_amdgcn_cosf(p), __builtin_amdgcn_sinf(p));
+        }
+        if (BWD && tsg == 0) {
             float2 z[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float p = static_cast<float>(tot[k]) * REV;
-                z[k] = make_float2(__builtin_amdgcn_cosf(p), __builtin_amdgcn_sinf(p));
-            }
+            for (int k = 0; k < 4; ++k) z[k] = make_float2(dtot[k] * turn_end[k].x, dtot[k] * turn_end[k].y);
+            put4<PREC_F32>(rec + A.bwd.gc + pc0 * 8, z);
+        } else if (tsg == 0) {
+            const float2 (&z)[4] = turn_end;
             *reinterpret_cast<float4*>(rec + A.lay.dm + pc0 * 4) = make_float4(dtot[0], dtot[1], dtot[2], dtot[3]);
             put4<PREC_F32>(rec + A.lay.rot + pc0 * 8, z);
         }
@@ -381,6 +394,7 @@ __device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigne
 
     // ---- K Q (and R Q D_beta) to the record, through the wave's area so that the stores are
     // whole lines
+    [[maybe_unused]] float2 kq_end[4][4];           // BWD: K Q turned to the block's end
     auto out_cols = [&](const float2 (&x)[4][4], int at, const float* wt) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -390,16 +404,21 @@ __device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigne
                 float s = Qb[u][k];
                 if constexpr (DEC) if (wt) s *= wt[tsg * 4 + u];
                 y[u] = make_float2(x[u][k].x * s, -x[u][k].y * s);
+                if constexpr (BWD) {
+                    const float2 e = turn_end[k];
+                    y[u] = make_float2(y[u].x * e.x - y[u].y * e.y, y[u].x * e.y + y[u].y * e.x);
+                    kq_end[u][k] = y[u];
+                }
             }
             const int l2 = (cg & 3) * 4 + k + 16 * tsg;       // the fragment's lane
-            put_frag<P>(w.r1 + (cg >> 2) * A.lay.frag, l2, frag4<P>(y));
+            put_frag<P>(w.r1 + (cg >> 2) * frag, l2, frag4<P>(y));
         }
         wave_order();
-        for (int i = 0; i < nkb * A.lay.frag; i += 1024)
+        for (int i = 0; i < nkb * frag; i += 1024)
             *reinterpret_cast<u32x4*>(rec + at + i + lane * 16) = *reinterpret_cast<const u32x4*>(w.r1 + i + lane * 16);
         wave_order();
     };
-    out_cols(kq, A.lay.kq, nullptr);
+    out_cols(kq, BWD ? A.bwd.kq : A.lay.kq, nullptr);
     if constexpr (DEC) out_cols(rq, A.lay.rq, w.wb);
 
     // ---- row operands: conj(Q) G, conj(K) G (kept in area 0), K / G
@@ -417,10 +436,50 @@ __device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigne
         wave_order();
     };
     Frag<P> qf[4], kf[4];
+    // BWD with bf16 operands: W, Z and A N are rounded once, as operands of the scans; what their
+    // own operands' rounding leaves over takes part in forming them (formed from rounded operands
+    // they put dS0 at 2.5e-3 of the 64-bit result, with the rest 1.9e-3)
+    constexpr bool FINE = BWD && P == PREC_BF16;
+    auto rest_rows = [&](const float2 (&x)[4][4]) __attribute__((always_inline)) {   // of x G, to area 1
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            float2 y[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y[k] = rest(make_float2(x[u][k].x * Pf[u][k], x[u][k].y * Pf[u][k]));
+            put4<P>(w.r1 + (tsg * 4 + u) * PITCH + pc0 * ES, y);
+        }
+        wave_order();
+    };
+    [[maybe_unused]] Frag<P> ql[FINE ? 4 : 1], kl[FINE ? 4 : 1];
+    if constexpr (BWD) {                  // conj(K Q), rows tokens
+        out_rows(w.r1, kq_end, [&](int, int) { return 1.f; }, -1.f);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            if (kb >= nkb) break;
+            put_frag<P>(rec + A.bwd.kr + kb * frag, lane, lds_row<P>(w.r1, c, kb, g));
+        }
+        wave_order();
+    }
     out_rows(w.r1, qq, [&](int u, int k) { return Pf[u][k]; }, 1.f);
+    // BWD: by columns (conj(Q) G is then formed on as rows tokens, by channel on the lanes)
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) qf[kb] = lds_row<P>(w.r1, c, kb, g);
+    [[maybe_unused]] Frag<P> qc[BWD ? 4 : 1];
+    if constexpr (BWD) {
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) qc[kb] = lds_col<P>(w.r1, kb * 16 + c, g);
+    }
     wave_order();
+    if constexpr (FINE) {
+        rest_rows(qq);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) ql[kb] = lds_col<P>(w.r1, kb * 16 + c, g);
+        wave_order();
+        rest_rows(kq);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) kl[kb] = lds_col<P>(w.r1, kb * 16 + c, g);
+        wave_order();
+    }
     out_rows(w.r0, kq, [&](int u, int k) { return Pf[u][k]; }, 1.f);
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) kf[kb] = lds_row<P>(w.r0, c, kb, g);
@@ -475,24 +534,101 @@ __device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigne
         wave_order();
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const float b = w.beta[4 * k + g];
+            const float b = BWD ? 1.f : w.beta[4 * k + g];      // T = N D_beta (BWD: N)
             xs[c * 18 + 4 * k + g] = make_float2(nr[k] * b, ni[k] * b);
         }
         wave_order();
     }
     Frag<P> tf, af;                    // T[c][4g + r]; A[c][4g + r]
+    [[maybe_unused]] Frag<P> tl, al;
     {
         float2 x[4], y[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             x[r] = xs[c * 18 + 4 * g + r];
+            if constexpr (BWD) {
+                const float b = w.beta[4 * g + r];
+                x[r] = make_float2(x[r].x * b, x[r].y * b);
+            }
             const bool keep = 4 * g + r <= c;
             y[r] = make_float2(keep ? za.re[r] : 0.f, keep ? za.im[r] : 0.f);
         }
         tf = frag4<P>(x);
         af = frag4<P>(y);
+        if constexpr (FINE) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                x[r] = rest(x[r]);
+                y[r] = rest(y[r]);
+            }
+            tl = frag4<P>(x);
+            al = frag4<P>(y);
+        }
     }
     const Right<P> tr = right<P>(tf), ar = right<P>(af);
+
+    if constexpr (BWD) {
+        auto conj_frag = [&](const CAcc& z, float s) __attribute__((always_inline)) {    // s conj(z)
+            float2 x[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = make_float2(s * z.re[r], -s * z.im[r]);
+            return frag4<P>(x);
+        };
+        // x += (a + al) (b + bl), the rests' own product left out
+        auto fine = [&](CAcc& x, const Frag<P>& a, const Frag<P>& ar_, const Right<P>& b, const Right<P>& br_) __attribute__((always_inline)) {
+            cmma<P>(x, a, b);
+            if constexpr (FINE) {
+                cmma<P>(x, a, br_);
+                cmma<P>(x, ar_, b);
+            }
+        };
+        // T, N^* (bf16: without its diagonal of ones, which the scan adds in fp32), (A N)^*
+        float2 x[4], xc[4], xl[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            x[r] = xs[(4 * g + r) * 18 + c];                                    // N[4g + r][c]
+            xc[r] = FINE && c == 4 * g + r ? make_float2(0.f, 0.f) : make_float2(x[r].x, -x[r].y);
+            xl[r] = rest(x[r]);
+        }
+        CAcc an;
+        czero(an);
+        fine(an, af, al, right<P>(frag4<P>(x)), right<P>(frag4<P>(xl)));
+        put_frag<P>(rec + A.bwd.x, lane, tf);
+        put_frag<P>(rec + A.bwd.ns, lane, frag4<P>(xc));
+        put_frag<P>(rec + A.bwd.an, lane, conj_frag(an, 1.f));
+        // -W, -W^*, Z^*
+        const Right<P> tlr = right<P>(FINE ? tl : tf);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            if (kb >= nkb) break;
+            const Frag<P> kt = lds_col<P>(w.r0, kb * 16 + c, g), ktl = kl[FINE ? kb : 0];
+            CAcc a, b, z;
+            czero(a); czero(b);
+            fine(a, tf, tl, right<P>(kt), right<P>(ktl));                       // W (rows tokens)
+            fine(b, kt, ktl, tr, tlr);                                          // W^T
+            put_frag<P>(rec + kb * frag, lane, frag_acc<P>(b, -1.f));
+            put_frag<P>(rec + A.bwd.ws + kb * frag, lane, conj_frag(a, -1.f));
+            CAcc nw, nl;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float2 q = frag_get<P>(qc[kb], r);
+                if constexpr (FINE) {
+                    const float2 y = frag_get<P>(ql[kb], r), l = rest(make_float2(-a.re[r], -a.im[r]));
+                    q = make_float2(q.x + y.x, q.y + y.y);
+                    nl.re[r] = l.x;
+                    nl.im[r] = l.y;
+                }
+                z.re[r] = q.x;
+                z.im[r] = q.y;
+                nw.re[r] = -a.re[r];
+                nw.im[r] = -a.im[r];
+            }
+            if constexpr (!FINE) nl = nw;
+            fine(z, af, al, right_acc<P>(nw), right_acc<P>(nl));                // Z = conj(Q) G - A W (rows tokens)
+            put_frag<P>(rec + A.bwd.zs + kb * frag, lane, conj_frag(z, 1.f));
+        }
+        return;
+    }
 
     // ---- X and Y
     {
@@ -548,11 +684,11 @@ __device__ __forceinline__ void prep(PrepSmem<P>& sm, const PrepArgs& A, unsigne
     }
 }
 
-template <int P, typename TIN, bool DEC>
+template <int P, typename TIN, int KIND>
 __global__ __launch_bounds__(256, 2) void prep_kernel(PrepArgs A)
 {
     __shared__ __align__(16) PrepSmem<P> sm;
-    prep<P, TIN, DEC>(sm, A, blockIdx.x);
+    prep<P, TIN, KIND>(sm, A, blockIdx.x);
 }
 
 // ------------------------------------------------------------------ forward scans
@@ -817,7 +953,7 @@ __global__ __launch_bounds__(256, 1) void scan_prep_f32_kernel(ScanArgs S, PrepA
 {
     __shared__ __align__(16) struct { ScanF32Smem scan; PrepSmem<PREC_F32> prep; } sm;
     if (blockIdx.x < nscan) scan_f32<TIN, TOUT, false>(sm.scan, S, blockIdx.x);
-    else prep<PREC_F32, TIN, false>(sm.prep, N, blockIdx.x - nscan);
+    else prep<PREC_F32, TIN, Kind::FWD>(sm.prep, N, blockIdx.x - nscan);
 }
 
 // bf16 operands.  Workgroup: 32 value columns.  The state's chain and the outputs on different
@@ -1038,14 +1174,500 @@ __global__ __launch_bounds__(512, 1) void scan_bf16_kernel(ScanArgs A)
     }
 }
 
+// ------------------------------------------------------------------ backward scans
+// The forward scan recording the state entering every block and Delta, and the adjoint scan
+// (blocks in reverse) recording dL/dS leaving every block and G_F and writing dv and dS0; both in
+// one launch (they read the same records and are independent).
+struct BwdArgs {
+    const char* fac;
+    const void *v, *dO, *beta;
+    const float *S0, *dS_T;              // may be null (zero)
+    float* dS0;                          // may be null
+    float *S_rec, *G_rec, *D_rows, *F_rows;
+    void* dv;
+    long heads;
+    int T, m, n, n_slices, nchunks, nsteps;
+    BwdLayout lay;
+};
+
+// One scan's walk over its blocks: `dir` +1 or -1, resources of the step a block belongs to
+// (operands four blocks ahead), and the block's places in the outputs by 64-bit pointers that
+// move with it (m n 8 bytes per block may pass what a scalar offset holds).  Blocks past the end
+// of the sequence, in the last step, write nothing.
+struct Walk {
+    int nsteps, nchunks;
+    long tok, mn8, row8;
+    const char* fac;
+    long head;
+    __device__ __forceinline__ Walk(const BwdArgs& A, long bh) {
+        nsteps = A.nsteps;
+        nchunks = A.nchunks;
+        head = bh;
+        tok = bh * A.T;
+        mn8 = static_cast<long>(A.m) * A.n * 8;
+        row8 = static_cast<long>(A.n) * 8;
+        fac = A.fac + bh * A.nsteps * static_cast<long>(NB) * A.lay.block;
+    }
+    __device__ __forceinline__ bool in(int st) const { return st >= 0 && st < nsteps; }
+    __device__ __forceinline__ rsrc_t rec(const BwdArgs& A, int st, bool on) const {
+        return rsrc(fac + static_cast<long>(st) * (NB * A.lay.block), on && in(st) ? NB * A.lay.block : 0);
+    }
+    // rows of a [T][n] complex array of `es`-byte parts, from step st on
+    __device__ __forceinline__ rsrc_t rows(const BwdArgs& A, const void* p, int es, int st) const {
+        const int left = in(st) ? min(A.T - st * CP, CP) : 0;
+        return rsrc(static_cast<const char*>(p) + (tok + static_cast<long>(st) * CP) * A.n * 2 * es, left * A.n * 2 * es);
+    }
+    __device__ __forceinline__ rsrc_t state(const float* p, int ch) const {
+        return rsrc(reinterpret_cast<const char*>(p) + (head * nchunks + ch) * mn8, ch < nchunks ? static_cast<int>(mn8) : 0);
+    }
+    __device__ __forceinline__ rsrc_t chunk_rows(const float* p, int ch) const {
+        return rsrc(reinterpret_cast<const char*>(p) + (head * nchunks + ch) * 16 * row8, ch < nchunks ? static_cast<int>(16 * row8) : 0);
+    }
+};
+
+// fp32 operands: the forward scan's layout of work (8 value columns, one channel block per wave).
+struct BwdF32Smem { f32x4 red[2][2][4][64]; };
+template <typename TV, typename TO>
+__device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsigned wg, bool adj)
+{
+    auto& red = sm.red;
+    long bh;
+    int sl;
+    if (!scan_place(wg, A.n_slices, A.heads, bh, sl)) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, g = lane >> 4, qp = lane & 1;
+    const int n = A.n, m = A.m;
+    const int j = sl * FCOLS + (c >> 1);
+    const bool live = wave < A.lay.nkb;
+    const Walk wk(A, bh);
+    const u32 l16 = lane * 16;
+    const int so = wave * A.lay.frag;
+    const u32 lx = (wave >> 1) * 1024 + lane * 16 + (wave & 1) * 8;           // K index 4g + wave
+    auto mma1 = [&](f32x4& acc, float a, float b) __attribute__((always_inline)) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+    };
+    auto mma8 = [&](f32x4& acc, f32x4 a, f32x4 b, const Frag8& y) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) mma1(acc, s < 4 ? a[s & 3] : b[s & 3], y.v[s]);
+    };
+    // this wave's part of a state [m][n]: rows wave * 16 + 4g + r (past m they lie past the
+    // range), column j, part qp
+    u32 soff[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        soff[r] = j < n && live ? static_cast<u32>((((wave * 16 + 4 * g + r) * n + j) * 2 + qp) * 4) : OOR;
+    f32x4 S;
+    {
+        const float* init = adj ? A.dS_T : A.S0;
+        const rsrc_t rs = rsrc(init ? reinterpret_cast<const char*>(init) + bh * wk.mn8 : nullptr, init ? static_cast<int>(wk.mn8) : 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S[r] = ld_f32(rs, soff[r]);
+    }
+    auto put_state = [&](rsrc_t rs) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[r]), rs, soff[r], 0, 0);
+    };
+    const u32 roff = j < n ? static_cast<u32>(((4 * g + wave) * n + j) * 2 + qp) * 4 : OOR;    // row 4g + wave of a block
+    // S <- g S (adjoint: conj(g) S)
+    auto decay = [&](f32x4 g0, f32x4 g1, float s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float x = r < 2 ? g0[2 * r] : g1[2 * r - 4], y = s * (r < 2 ? g0[2 * r + 1] : g1[2 * r - 3]);
+            const float own = S[r], oth = partner(own);
+            S[r] = qp ? __builtin_fmaf(x, own, y * oth) : __builtin_fmaf(x, own, -y * oth);
+        }
+    };
+
+    if (!adj) {
+        const int row_v = n * 2 * static_cast<int>(sizeof(TV));
+        const u32 lv = j < n ? static_cast<u32>((4 * g + wave) * n + j) * 2 * static_cast<u32>(sizeof(TV)) : OOR;
+        struct Pre { f32x4 w0, w1, k0, k1, g0, g1; float2 x, v; };
+        Pre pre[NB];
+        struct Step { rsrc_t own, all, v; };
+        auto step_of = [&](int st) __attribute__((always_inline)) {
+            return Step{wk.rec(A, st, live), wk.rec(A, st, true), wk.rows(A, A.v, sizeof(TV), st)};
+        };
+        auto fetch_w = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+            const int at = b * A.lay.block;
+            p.w0 = ldv4(q.own, l16, at + so);
+            p.w1 = ldv4(q.own, l16 + 1024, at + so);
+            p.x = ldv2(q.all, lx, at + A.lay.x);
+            p.v = ld_cplx<TV>(q.v, lv, b * 16 * row_v);
+            LOAD_ORDER();
+        };
+        auto fetch_k = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+            const int at = b * A.lay.block;
+            p.g0 = ldv4(q.own, g * 32, at + A.lay.gc + wave * 128);
+            p.g1 = ldv4(q.own, g * 32 + 16, at + A.lay.gc + wave * 128);
+            p.k0 = ldv4(q.own, l16, at + so + A.lay.kq);
+            p.k1 = ldv4(q.own, l16 + 1024, at + so + A.lay.kq);
+            LOAD_ORDER();
+        };
+        Step cur = step_of(0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) { fetch_w(cur, b, pre[b]); fetch_k(cur, b, pre[b]); }
+        for (int st = 0; st < A.nsteps; ++st) {
+            const Step next = step_of(st + 1);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                Pre& p = pre[b];
+                const int ch = st * NB + b;
+                put_state(wk.state(A.S_rec, ch));
+                f32x4 pw = zero4();
+                mma1(pw, p.x.x, qp ? -p.v.y : p.v.x);        // conj(v) = (x, -y)
+                mma1(pw, p.x.y, qp ? p.v.x : p.v.y);
+                mma8(pw, p.w0, p.w1, bfrag_from_acc(S, qp));
+                fetch_w(next, b, p);
+                red[b & 1][0][wave][lane] = pw;
+                __syncthreads();
+                f32x4 d[4];
+#pragma unroll
+                for (int w2 = 0; w2 < 4; ++w2) d[w2] = red[b & 1][0][w2][lane];
+                decay(p.g0, p.g1, 1.f);
+                const f32x4 dd = (d[0] + d[1]) + (d[2] + d[3]);
+                mma8(S, p.k0, p.k1, bfrag_from_acc(dd, qp));
+                fetch_k(next, b, p);
+                const float mine = wave == 0 ? dd[0] : wave == 1 ? dd[1] : wave == 2 ? dd[2] : dd[3];
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(mine), wk.chunk_rows(A.D_rows, ch), roff, 0, 0);
+            }
+        }
+        return;
+    }
+
+    const int row_o = n * 2 * static_cast<int>(sizeof(TO));
+    auto ooff = [&](int r) { return j < n ? static_cast<u32>((4 * g + r) * n + j) * 2 * static_cast<u32>(sizeof(TO)) : OOR; };
+    struct Pre { f32x4 k0, k1, w0, w1, z0, z1, g0, g1; float2 ns, an, gw, u0, u1, u2, u3; };
+    Pre pre[NB];
+    struct Step { rsrc_t own, all, o; };
+    auto step_of = [&](int st) __attribute__((always_inline)) {
+        return Step{wk.rec(A, st, live), wk.rec(A, st, true), wk.rows(A, A.dO, sizeof(TO), st)};
+    };
+    auto fetch_k = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+        const int at = b * A.lay.block;
+        p.k0 = ldv4(q.own, l16, at + so + A.lay.kr);
+        p.k1 = ldv4(q.own, l16 + 1024, at + so + A.lay.kr);
+        LOAD_ORDER();
+    };
+    auto fetch_z = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+        const int at = b * A.lay.block, t = b * 16 * row_o;
+        p.g0 = ldv4(q.own, g * 32, at + A.lay.gc + wave * 128);
+        p.g1 = ldv4(q.own, g * 32 + 16, at + A.lay.gc + wave * 128);
+        p.u0 = ld_cplx<TO>(q.o, ooff(0), t);
+        p.u1 = ld_cplx<TO>(q.o, ooff(1), t);
+        p.u2 = ld_cplx<TO>(q.o, ooff(2), t);
+        p.u3 = ld_cplx<TO>(q.o, ooff(3), t);
+        p.z0 = ldv4(q.own, l16, at + so + A.lay.zs);
+        p.z1 = ldv4(q.own, l16 + 1024, at + so + A.lay.zs);
+        LOAD_ORDER();
+    };
+    auto fetch_w = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+        const int at = b * A.lay.block;
+        p.w0 = ldv4(q.own, l16, at + so + A.lay.ws);
+        p.w1 = ldv4(q.own, l16 + 1024, at + so + A.lay.ws);
+        p.ns = ldv2(q.all, lx, at + A.lay.ns);
+        p.an = ldv2(q.all, lx, at + A.lay.an);
+        p.gw = ld_cplx<TO>(q.o, ooff(wave), b * 16 * row_o);
+        LOAD_ORDER();
+    };
+    // G_F of block ch, whose shares lie in red[b & 1][1]: wave w sums rows 4g + w, records them
+    // and writes dv = conj(beta G_F)
+    const TV* const gb = static_cast<const TV*>(A.beta);
+    TV* const gdv = static_cast<TV*>(A.dv);
+    auto finish = [&](int b, int ch, bool some) __attribute__((always_inline)) {
+        float f = 0.f;
+#pragma unroll
+        for (int w2 = 0; w2 < 4; ++w2) f += reinterpret_cast<const float*>(&red[b & 1][1][w2][lane])[wave];
+        const int rows = some ? max(min(A.T - ch * 16, 16), 0) : 0;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f), wk.chunk_rows(A.F_rows, some ? ch : A.nchunks), roff, 0, 0);
+        const float bt = ld_real<TV>(rsrc(gb + wk.tok + ch * 16, rows * static_cast<int>(sizeof(TV))), (4 * g + wave) * static_cast<u32>(sizeof(TV)));
+        const rsrc_t rv = rsrc(gdv + 2 * (wk.tok + ch * 16) * n, rows * n * 2 * static_cast<int>(sizeof(TV)));
+        const float x = qp ? -bt * f : bt * f;
+        st_real<TV>(rv, j < n ? static_cast<u32>(((4 * g + wave) * n + j) * 2 + qp) * static_cast<u32>(sizeof(TV)) : OOR, 0, x);
+    };
+    Step cur = step_of(A.nsteps - 1);
+#pragma unroll
+    for (int b = NB - 1; b >= 0; --b) { fetch_k(cur, b, pre[b]); fetch_z(cur, b, pre[b]); fetch_w(cur, b, pre[b]); }
+    for (int st = A.nsteps - 1; st >= 0; --st) {
+        const Step next = step_of(st - 1);
+#pragma unroll
+        for (int b = NB - 1; b >= 0; --b) {
+            Pre& p = pre[b];
+            const int ch = st * NB + b;
+            put_state(wk.state(A.G_rec, ch));
+            f32x4 px = zero4();                              // share of X' = conj(K Q) G
+            mma8(px, p.k0, p.k1, bfrag_from_acc(S, qp));
+            fetch_k(next, b, p);
+            red[b & 1][0][wave][lane] = px;
+            __syncthreads();
+            f32x4 d[4];
+#pragma unroll
+            for (int w2 = 0; w2 < 4; ++w2) d[w2] = red[b & 1][0][w2][lane];
+            decay(p.g0, p.g1, -1.f);
+            {
+                Frag8 gr;                                    // G_R = conj(dL/do)
+                bpair(gr, 0, p.u0.x, -p.u0.y, qp);
+                bpair(gr, 1, p.u1.x, -p.u1.y, qp);
+                bpair(gr, 2, p.u2.x, -p.u2.y, qp);
+                bpair(gr, 3, p.u3.x, -p.u3.y, qp);
+                mma8(S, p.z0, p.z1, gr);
+            }
+            fetch_z(next, b, p);
+            const Frag8 xb = bfrag_from_acc((d[0] + d[1]) + (d[2] + d[3]), qp);
+            mma8(S, p.w0, p.w1, xb);
+            f32x4 pf = zero4();                              // share of G_F: K index 4g + wave
+            const float x0 = wave == 0 ? xb.v[0] : wave == 1 ? xb.v[2] : wave == 2 ? xb.v[4] : xb.v[6];
+            const float x1 = wave == 0 ? xb.v[1] : wave == 1 ? xb.v[3] : wave == 2 ? xb.v[5] : xb.v[7];
+            mma1(pf, p.ns.x, x0);
+            mma1(pf, p.ns.y, x1);
+            mma1(pf, p.an.x, qp ? -p.gw.y : p.gw.x);
+            mma1(pf, p.an.y, qp ? p.gw.x : p.gw.y);
+            finish((b + 1) % NB, ch + 1, ch + 1 < A.nsteps * NB);       // the block before this one in the walk
+            red[b & 1][1][wave][lane] = pf;
+            fetch_w(next, b, p);
+        }
+    }
+    __syncthreads();
+    finish(0, 0, true);
+    if (A.dS0 != nullptr) put_state(rsrc(reinterpret_cast<const char*>(A.dS0) + bh * wk.mn8, static_cast<int>(wk.mn8)));
+}
+template <typename TV, typename TO>
+__global__ __launch_bounds__(256, 2) void bwd_f32_kernel(BwdArgs A, unsigned nfwd)
+{
+    __shared__ BwdF32Smem sm;
+    const bool adj = blockIdx.x >= nfwd;
+    bwd_f32<TV, TO>(sm, A, adj ? blockIdx.x - nfwd : blockIdx.x, adj);
+}
+
+// bf16 operands: the forward scan's layout of work (32 value columns; state waves with half the
+// channels each, row waves that take Delta or X' from the exchange and write the rows).
+template <typename TO>
+__global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nfwd)
+{
+    constexpr int P = PREC_BF16;
+    __shared__ f32x4 red[2][4][2][64];                 // [parity][state wave][re, im][lane]
+    const bool adj = blockIdx.x >= nfwd;
+    long bh;
+    int sl;
+    if (!scan_place(adj ? blockIdx.x - nfwd : blockIdx.x, A.n_slices, A.heads, bh, sl)) return;
+    const int lane = threadIdx.x & 63;
+    const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3;
+    const int c = lane & 15, g = lane >> 4, h = wave & 1, cw = wave >> 1;
+    const int n = A.n, m = A.m;
+    const int j = sl * BCOLS + cw * 16 + c;
+    const Walk wk(A, bh);
+    const u32 l16 = lane * 16;
+    auto ldf = [&](rsrc_t r, u32 off, int s) __attribute__((always_inline)) {
+        Frag<P> f;
+        f.w = __builtin_amdgcn_raw_buffer_load_b128(r, off, s, 0);
+        return f;
+    };
+    // rows 4g + r of a block, complex bf16 (v, dL/do as bf16) or fp32 (records, dL/do as fp32)
+    u32 off4[4], off8[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        off4[r] = j < n ? static_cast<u32>((4 * g + r) * n + j) * 4u : OOR;
+        off8[r] = j < n ? static_cast<u32>((4 * g + r) * n + j) * 8u : OOR;
+    }
+    auto rows_frag = [&](rsrc_t q, int es, int b) __attribute__((always_inline)) {   // conj of a block's rows
+        Frag<P> f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (es == 2) {
+                f.w[r] = __builtin_amdgcn_raw_buffer_load_b32(q, off4[r], b * 16 * n * 4, 0);
+            } else {
+                const float2 x = ldv2(q, off8[r], b * 16 * n * 8);
+                f.w[r] = pack_bf16(x.x, x.y);
+            }
+        }
+        return f;
+    };
+    auto conj_right = [&](Frag<P> f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f.w[r] ^= 0x80000000u;
+        return right<P>(f);
+    };
+    const int st0 = adj ? A.nsteps - 1 : 0, dst = adj ? -1 : 1;
+
+    if (wave8 < 4) {
+        // ================================================ state waves
+        const bool live0 = 2 * h < A.lay.nkb, live1 = 2 * h + 1 < A.lay.nkb;
+        u32 soff[2][4];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = (2 * h + kb) * 16 + 4 * g + r;
+                soff[kb][r] = j < n && i < m ? static_cast<u32>(i * n + j) * 8u : OOR;
+            }
+        CAcc S[2];
+        {
+            const float* init = adj ? A.dS_T : A.S0;
+            const rsrc_t rs = rsrc(init ? reinterpret_cast<const char*>(init) + bh * wk.mn8 : nullptr, init ? static_cast<int>(wk.mn8) : 0);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float2 x = ld_c64(rs, soff[kb][r]);
+                    S[kb].re[r] = x.x;
+                    S[kb].im[r] = x.y;
+                }
+        }
+        auto put_state = [&](rsrc_t rs) __attribute__((always_inline)) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(S[kb].re[r]), __float_as_uint(S[kb].im[r])}, rs, soff[kb][r], 0, 0);
+        };
+        // a: the operand of the first product (-W; adjoint: conj(K Q)); k: of the second (K Q;
+        // adjoint: -W^*); z, rows: the term known beforehand (T conj(V); adjoint: Z^* G_R)
+        struct Pre { Frag<P> a[2], k[2], z[2], u; f32x4 g[2][2]; };
+        Pre pre[NB];
+        const int so = 2 * h * 1024, oa = adj ? A.lay.kr : 0, ok = adj ? A.lay.ws : A.lay.kq;
+        struct Step { rsrc_t own[2], x, u; };
+        auto step_of = [&](int st) __attribute__((always_inline)) {
+            return Step{{wk.rec(A, st, live0), wk.rec(A, st, live1)}, wk.rec(A, st, h == 0),
+                        adj ? wk.rows(A, A.dO, sizeof(TO), st) : wk.rows(A, A.v, 2, st)};
+        };
+        auto fetch_a = [&](const Step& q, int b, Pre& p) __attribute__((always_inline)) {
+            const int at = b * A.lay.block;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) p.a[kb] = ldf(q.own[kb], l16 + kb * 1024, at + so + oa);
+            LOAD_ORDER();
+        };
+        auto fetch_k = [&](const Step& q, int b, Pre& p, auto adj_c) __attribute__((always_inline)) {
+            constexpr bool ADJ = decltype(adj_c)::value;
+            const int at = b * A.lay.block;
+            p.u = rows_frag(q.u, ADJ ? static_cast<int>(sizeof(TO)) : 2, b);
+            if constexpr (!ADJ) p.z[0] = ldf(q.x, l16, at + A.lay.x);      // T, on the first half's wave
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) p.g[kb][e] = ldv4(q.own[kb], g * 32 + kb * 128 + e * 16, at + A.lay.gc + h * 256);
+                if constexpr (ADJ) p.z[kb] = ldf(q.own[kb], l16 + kb * 1024, at + so + A.lay.zs);
+                p.k[kb] = ldf(q.own[kb], l16 + kb * 1024, at + so + ok);
+            }
+            LOAD_ORDER();
+        };
+        auto walk = [&](auto adj_c) __attribute__((always_inline)) {
+            constexpr bool ADJ = decltype(adj_c)::value;
+            auto block = [&](int b, int ch, Pre& p, const Step& next) __attribute__((always_inline)) {
+                put_state(wk.state(ADJ ? A.G_rec : A.S_rec, ch));
+                const Right<P> ub = conj_right(p.u);
+                CAcc d;
+                czero(d);
+                if constexpr (!ADJ) cmma<P>(d, p.z[0], ub);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) cmma<P>(d, p.a[kb], right_acc<P>(S[kb]));
+                red[b & 1][wave][0][lane] = d.re;
+                red[b & 1][wave][1][lane] = d.im;
+                fetch_a(next, b, p);
+                __syncthreads();
+                const f32x4 ore = red[b & 1][wave ^ 1][0][lane], oim = red[b & 1][wave ^ 1][1][lane];
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {             // S <- g S (adjoint: conj(g) S)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float x = p.g[kb][r >> 1][2 * (r & 1)], y0 = p.g[kb][r >> 1][2 * (r & 1) + 1], y = ADJ ? -y0 : y0;
+                        const float a = S[kb].re[r], i = S[kb].im[r];
+                        S[kb].re[r] = __builtin_fmaf(x, a, -y * i);
+                        S[kb].im[r] = __builtin_fmaf(x, i, y * a);
+                    }
+                    if constexpr (ADJ) cmma<P>(S[kb], p.z[kb], ub);
+                }
+                d.re += ore;
+                d.im += oim;
+                const Right<P> db = right_acc<P>(d);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) cmma<P>(S[kb], p.k[kb], db);
+                fetch_k(next, b, p, adj_c);
+            };
+            Step cur = step_of(st0);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int b = ADJ ? NB - 1 - i : i;
+                fetch_a(cur, b, pre[b]);
+                fetch_k(cur, b, pre[b], adj_c);
+            }
+            for (int s = 0, st = st0; s < A.nsteps; ++s, st += dst) {
+                const Step next = step_of(st + dst);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    const int b = ADJ ? NB - 1 - i : i;
+                    block(b, st * NB + b, pre[b], next);
+                }
+            }
+        };
+        if (adj) walk(std::true_type{});
+        else walk(std::false_type{});
+        if (adj && A.dS0 != nullptr) put_state(rsrc(reinterpret_cast<const char*>(A.dS0) + bh * wk.mn8, static_cast<int>(wk.mn8)));
+    } else {
+        // ================================================ row waves: blocks of parity h
+        float* const rowrec = adj ? A.F_rows : A.D_rows;
+        struct Pre { Frag<P> ns, an, u; float b[4]; };
+        Pre pre[2];
+        const uint16_t* const gb = static_cast<const uint16_t*>(A.beta);
+        uint16_t* const gdv = static_cast<uint16_t*>(A.dv);
+        auto fetch = [&](int st, int b, Pre& p) __attribute__((always_inline)) {
+            const rsrc_t q = wk.rec(A, st, true);
+            const int at = b * A.lay.block;
+            p.ns = ldf(q, l16, at + A.lay.ns);
+            p.an = ldf(q, l16, at + A.lay.an);
+            p.u = rows_frag(wk.rows(A, A.dO, sizeof(TO), st), sizeof(TO), b);
+            const int rows = wk.in(st) ? max(min(A.T - (st * NB + b) * 16, 16), 0) : 0;
+            const rsrc_t qb = rsrc(gb + wk.tok + (st * NB + b) * 16, rows * 2);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p.b[r] = ld_real<uint16_t>(qb, (4 * g + r) * 2);
+            LOAD_ORDER();
+        };
+        if (adj) {
+            fetch(st0, NB - 2 + h, pre[1]);
+            fetch(st0, h, pre[0]);
+        }
+        for (int s = 0, st = st0; s < A.nsteps; ++s, st += dst) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                __syncthreads();
+                // (the walks meet parity b & 1 = i & 1 forwards and 1 - (i & 1) backwards)
+                const int par = adj ? 1 - (i & 1) : i & 1;
+                if (par != h) continue;
+                const int ch = st * NB + (adj ? NB - 1 - i : i);
+                CAcc d;
+                d.re = red[par][2 * cw][0][lane] + red[par][2 * cw + 1][0][lane];
+                d.im = red[par][2 * cw][1][lane] + red[par][2 * cw + 1][1][lane];
+                if (adj) {
+                    Pre& p = pre[(NB - 1 - i) >> 1];
+                    cmma<P>(d, p.ns, right_acc<P>(d));           // (N^* without its ones)
+                    cmma<P>(d, p.an, conj_right(p.u));
+                    const rsrc_t rv = rsrc(gdv + 2 * (wk.tok + ch * 16) * n, max(min(A.T - ch * 16, 16), 0) * n * 4);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)              // dv = conj(beta G_F)
+                        __builtin_amdgcn_raw_buffer_store_b32(pack_bf16(p.b[r] * d.re[r], -p.b[r] * d.im[r]), rv, off4[r], 0, 0);
+                    fetch(st - 1, ch - st * NB, p);
+                }
+                const rsrc_t rr = wk.chunk_rows(rowrec, ch);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(d.re[r]), __float_as_uint(d.im[r])}, rr, off8[r], 0, 0);
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------ launches
 
-template <int P, typename TIN, bool DEC>
-static hipError_t prep_t(const ChunkLaunch& L, const PrepArgs& a, hipStream_t st)
+template <int P, typename TIN, int KIND>
+static hipError_t prep_t(const PrepArgs& a, long heads, hipStream_t st)
 {
-    const long heads = static_cast<long>(L.B) * L.H;
-    hipLaunchKernelGGL((prep_kernel<P, TIN, DEC>), dim3(static_cast<unsigned>(heads * a.nsteps)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((prep_kernel<P, TIN, KIND>), dim3(static_cast<unsigned>(heads * a.nsteps)), dim3(256), 0, st, a);
     return hipGetLastError();
+}
+template <int KIND>
+static hipError_t prepare(const PrepArgs& a, long heads, bool bf, bool in_bf16, hipStream_t st)
+{
+    if (bf) return prep_t<PREC_BF16, uint16_t, KIND>(a, heads, st);
+    return in_bf16 ? prep_t<PREC_F32, uint16_t, KIND>(a, heads, st) : prep_t<PREC_F32, float, KIND>(a, heads, st);
 }
 
 template <bool DEC>
@@ -1101,14 +1723,7 @@ hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus
     ScanArgs sa{static_cast<const char*>(ws), L.v, L.o, L.S0, nullptr, heads, L.T, L.m, L.n, 0, 0, 0, RecLayout(L.m, bf, dec)};
     const int cols = bf ? BCOLS : FCOLS;
     sa.n_slices = (L.n + cols - 1) / cols;
-    PrepArgs pa{L.q, L.k, L.alpha, L.theta, L.beta, L.r, L.wbeta, static_cast<char*>(ws), L.T, L.m, 0, 0, sa.lay};
-    auto prepare = [&](const PrepArgs& p) {
-        if (dec)
-            return bf ? prep_t<PREC_BF16, uint16_t, true>(L, p, st)
-                      : L.in_bf16 ? prep_t<PREC_F32, uint16_t, true>(L, p, st) : prep_t<PREC_F32, float, true>(L, p, st);
-        return bf ? prep_t<PREC_BF16, uint16_t, false>(L, p, st)
-                  : L.in_bf16 ? prep_t<PREC_F32, uint16_t, false>(L, p, st) : prep_t<PREC_F32, float, false>(L, p, st);
-    };
+    PrepArgs pa{L.q, L.k, L.alpha, L.theta, L.beta, L.r, L.wbeta, static_cast<char*>(ws), L.T, L.m, 0, 0, sa.lay, BwdLayout(L.m, bf)};
     // float32 scans on at most half of the compute units: each piece's scan with the next one's
     // preparation beside it, the records in two halves of the workspace (H16 T65536: 3.86 ms
     // one after the other)
@@ -1131,7 +1746,8 @@ hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus
         sa.fac = at;
         sa.Sout = s + here < steps ? carry : L.S_T;
         hipError_t e = hipSuccess;
-        if (!beside || s == 0) e = prepare(pa);
+        if (!beside || s == 0)
+            e = dec ? prepare<Kind::DEC>(pa, heads, bf, L.in_bf16, st) : prepare<Kind::FWD>(pa, heads, bf, L.in_bf16, st);
         if (e != hipSuccess) return e;
         if (beside && after > 0) {
             pa.step0 = s + here;
@@ -1148,6 +1764,44 @@ hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus
         sa.Sin = carry;
     }
     return hipSuccess;
+}
+
+// ------------------------------------------------------------------ backward
+
+size_t bwd_factors_bytes(long heads, int T, int m, bool in_bf16)
+{
+    const long steps = (static_cast<long>(T) + fac::CP - 1) / fac::CP;
+    return static_cast<size_t>(heads) * steps * fac::NB * fac::BwdLayout(m, bf16_operands(in_bf16, m)).block;
+}
+
+// F: the forward's inputs, records and dv as in launch_bwd_scans (A the adjoint's)
+hipError_t launch_bwd_factored(const ChunkLaunch& F, const ChunkLaunch& L, void* ws, hipStream_t st)
+{
+    using namespace fac;
+    const bool bf = bf16_operands(F.in_bf16, F.m);
+    const long heads = static_cast<long>(F.B) * F.H;
+    const int steps = (F.T + CP - 1) / CP;
+    BwdArgs a{static_cast<const char*>(ws), F.v, L.dO, F.beta, F.S0, L.S0, L.S_T, F.ck_state, L.ck_state, F.ck_rows, L.ck_rows,
+              L.dv, heads, F.T, F.m, F.n, 0, (F.T + 15) / 16, steps, BwdLayout(F.m, bf)};
+    const int cols = bf ? BCOLS : FCOLS;
+    a.n_slices = (F.n + cols - 1) / cols;
+    const PrepArgs pa{F.q, F.k, F.alpha, F.theta, F.beta, nullptr, nullptr, static_cast<char*>(ws), F.T, F.m, 0, steps,
+                      RecLayout(F.m, bf, false), a.lay};
+    hipError_t e = prepare<Kind::BWD>(pa, heads, bf, F.in_bf16, st);
+    if (e != hipSuccess) return e;
+    const unsigned nfwd = static_cast<unsigned>(scan_grid(heads, a.n_slices));
+    const dim3 grid(2 * nfwd);
+    if (bf) {
+        if (F.out_bf16) hipLaunchKernelGGL((bwd_bf16_kernel<uint16_t>), grid, dim3(512), 0, st, a, nfwd);
+        else hipLaunchKernelGGL((bwd_bf16_kernel<float>), grid, dim3(512), 0, st, a, nfwd);
+    } else if (F.in_bf16) {
+        if (F.out_bf16) hipLaunchKernelGGL((bwd_f32_kernel<uint16_t, uint16_t>), grid, dim3(256), 0, st, a, nfwd);
+        else hipLaunchKernelGGL((bwd_f32_kernel<uint16_t, float>), grid, dim3(256), 0, st, a, nfwd);
+    } else {
+        if (F.out_bf16) hipLaunchKernelGGL((bwd_f32_kernel<float, uint16_t>), grid, dim3(256), 0, st, a, nfwd);
+        else hipLaunchKernelGGL((bwd_f32_kernel<float, float>), grid, dim3(256), 0, st, a, nfwd);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace sfda

@@ -25,7 +25,8 @@ EXPORTS = ("sfda_chunk_fwd", "sfda_chunk_fwd_sliced", "sfda_chunk_fwd_gated", "s
            "sfda_chunk_fwd_factored", "sfda_chunk_fwd_decoupled_factored",
            "sfda_chunk_fwd_factored_workspace_bytes", "sfda_chunk_fwd_segmented", "sfda_chunk_fwd_segmented_noalloc",
            "sfda_chunk_fwd_segmented_workspace_bytes", "sfda_chunk_fwd_auto_segments",
-           "sfda_chunk_bwd", "sfda_chunk_bwd_workspace_bytes", "sfda_chunk_solve_monitor",
+           "sfda_chunk_bwd", "sfda_chunk_bwd_workspace_bytes",
+           "sfda_chunk_bwd_factored_workspace_bytes", "sfda_chunk_solve_monitor",
            "sfda_step", "sfda_status_string", "sfda_abi_version")
 
 _lib = None
@@ -91,6 +92,8 @@ def load_library(path: str = LIB_PATH):
     lib.sfda_chunk_bwd.restype = i
     lib.sfda_chunk_bwd_workspace_bytes.argtypes = [i] * 6
     lib.sfda_chunk_bwd_workspace_bytes.restype = ctypes.c_size_t
+    lib.sfda_chunk_bwd_factored_workspace_bytes.argtypes = [i] * 7
+    lib.sfda_chunk_bwd_factored_workspace_bytes.restype = ctypes.c_size_t
     lib.sfda_step.argtypes = [vp] * 8 + [i] * 4 + [i, i, vp]
     lib.sfda_step.restype = i
     lib.sfda_status_string.argtypes = [i]
@@ -353,7 +356,7 @@ def chunk_bwd(q, k, v, alpha, theta, beta, S0, dO, dS_T=None, C: int = 64, *,
     Inputs as chunk_fwd.  Returns dq, dk, dv, dalpha, dtheta, dbeta in the inputs' dtype and
     dS0 (float32, or None without want_dS0); complex gradients are dL/dRe + i dL/dIm.
     `workspace`: a uint8 device tensor of at least bwd_workspace_bytes(...) bytes, allocated
-    here when not given."""
+    here when not given (at sfda_chunk_bwd_factored_workspace_bytes, where the call is fastest)."""
     import torch
     lib = load_library()
     B, H, T, m, _ = _dims(q, v, 5)
@@ -370,9 +373,10 @@ def chunk_bwd(q, k, v, alpha, theta, beta, S0, dO, dS_T=None, C: int = 64, *,
     g = dict(dq=torch.empty_like(q), dk=torch.empty_like(k), dv=torch.empty_like(v),
              dalpha=torch.empty_like(alpha), dtheta=torch.empty_like(theta), dbeta=torch.empty_like(beta),
              dS0=torch.empty((B, H, m, n, 2), dtype=torch.float32, device=q.device) if want_dS0 else None)
-    nws = lib.sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C)
     if workspace is None:
-        workspace = torch.empty(max(nws, 1), dtype=torch.uint8, device=q.device)
+        nws = max(lib.sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C),
+                  lib.sfda_chunk_bwd_factored_workspace_bytes(B, H, T, m, n, C, in_code))
+        workspace = _workspace(max(nws, 1), q.device, stream)
     _check(dict(q=(q, (B, H, T, m, 2)), workspace=(workspace, tuple(workspace.shape))))
     st = lib.sfda_chunk_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(beta), _ptr(S0),
                             _ptr(dO), _ptr(dS_T), _ptr(g["dq"]), _ptr(g["dk"]), _ptr(g["dv"]),

@@ -12,7 +12,7 @@ import ctypes
 import numpy as np
 import pytest
 
-from gpu_util import I, ensure_built, rel_err, run_oracle, to_complex, upload
+from gpu_util import I, ensure_built, rel_err, run_oracle, to_complex, to_device, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -116,3 +116,41 @@ def test_bad_gate_gives_nan_from_its_block_on(lib, field, bad):
     assert np.all(np.isnan(o[0, 1, 48:])) and np.all(np.isnan(S[0, 1]))
     assert rel_err(o[0, 1, :48], o_ref[0, 1, :48]) <= 1e-4 and rel_err(o[0, 0], o_ref[0, 0]) <= 1e-4
     assert np.all(np.isfinite(S[0, 0]))
+
+
+@pytest.mark.parametrize("dtype,out", [("f32", "f32"), ("f32", "bf16"), ("bf16", "bf16"), ("bf16", "f32")])
+@pytest.mark.parametrize("B,H,T,m,n", [
+    (2, 4, 1, 64, 64), (1, 2, 16, 16, 8), (2, 5, 17, 17, 9), (1, 3, 63, 33, 33), (1, 8, 64, 48, 32),
+    (3, 3, 65, 64, 65), (1, 9, 129, 5, 7), (1, 2, 200, 47, 1), (1, 1, 130, 3, 40), (2, 1, 96, 62, 96),
+])
+def test_backward_edges(lib, B, H, T, m, n, dtype, out):
+    """sfda_chunk_bwd with the workspace of its scans on prepared operands and with the smaller
+    one (scans in place), each poisoned: both against the oracle, at the bars of the backward's tests
+    (1e-4 float32, 2e-2 bfloat16 inputs or dL/do).  Those are relative to a gradient's largest
+    entry, so no case has one token alone: its one dbeta is a sum of n products of either sign, each
+    in error by up to 2^-8 of its size, and nothing bounds the sum from below."""
+    import torch
+    from oracle import backward as BW
+    from paper_2607_11897_amd import sfda
+    x = I.make_chunk_inputs(I.Workload("edge", B, H, T, m, n, 64, dtype, I.LAWS_MAIN, 970 + T + m, 1e-4))
+    dO, dS = I.make_cotangents(B, H, T, m, n, out, seed=980 + T)
+    d = upload(x)
+    dO_t, dS_t = to_device(I.to_storage(dO, out), out), to_device(I.to_storage(dS, "f32"), "f32")
+    ref = BW.recurrence_backward(x.q, x.k, x.v, x.alpha, x.theta, x.beta, x.S0, dO, dS)
+    code = sfda.SFDA_F32 if dtype == "f32" else sfda.SFDA_BF16
+    full = lib.sfda_chunk_bwd_factored_workspace_bytes(B, H, T, m, n, 64, code)
+    least = sfda.bwd_workspace_bytes(B, H, T, m, n, 64)
+    assert full > least
+    tol = 2e-2 if "bf16" in (dtype, out) else 1e-4
+    for size in (full, least):
+        say("backward", (B, H, T, m, n), dtype, out, size)
+        g = sfda.chunk_bwd(d["q"], d["k"], d["v"], d["alpha"], d["theta"], d["beta"], d["S0"], dO_t, dS_t,
+                           workspace=torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        errs = {}
+        for name, t in g.items():
+            got = to_complex(t) if t.shape[-1] == 2 and name in ("dq", "dk", "dv", "dS0") else t.double().cpu().numpy()
+            assert np.all(np.isfinite(got)), name
+            errs[name] = rel_err(got, ref[name])
+        say({k: f"{e:.2e}" for k, e in errs.items()})
+        assert max(errs.values()) <= tol, errs
