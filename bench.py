@@ -511,7 +511,7 @@ def backward(args):
         dO_t = up(I.to_storage(dO, w.dtype), w.dtype)
         dS_t = up(I.to_storage(dS, "f32"), "f32")
         B, H, T, m, n = x.shape
-        ws = torch.empty(sfda.bwd_workspace_bytes(B, H, T, m, n, C_BWD), dtype=torch.uint8, device="cuda")
+        ws = torch.empty(sfda.bwd_auto_workspace_bytes(B, H, T, m, n, C_BWD, w.dtype), dtype=torch.uint8, device="cuda")
         stream = torch.cuda.current_stream()
 
         def run():
@@ -618,7 +618,8 @@ def decoupled(args):
 
 def bwd_hash() -> str:
     h = hashlib.sha256()
-    for p in ("paper_2607_11897_amd/csrc/sfda_chunk.hip", "paper_2607_11897_amd/csrc/sfda_chunk_grad.hip",
+    for p in ("paper_2607_11897_amd/csrc/sfda_factored.hip", "paper_2607_11897_amd/csrc/sfda_factored.h",
+              "paper_2607_11897_amd/csrc/sfda_grad.hip", "paper_2607_11897_amd/csrc/sfda_frag.h",
               "paper_2607_11897_amd/csrc/sfda_chunk_common.h", "paper_2607_11897_amd/csrc/sfda_device.h"):
         with open(os.path.join(ROOT, p), "rb") as f:
             h.update(f.read())

@@ -193,6 +193,14 @@ sfda_status_t sfda_chunk_fwd_decoupled(const void* q, const void* k, const void*
 size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n,
                                                sfda_dtype_t in_dtype, int decoupled);
 
+/*
+ * sfda_chunk_fwd_auto_factored -- 1 where the factored forward (decoupled: the write-decoupled one)
+ * is the faster one on the current device, 0 where the one-launch entry point is: short sequences,
+ * many heads in float32, and bfloat16 inputs without decoupling.
+ */
+int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, sfda_dtype_t in_dtype,
+                                 int decoupled);
+
 sfda_status_t sfda_chunk_fwd_factored(const void* q, const void* k, const void* v,
                                       const void* alpha, const void* theta, const void* beta,
                                       const float* S0, void* o, float* S_T,
@@ -314,13 +322,13 @@ sfda_status_t sfda_chunk_fwd_segmented(const void* q, const void* k, const void*
 size_t sfda_chunk_bwd_workspace_bytes(int B, int H, int T, int m, int n, int C);
 
 /*
- * sfda_chunk_bwd_factored_workspace_bytes -- the workspace at which sfda_chunk_bwd prepares its
- * scans' operands for all blocks in parallel (as sfda_chunk_fwd_factored does; faster, the same
- * gradients up to rounding): at least sfda_chunk_bwd_workspace_bytes; 0 where there is none
- * (sizes sfda_chunk_bwd refuses, and T == 0).
+ * sfda_chunk_bwd_auto_workspace_bytes -- the workspace at which sfda_chunk_bwd is fastest on the
+ * current device, at least sfda_chunk_bwd_workspace_bytes (0 where that is): with more, where the
+ * sequence is not short, the call prepares its scans' operands for all blocks in parallel (as
+ * sfda_chunk_fwd_factored does; the same gradients up to rounding) and records fewer states.
  */
-size_t sfda_chunk_bwd_factored_workspace_bytes(int B, int H, int T, int m, int n, int C,
-                                               sfda_dtype_t in_dtype);
+size_t sfda_chunk_bwd_auto_workspace_bytes(int B, int H, int T, int m, int n, int C,
+                                           sfda_dtype_t in_dtype);
 
 sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const void* alpha,
                              const void* theta, const void* beta, const float* S0,

@@ -13,8 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsfda.so")
 POISON_LIB = os.path.join(HERE, "libsfda_poison.so")
 SOURCES = ["sfda_api.hip", "sfda_chunk.hip", "sfda_chunk_grad.hip", "sfda_chunk_bf16.hip", "sfda_segments.hip",
-           "sfda_factored.hip",
-           "sfda_step.hip"]
+           "sfda_factored.hip", "sfda_grad.hip", "sfda_step.hip"]
 ARCH = "gfx950"
 JOBS = 8
 

@@ -1,6 +1,7 @@
 // C-ABI entry points of libsfda: argument validation, then one kernel launch.
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/sfda.h"
@@ -87,6 +88,43 @@ int auto_slice(long BH, int n)
 bool factored_fits(long BH, int n)
 {
     return (BH + 7) * ((n + 7) / 8) <= 0x7FFFFFFFL && static_cast<long>(64) * n * 8 < 0x80000000L;
+}
+
+// Whether the factored forward is the faster one.  It costs two launches and, per 64-token step,
+// time that grows with heads x value columns (x channel blocks); the scan in place costs one launch
+// and a chain of blocks per workgroup of a head and 64 columns, the same up to one workgroup per
+// compute unit.  Measured on MI355X (us, in place / factored):
+//  * short sequences pay the second launch: float32 T 32 20/23, T 48 22/23, T 64 28/23;
+//    decoupled float32 T 32 23/24, T 48 32/24, bfloat16 T 48 21/24, T 64 26/24;
+//  * with many heads a step costs more than the few blocks of the chain: float32 m n 64, 96 heads
+//    T 80 35/41, T 96 41/41, 128 heads T 96 41/44, T 128 52/44 (decoupled 96 heads T 48 33/39, T 80
+//    51/50, 128 heads T 80 51/55, T 96 60/56);
+//  * in float32, workgroups that fill whole rounds of the chip leave the chain nothing to wait for:
+//    m n 64 T 512, 192 heads 256/217, 256 heads 265/286, 384 heads 517/456, 512 heads 524/590;
+//    fewer channels or columns never get there (m 16, 256 heads 257/203; n 32, 189/151).
+bool fills_rounds(long BH, int m, int n, long cus)
+{
+    const long rounds = (BH * ((n + 63L) / 64) + cus - 1) / cus;
+    return BH * ((n + 7L) / 8) * ((m + 15) / 16) >= 0.92 * 32 * static_cast<double>(cus * rounds);
+}
+bool factored_faster(long BH, int T, int m, int n, bool bf16, bool dec)
+{
+    if (T <= (dec && !bf16 ? 32 : 48)) return false;
+    if (bf16) return true;
+    const long cus = device_cus() > 0 ? device_cus() : 256;
+    const long cols = (static_cast<long>(n) + 7) / 8;
+    if (T <= (dec ? 80 : 96) && BH * cols >= 3 * cus) return false;
+    return !fills_rounds(BH, m, n, cus);
+}
+// and the backward on prepared operands (three launches; two in place): float32 T 16 34/35, T 32
+// 42/35, 64 heads m n 64 T 32 46/53, T 48 56/53, 96 heads T 80 83/97, T 96 108/97, 128 heads T 96
+// 111/117, T 128 138/119, 256 heads T 256 511/530; bfloat16 T 32 30/33, T 48 34/34,
+// T 64 40/34
+bool bwd_factored_faster(long BH, int T, int m, int n, bool bf16)
+{
+    if (bf16) return T > 48;
+    const long cus = device_cus() > 0 ? device_cus() : 256, cols = BH * ((n + 7L) / 8);
+    return T > (cols >= 4 * cus ? 96 : cols >= 3 * cus ? 80 : cols >= 2 * cus ? 32 : 16) && !fills_rounds(BH, m, n, cus);
 }
 // most bytes of operand records that the suggested workspace holds at a time (the sequence then
 // runs in pieces; the records of one piece also stay within reach of the 256 MiB last-level
@@ -290,6 +328,13 @@ size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n
     const long BH = static_cast<long>(B) * H;
     if (!factored_fits(BH, n)) return 0;
     return sfda::factored_bytes(BH, T, m, n, in_dtype == SFDA_BF16, decoupled != 0, FACTORED_CAP);
+}
+
+int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, sfda_dtype_t in_dtype, int decoupled)
+{
+    if (sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_dtype, decoupled) == 0) return 0;
+    if (in_dtype == SFDA_BF16 && !decoupled) return 0;     // sfda_chunk_fwd's bfloat16 kernel is the faster one
+    return factored_faster(static_cast<long>(B) * H, T, m, n, in_dtype == SFDA_BF16, decoupled != 0) ? 1 : 0;
 }
 
 // the checks of both factored entry points past sfda_chunk_fwd's, then the launches
@@ -504,13 +549,21 @@ size_t sfda_chunk_bwd_workspace_bytes(int B, int H, int T, int m, int n, int C)
     return chunks * (2 * static_cast<size_t>(m) * n + 2 * static_cast<size_t>(C) * n) * 8;
 }
 
-size_t sfda_chunk_bwd_factored_workspace_bytes(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype)
+// the workspace of the backward on prepared operands, 0 where the call never takes it
+static size_t bwd_factored_need(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype)
 {
     const size_t need = sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C);
     const long BH = static_cast<long>(B) * H;
-    // (twice the forward's scans in one launch)
-    if (need == 0 || !dtype_ok(in_dtype) || !factored_fits(2 * BH + 8, n)) return 0;
-    return (need + 255) / 256 * 256 + sfda::bwd_factors_bytes(BH, T, m, in_dtype == SFDA_BF16);
+    if (need == 0 || !dtype_ok(in_dtype) || !sfda::bwd_factored_fits(BH, T, n) ||
+        !bwd_factored_faster(BH, T, m, n, in_dtype == SFDA_BF16))
+        return 0;
+    return std::max(need, sfda::bwd_factored_bytes(BH, T, m, n, in_dtype == SFDA_BF16));
+}
+
+size_t sfda_chunk_bwd_auto_workspace_bytes(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype)
+{
+    const size_t factored = bwd_factored_need(B, H, T, m, n, C, in_dtype);
+    return factored ? factored : sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C);
 }
 
 sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const void* alpha,
@@ -563,7 +616,7 @@ sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const 
     }
     // the factored scans, where the workspace has room for the operand records (a caller's
     // tensors past the needed bytes, inside workspace_bytes, are none of its own: scans in place)
-    const size_t facs = sfda_chunk_bwd_factored_workspace_bytes(B, H, T, m, n, requested_C, in_dtype);
+    const size_t facs = bwd_factored_need(B, H, T, m, n, requested_C, in_dtype);
     bool factored = facs > 0 && workspace_bytes >= facs;
     const Range whole = range_of(workspace, static_cast<long>(facs));
     if (factored) {
@@ -587,18 +640,16 @@ sfda_status_t sfda_chunk_bwd(const void* q, const void* k, const void* v, const 
     sfda::ChunkLaunch F = L;
     F.S0 = S0; F.S_T = nullptr; F.ck_state = S_rec; F.ck_rows = D_rows;
     L.S0 = dS_T; L.S_T = dS0; L.ck_state = G_rec; L.ck_rows = F_rows; L.dO = dO; L.dv = dv;
-    const hipError_t scans = factored ? sfda::launch_bwd_factored(F, L, static_cast<char*>(workspace) + (need + 255) / 256 * 256, st)
-                                      : sfda::launch_bwd_scans(F, L, st);
-    if (scans != hipSuccess) return SFDA_ERR_HIP;
-    if (!need_inputs) return SFDA_OK;
     sfda::GradLaunch Gl;
     Gl.q = q; Gl.k = k; Gl.v = v; Gl.alpha = alpha; Gl.theta = theta; Gl.beta = beta; Gl.dO = dO;
     Gl.S_rec = S_rec; Gl.G_rec = G_rec; Gl.D_rows = D_rows; Gl.F_rows = F_rows;
     Gl.dq = dq; Gl.dk = dk; Gl.dalpha = dalpha; Gl.dtheta = dtheta; Gl.dbeta = dbeta;
     Gl.B = B; Gl.H = H; Gl.T = T; Gl.m = m; Gl.n = n; Gl.C = C;
     Gl.in_bf16 = L.in_bf16; Gl.out_bf16 = L.out_bf16;
-    if (sfda::launch_chunk_grad(Gl, st) != hipSuccess) return SFDA_ERR_HIP;
-    return SFDA_OK;
+    if (factored) return sfda::launch_bwd_factored(F, L, Gl, workspace, st) == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
+    if (sfda::launch_bwd_scans(F, L, st) != hipSuccess) return SFDA_ERR_HIP;
+    if (!need_inputs) return SFDA_OK;
+    return sfda::launch_chunk_grad(Gl, st) == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
 }
 
 sfda_status_t sfda_chunk_solve_monitor(const void* k, const void* alpha, const void* theta,

@@ -84,5 +84,34 @@ struct BwdLayout {
     }
 };
 
+// What the backward's scans leave for the gradient kernel, per head:
+//   states: S entering and dL/dS leaving every grad_blocks() blocks, fp32, as right operands over
+//     the value columns: [channel block][column block of 16][lane (c, g)][4] complex, channel c,
+//     columns 4g .. 4g + 3;
+//   rows: Delta and G_F of every block.  bf16 operands: as they enter the products, pairs in
+//     column fragments [column block][lane (c, g)][4], column c, tokens 4g .. 4g + 3 (rounding
+//     them here is the rounding every use of them makes); fp32: [token][column].
+// The gradient kernel walks from a run's ends to its blocks, three matrix products per block.  In
+// fp32 (32 cycles an instruction, and the SIMD issues nothing beside it) that costs more than
+// recording every block.  bf16, B8 H16 T4096 m n 64: runs of 1, 2, 4 blocks: scans 1150, 795, 615 us
+// (what they write), gradients 720, 670, 1060-1570 (four blocks' sums do not fit the registers).
+__host__ __device__ constexpr int grad_blocks(bool bf16) { return bf16 ? 2 : 1; }
+struct GradLayout {
+    int nkb, ncb, recs;                  // recs: state records per head
+    int state, rows;                     // bytes of a state record, of a block's rows
+    long blocks;                         // blocks per head (whole 64-token steps)
+    __host__ __device__ GradLayout(int T, int m, int n, bool bf16) {
+        nkb = (m + 15) / 16;
+        ncb = (n + 15) / 16;
+        blocks = (static_cast<long>(T) + CP - 1) / CP * NB;
+        recs = static_cast<int>(blocks / grad_blocks(bf16));
+        state = nkb * ncb * 2048;
+        rows = ncb * (bf16 ? 1024 : 2048);
+    }
+    __host__ __device__ size_t bytes(long heads) const {
+        return static_cast<size_t>(heads) * 2 * (static_cast<size_t>(recs) * state + static_cast<size_t>(blocks) * rows);
+    }
+};
+
 }  // namespace fac
 }  // namespace sfda

@@ -2,124 +2,11 @@
 // the preparing kernel and the scans.
 #include <type_traits>
 
-#include "sfda_chunk_common.h"
 #include "sfda_factored.h"
+#include "sfda_frag.h"
 
 namespace sfda {
 namespace fac {
-
-typedef uint32_t u32;
-typedef u32 u32x2 __attribute__((ext_vector_type(2)));
-typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// LDS written and read by one wave: its LDS instructions run in order, so only the compiler has
-// to keep the order
-__device__ __forceinline__ void wave_order() { asm volatile("" ::: "memory"); }
-
-// two floats -> (lo, hi) bf16 pair, round to nearest even
-__device__ __forceinline__ u32 pack_bf16(float lo, float hi) {
-    const f32x2 v = {lo, hi};
-    return __builtin_bit_cast(u32, __builtin_convertvector(v, bf16x2));
-}
-__device__ __forceinline__ float bf_lo(u32 w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf_hi(u32 w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// wave-uniform size kept in a scalar register (a size in a vector register turns every access
-// into a loop over the wave's descriptors)
-__device__ __forceinline__ rsrc_t rsrc(const void* base, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, __builtin_amdgcn_readfirstlane(bytes),
-                                             0x00020000);
-}
-__device__ __forceinline__ u32x4 ld128(rsrc_t r, u32 off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
-
-// ------------------------------------------------------------------ complex matrix operands
-// A complex 16 x 16 result is two accumulator tiles (real and imaginary part; lane (c, g) holds
-// rows 4g + r of column c).  A fragment holds 4 consecutive K entries of one row (left operand)
-// or of one column (right operand) as (re, im) pairs; a right operand enters one product per
-// output part, as (Re, -Im) and as (Im, Re).
-struct CAcc { f32x4 re, im; };
-__device__ __forceinline__ void czero(CAcc& z) { z.re = zero4(); z.im = zero4(); }
-
-template <int P> struct Frag;
-template <> struct Frag<PREC_BF16> { u32x4 w; };
-template <> struct Frag<PREC_F32> { float2 x[4]; };
-template <int P> struct Right;
-template <> struct Right<PREC_BF16> { u32x4 re, im; };
-template <> struct Right<PREC_F32> { float re[4], im[4], nim[4]; };
-
-template <int P> __device__ __forceinline__ Frag<P> frag4(const float2 (&x)[4]) {
-    Frag<P> f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        if constexpr (P == PREC_BF16) f.w[r] = pack_bf16(x[r].x, x[r].y);
-        else f.x[r] = x[r];
-    }
-    return f;
-}
-// s = -1 negates
-template <int P> __device__ __forceinline__ Frag<P> frag_acc(const CAcc& z, float s = 1.f) {
-    float2 x[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) x[r] = make_float2(s * z.re[r], s * z.im[r]);
-    return frag4<P>(x);
-}
-// what the rounding of x to a fragment leaves over
-__device__ __forceinline__ float2 rest(float2 x) {
-    const uint32_t w = pack_bf16(x.x, x.y);
-    return make_float2(x.x - bf_lo(w), x.y - bf_hi(w));
-}
-template <int P> __device__ __forceinline__ float2 frag_get(const Frag<P>& f, int r) {
-    if constexpr (P == PREC_BF16) return make_float2(bf_lo(f.w[r]), bf_hi(f.w[r]));
-    else return f.x[r];
-}
-template <int P> __device__ __forceinline__ Right<P> right(const Frag<P>& f) {
-    Right<P> b;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        if constexpr (P == PREC_BF16) {
-            b.re[r] = f.w[r] ^ 0x80000000u;
-            b.im[r] = __builtin_amdgcn_alignbit(f.w[r], f.w[r], 16);
-        } else {
-            b.re[r] = f.x[r].x;
-            b.im[r] = f.x[r].y;
-            b.nim[r] = -f.x[r].y;
-        }
-    }
-    return b;
-}
-// right operand from a split accumulator
-template <int P> __device__ __forceinline__ Right<P> right_acc(const CAcc& y) {
-    Right<P> b;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        if constexpr (P == PREC_BF16) {
-            b.re[r] = pack_bf16(y.re[r], -y.im[r]);
-            b.im[r] = pack_bf16(y.im[r], y.re[r]);
-        } else {
-            b.re[r] = y.re[r];
-            b.im[r] = y.im[r];
-            b.nim[r] = -y.im[r];
-        }
-    }
-    return b;
-}
-// z += X Y over 16 complex K indices
-template <int P> __device__ __forceinline__ void cmma(CAcc& z, const Frag<P>& a, const Right<P>& b) {
-    if constexpr (P == PREC_BF16) {
-        z.re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.w), __builtin_bit_cast(bf16x8, b.re), z.re, 0, 0, 0);
-        z.im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.w), __builtin_bit_cast(bf16x8, b.im), z.im, 0, 0, 0);
-    } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            z.re = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[r].x, b.re[r], z.re, 0, 0, 0);
-            z.im = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[r].x, b.im[r], z.im, 0, 0, 0);
-            z.re = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[r].y, b.nim[r], z.re, 0, 0, 0);
-            z.im = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[r].y, b.re[r], z.im, 0, 0, 0);
-        }
-    }
-}
 
 // ------------------------------------------------------------------ preparing kernel
 // One wave per 16-token block: everything after the phase totals stays inside the wave, so the
@@ -175,16 +62,6 @@ template <int P> __device__ __forceinline__ void put4(char* p, const float2 (&x)
         *reinterpret_cast<float4*>(p + 16) = make_float4(x[2].x, x[2].y, x[3].x, x[3].y);
     }
 }
-// a lane's entries of a fragment in the records' order
-template <int P> __device__ __forceinline__ void put_frag(char* f, int lane, const Frag<P>& x) {
-    if constexpr (P == PREC_BF16) {
-        *reinterpret_cast<u32x4*>(f + lane * 16) = x.w;
-    } else {
-        *reinterpret_cast<float4*>(f + lane * 16) = make_float4(x.x[0].x, x.x[0].y, x.x[1].x, x.x[1].y);
-        *reinterpret_cast<float4*>(f + 1024 + lane * 16) = make_float4(x.x[2].x, x.x[2].y, x.x[3].x, x.x[3].y);
-    }
-}
-
 template <typename TIN, bool WIDE>
 __device__ __forceinline__ void load4r(rsrc_t rs, u32 e, int left, float (&x)[4])
 {
@@ -721,19 +598,6 @@ __device__ __forceinline__ bool scan_place(unsigned w, int S, long heads, long& 
 }
 static long scan_grid(long heads, int S) { return (heads >= 8 ? (heads + 7) / 8 * 8 : heads) * S; }
 
-template <typename TOUT> __device__ __forceinline__ void st_real(rsrc_t r, u32 off, int s, float x) {
-    if constexpr (sizeof(TOUT) == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, off, s, 0);
-    else __builtin_amdgcn_raw_buffer_store_b16(static_cast<uint16_t>(pack_bf16(x, 0.f)), r, off, s, 0);
-}
-template <typename TV> __device__ __forceinline__ float2 ld_cplx(rsrc_t r, u32 off, int s) {
-    if constexpr (sizeof(TV) == 4) {
-        return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, s, 0));
-    } else {
-        const u32 w = __builtin_amdgcn_raw_buffer_load_b32(r, off, s, 0);
-        return make_float2(bf_lo(w), bf_hi(w));
-    }
-}
-
 // What the scans share: the piece's tokens, and one step's resources.  A block's offset in them is
 // scalar, and a step past the end is an empty range (loads read zero, stores drop).  Every step
 // has four blocks: those past the end of the sequence hold identity tokens (no change of the
@@ -755,15 +619,6 @@ struct Span {
     __device__ __forceinline__ const char* rec(const ScanArgs& A, int st) const { return fac + static_cast<long>(st) * (NB * A.lay.block); }
     __device__ __forceinline__ long elem(const ScanArgs& A, int st) const { return 2 * (base_tn + static_cast<long>(st) * CP * A.n); }
 };
-__device__ __forceinline__ f32x4 ldv4(rsrc_t r, u32 off, int s) {
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, s, 0));
-}
-__device__ __forceinline__ float2 ldv2(rsrc_t r, u32 off, int s) {
-    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, s, 0));
-}
-// keeps the loads before it in this order for every block, so that the wait counts stay exact
-#define LOAD_ORDER() __builtin_amdgcn_sched_barrier(0)
-
 // fp32 operands.  Workgroup: 8 value columns on four waves; wave w holds channel block w of them
 // (16 x 8 complex, interleaved columns: lane (c, g) part c & 1 of column c / 2), so a block's
 // chain is 10 matrix instructions for its share of Delta, one exchange of the shares through LDS,
@@ -1175,37 +1030,38 @@ __global__ __launch_bounds__(512, 1) void scan_bf16_kernel(ScanArgs A)
 }
 
 // ------------------------------------------------------------------ backward scans
-// The forward scan recording the state entering every block and Delta, and the adjoint scan
-// (blocks in reverse) recording dL/dS leaving every block and G_F and writing dv and dS0; both in
-// one launch (they read the same records and are independent).
+// The forward scan recording the state entering every run of blocks and Delta, and the adjoint scan
+// (blocks in reverse) recording dL/dS leaving every run and G_F and writing dv and dS0; both in
+// one launch (they read the same records and are independent).  fp32 is bound by the SIMDs' issue
+// (both scans' workgroups share them: 330 us for B4 H8 T2048, 128 blocks at 2.6 us), bf16 at many
+// heads by what it writes (B8 H16 T4096: 1.07 GB of states and 0.27 GB of rows, 800 us; with the
+// states of every block 1150 us, of every fourth 615 us, but see grad_blocks).  The scans in place
+// take 1112 and 1290 us.
 struct BwdArgs {
     const char* fac;
     const void *v, *dO, *beta;
     const float *S0, *dS_T;              // may be null (zero)
     float* dS0;                          // may be null
-    float *S_rec, *G_rec, *D_rows, *F_rows;
+    char *S_rec, *G_rec, *D_rows, *F_rows;
     void* dv;
     long heads;
-    int T, m, n, n_slices, nchunks, nsteps;
+    int T, m, n, n_slices, nsteps;
     BwdLayout lay;
+    GradLayout grad;
 };
 
-// One scan's walk over its blocks: `dir` +1 or -1, resources of the step a block belongs to
-// (operands four blocks ahead), and the block's places in the outputs by 64-bit pointers that
-// move with it (m n 8 bytes per block may pass what a scalar offset holds).  Blocks past the end
-// of the sequence, in the last step, write nothing.
+// One scan's walk over its steps: resources of a step's inputs (operands four blocks ahead; steps
+// outside the sequence are empty ranges), of the outputs' blocks.  Blocks past the end of the
+// sequence, in the last step, are identities and write their records like any other.
 struct Walk {
-    int nsteps, nchunks;
-    long tok, mn8, row8;
+    int nsteps;
+    long tok, mn8, head;
     const char* fac;
-    long head;
     __device__ __forceinline__ Walk(const BwdArgs& A, long bh) {
         nsteps = A.nsteps;
-        nchunks = A.nchunks;
         head = bh;
         tok = bh * A.T;
         mn8 = static_cast<long>(A.m) * A.n * 8;
-        row8 = static_cast<long>(A.n) * 8;
         fac = A.fac + bh * A.nsteps * static_cast<long>(NB) * A.lay.block;
     }
     __device__ __forceinline__ bool in(int st) const { return st >= 0 && st < nsteps; }
@@ -1217,11 +1073,11 @@ struct Walk {
         const int left = in(st) ? min(A.T - st * CP, CP) : 0;
         return rsrc(static_cast<const char*>(p) + (tok + static_cast<long>(st) * CP) * A.n * 2 * es, left * A.n * 2 * es);
     }
-    __device__ __forceinline__ rsrc_t state(const float* p, int ch) const {
-        return rsrc(reinterpret_cast<const char*>(p) + (head * nchunks + ch) * mn8, ch < nchunks ? static_cast<int>(mn8) : 0);
+    __device__ __forceinline__ rsrc_t state(const BwdArgs& A, const char* p, int rec) const {
+        return rsrc(p + (head * A.grad.recs + rec) * A.grad.state, A.grad.state);
     }
-    __device__ __forceinline__ rsrc_t chunk_rows(const float* p, int ch) const {
-        return rsrc(reinterpret_cast<const char*>(p) + (head * nchunks + ch) * 16 * row8, ch < nchunks ? static_cast<int>(16 * row8) : 0);
+    __device__ __forceinline__ rsrc_t block_rows(const BwdArgs& A, const char* p, int ch, bool on = true) const {
+        return rsrc(p + (head * A.grad.blocks + ch) * A.grad.rows, on ? A.grad.rows : 0);
     }
 };
 
@@ -1264,11 +1120,15 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
 #pragma unroll
         for (int r = 0; r < 4; ++r) S[r] = ld_f32(rs, soff[r]);
     }
+    constexpr int GB = grad_blocks(false);
+    const bool in_rec = live && (j >> 4) < A.grad.ncb;
+    const u32 so_rec = in_rec ? static_cast<u32>((wave * A.grad.ncb + (j >> 4)) * 2048 + (4 * g + 16 * ((j & 15) >> 2)) * 32 + (j & 3) * 8 + qp * 4) : OOR;
     auto put_state = [&](rsrc_t rs) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[r]), rs, soff[r], 0, 0);
+        for (int r = 0; r < 4; ++r) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[r]), rs, so_rec + r * 32, 0, 0);
     };
-    const u32 roff = j < n ? static_cast<u32>(((4 * g + wave) * n + j) * 2 + qp) * 4 : OOR;    // row 4g + wave of a block
+    // row 4g + wave of a block's rows
+    const u32 roff = (j >> 4) < A.grad.ncb ? static_cast<u32>((((4 * g + wave) * A.grad.ncb * 16 + j) * 2 + qp) * 4) : OOR;
     // S <- g S (adjoint: conj(g) S)
     auto decay = [&](f32x4 g0, f32x4 g1, float s) __attribute__((always_inline)) {
 #pragma unroll
@@ -1313,7 +1173,7 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
             for (int b = 0; b < NB; ++b) {
                 Pre& p = pre[b];
                 const int ch = st * NB + b;
-                put_state(wk.state(A.S_rec, ch));
+                if (b % GB == 0) put_state(wk.state(A, A.S_rec, ch / GB));
                 f32x4 pw = zero4();
                 mma1(pw, p.x.x, qp ? -p.v.y : p.v.x);        // conj(v) = (x, -y)
                 mma1(pw, p.x.y, qp ? p.v.x : p.v.y);
@@ -1329,7 +1189,7 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
                 mma8(S, p.k0, p.k1, bfrag_from_acc(dd, qp));
                 fetch_k(next, b, p);
                 const float mine = wave == 0 ? dd[0] : wave == 1 ? dd[1] : wave == 2 ? dd[2] : dd[3];
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(mine), wk.chunk_rows(A.D_rows, ch), roff, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(mine), wk.block_rows(A, A.D_rows, ch), roff, 0, 0);
             }
         }
         return;
@@ -1379,7 +1239,7 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
 #pragma unroll
         for (int w2 = 0; w2 < 4; ++w2) f += reinterpret_cast<const float*>(&red[b & 1][1][w2][lane])[wave];
         const int rows = some ? max(min(A.T - ch * 16, 16), 0) : 0;
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f), wk.chunk_rows(A.F_rows, some ? ch : A.nchunks), roff, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f), wk.block_rows(A, A.F_rows, ch, some), roff, 0, 0);
         const float bt = ld_real<TV>(rsrc(gb + wk.tok + ch * 16, rows * static_cast<int>(sizeof(TV))), (4 * g + wave) * static_cast<u32>(sizeof(TV)));
         const rsrc_t rv = rsrc(gdv + 2 * (wk.tok + ch * 16) * n, rows * n * 2 * static_cast<int>(sizeof(TV)));
         const float x = qp ? -bt * f : bt * f;
@@ -1394,7 +1254,7 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
         for (int b = NB - 1; b >= 0; --b) {
             Pre& p = pre[b];
             const int ch = st * NB + b;
-            put_state(wk.state(A.G_rec, ch));
+            if (b % GB == GB - 1) put_state(wk.state(A, A.G_rec, ch / GB));
             f32x4 px = zero4();                              // share of X' = conj(K Q) G
             mma8(px, p.k0, p.k1, bfrag_from_acc(S, qp));
             fetch_k(next, b, p);
@@ -1429,7 +1289,11 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
     }
     __syncthreads();
     finish(0, 0, true);
-    if (A.dS0 != nullptr) put_state(rsrc(reinterpret_cast<const char*>(A.dS0) + bh * wk.mn8, static_cast<int>(wk.mn8)));
+    if (A.dS0 != nullptr) {
+        const rsrc_t rs = rsrc(reinterpret_cast<const char*>(A.dS0) + bh * wk.mn8, static_cast<int>(wk.mn8));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[r]), rs, soff[r], 0, 0);
+    }
 }
 template <typename TV, typename TO>
 __global__ __launch_bounds__(256, 2) void bwd_f32_kernel(BwdArgs A, unsigned nfwd)
@@ -1492,14 +1356,10 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
     if (wave8 < 4) {
         // ================================================ state waves
         const bool live0 = 2 * h < A.lay.nkb, live1 = 2 * h + 1 < A.lay.nkb;
-        u32 soff[2][4];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = (2 * h + kb) * 16 + 4 * g + r;
-                soff[kb][r] = j < n && i < m ? static_cast<u32>(i * n + j) * 8u : OOR;
-            }
+        auto soff = [&](int g4, int kb, int r) {             // [m][n]
+            const int i = (2 * h + kb) * 16 + g4 + r;
+            return j < n && i < m ? static_cast<u32>(i * n + j) * 8u : OOR;
+        };
         CAcc S[2];
         {
             const float* init = adj ? A.dS_T : A.S0;
@@ -1508,17 +1368,23 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float2 x = ld_c64(rs, soff[kb][r]);
+                    const float2 x = ld_c64(rs, soff(4 * g, kb, r));
                     S[kb].re[r] = x.x;
                     S[kb].im[r] = x.y;
                 }
         }
+        constexpr int GB = grad_blocks(true);
+        const bool in_rec = sl * 2 + cw < A.grad.ncb;
+        u32 so_rec[2];                                       // records: channel 4g + r, column c of its block
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+            so_rec[kb] = in_rec && (kb ? live1 : live0) ? static_cast<u32>(((2 * h + kb) * A.grad.ncb + sl * 2 + cw) * 2048 + (4 * g + 16 * (c >> 2)) * 32 + (c & 3) * 8) : OOR;
         auto put_state = [&](rsrc_t rs) __attribute__((always_inline)) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(S[kb].re[r]), __float_as_uint(S[kb].im[r])}, rs, soff[kb][r], 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(S[kb].re[r]), __float_as_uint(S[kb].im[r])}, rs, so_rec[kb] + r * 32, 0, 0);
         };
         // a: the operand of the first product (-W; adjoint: conj(K Q)); k: of the second (K Q;
         // adjoint: -W^*); z, rows: the term known beforehand (T conj(V); adjoint: Z^* G_R)
@@ -1553,7 +1419,7 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
         auto walk = [&](auto adj_c) __attribute__((always_inline)) {
             constexpr bool ADJ = decltype(adj_c)::value;
             auto block = [&](int b, int ch, Pre& p, const Step& next) __attribute__((always_inline)) {
-                put_state(wk.state(ADJ ? A.G_rec : A.S_rec, ch));
+                if (b % GB == (ADJ ? GB - 1 : 0)) put_state(wk.state(A, ADJ ? A.G_rec : A.S_rec, ch / GB));
                 const Right<P> ub = conj_right(p.u);
                 CAcc d;
                 czero(d);
@@ -1601,10 +1467,20 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
         };
         if (adj) walk(std::true_type{});
         else walk(std::false_type{});
-        if (adj && A.dS0 != nullptr) put_state(rsrc(reinterpret_cast<const char*>(A.dS0) + bh * wk.mn8, static_cast<int>(wk.mn8)));
+        if (adj && A.dS0 != nullptr) {
+            const rsrc_t rs = rsrc(reinterpret_cast<const char*>(A.dS0) + bh * wk.mn8, static_cast<int>(wk.mn8));
+            int g4 = 4 * g;                                  // (formed again: not held through the walk)
+            asm volatile("" : "+v"(g4));
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(S[kb].re[r]), __float_as_uint(S[kb].im[r])}, rs, soff(g4, kb, r), 0, 0);
+        }
     } else {
         // ================================================ row waves: blocks of parity h
-        float* const rowrec = adj ? A.F_rows : A.D_rows;
+        const char* const rowrec = adj ? A.F_rows : A.D_rows;
+        const u32 rec_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 1024) + l16 : OOR;
         struct Pre { Frag<P> ns, an, u; float b[4]; };
         Pre pre[2];
         const uint16_t* const gb = static_cast<const uint16_t*>(A.beta);
@@ -1646,10 +1522,8 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
                         __builtin_amdgcn_raw_buffer_store_b32(pack_bf16(p.b[r] * d.re[r], -p.b[r] * d.im[r]), rv, off4[r], 0, 0);
                     fetch(st - 1, ch - st * NB, p);
                 }
-                const rsrc_t rr = wk.chunk_rows(rowrec, ch);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(d.re[r]), __float_as_uint(d.im[r])}, rr, off8[r], 0, 0);
+                const Frag<P> rows = frag_acc<P>(d);
+                __builtin_amdgcn_raw_buffer_store_b128(rows.w, wk.block_rows(A, rowrec, ch), rec_off, 0, 0);
             }
         }
     }
@@ -1768,21 +1642,31 @@ hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus
 
 // ------------------------------------------------------------------ backward
 
-size_t bwd_factors_bytes(long heads, int T, int m, bool in_bf16)
+// (n: a state record's bytes and a step's rows are 32-bit offsets)
+bool bwd_factored_fits(long heads, int T, int n)
 {
-    const long steps = (static_cast<long>(T) + fac::CP - 1) / fac::CP;
-    return static_cast<size_t>(heads) * steps * fac::NB * fac::BwdLayout(m, bf16_operands(in_bf16, m)).block;
+    return heads * (T / 16L + fac::NB) <= 0x7FFFFFFFL && n <= (1 << 20) && 2 * (heads + 7) * (((static_cast<long>(n) + 15) / 16) * 2) <= 0x7FFFFFFFL;
 }
 
-// F: the forward's inputs, records and dv as in launch_bwd_scans (A the adjoint's)
-hipError_t launch_bwd_factored(const ChunkLaunch& F, const ChunkLaunch& L, void* ws, hipStream_t st)
+size_t bwd_factored_bytes(long heads, int T, int m, int n, bool in_bf16)
+{
+    const bool bf = bf16_operands(in_bf16, m);
+    const fac::GradLayout g(T, m, n, bf);
+    return g.bytes(heads) + static_cast<size_t>(heads) * g.blocks * fac::BwdLayout(m, bf).block;
+}
+
+// F: the forward's inputs; L: dL/do, dL/dS_T (S0), dS0 (S_T) and dv; Gl: the gradients' pointers
+hipError_t launch_bwd_factored(const ChunkLaunch& F, const ChunkLaunch& L, const GradLaunch& Gl, void* ws, hipStream_t st)
 {
     using namespace fac;
     const bool bf = bf16_operands(F.in_bf16, F.m);
     const long heads = static_cast<long>(F.B) * F.H;
     const int steps = (F.T + CP - 1) / CP;
-    BwdArgs a{static_cast<const char*>(ws), F.v, L.dO, F.beta, F.S0, L.S0, L.S_T, F.ck_state, L.ck_state, F.ck_rows, L.ck_rows,
-              L.dv, heads, F.T, F.m, F.n, 0, (F.T + 15) / 16, steps, BwdLayout(F.m, bf)};
+    const GradLayout gl(F.T, F.m, F.n, bf);
+    char* const rec = static_cast<char*>(ws) + heads * gl.blocks * BwdLayout(F.m, bf).block;
+    const size_t states = static_cast<size_t>(heads) * gl.recs * gl.state, rows = static_cast<size_t>(heads) * gl.blocks * gl.rows;
+    BwdArgs a{static_cast<const char*>(ws), F.v, L.dO, F.beta, F.S0, L.S0, L.S_T, rec, rec + states, rec + 2 * states,
+              rec + 2 * states + rows, L.dv, heads, F.T, F.m, F.n, 0, steps, BwdLayout(F.m, bf), gl};
     const int cols = bf ? BCOLS : FCOLS;
     a.n_slices = (F.n + cols - 1) / cols;
     const PrepArgs pa{F.q, F.k, F.alpha, F.theta, F.beta, nullptr, nullptr, static_cast<char*>(ws), F.T, F.m, 0, steps,
@@ -1801,7 +1685,9 @@ hipError_t launch_bwd_factored(const ChunkLaunch& F, const ChunkLaunch& L, void*
         if (F.out_bf16) hipLaunchKernelGGL((bwd_f32_kernel<float, uint16_t>), grid, dim3(256), 0, st, a, nfwd);
         else hipLaunchKernelGGL((bwd_f32_kernel<float, float>), grid, dim3(256), 0, st, a, nfwd);
     }
-    return hipGetLastError();
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_grad_steps(Gl, {a.S_rec, a.G_rec, a.D_rows, a.F_rows}, st);
 }
 
 }  // namespace sfda

@@ -74,9 +74,13 @@ hipError_t launch_chunk_decoupled(const ChunkLaunch& L, hipStream_t st);   // C 
 // most the whole sequence's), with the state carried between pieces
 size_t factored_bytes(long heads, int T, int m, int n, bool in_bf16, bool dec, size_t cap);
 hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus, hipStream_t st);   // cus: compute units
-// the backward's scans on operand records in `ws` (bwd_factors_bytes), arguments as launch_bwd_scans
-size_t bwd_factors_bytes(long heads, int T, int m, bool in_bf16);
-hipError_t launch_bwd_factored(const ChunkLaunch& F, const ChunkLaunch& A, void* ws, hipStream_t st);
+// the backward on operand records (sfda_factored.h): preparation, both scans, gradient kernel;
+// F, A as launch_bwd_scans without the records, G without them too; ws of bwd_factored_bytes
+bool bwd_factored_fits(long heads, int T, int n);
+size_t bwd_factored_bytes(long heads, int T, int m, int n, bool in_bf16);
+hipError_t launch_bwd_factored(const ChunkLaunch& F, const ChunkLaunch& A, const GradLaunch& G, void* ws, hipStream_t st);
+struct GradRecords { const char *S, *G, *D, *F; };
+hipError_t launch_grad_steps(const GradLaunch& L, const GradRecords& rec, hipStream_t st);
 // backward: the forward scan recording states and Delta (F; none when F.T == 0) and the
 // reverse adjoint scan (A) in one launch, then the per-chunk gradient pass
 hipError_t launch_bwd_scans(const ChunkLaunch& F, const ChunkLaunch& A, hipStream_t st);

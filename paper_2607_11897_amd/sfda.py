@@ -26,7 +26,8 @@ EXPORTS = ("sfda_chunk_fwd", "sfda_chunk_fwd_sliced", "sfda_chunk_fwd_gated", "s
            "sfda_chunk_fwd_factored_workspace_bytes", "sfda_chunk_fwd_segmented", "sfda_chunk_fwd_segmented_noalloc",
            "sfda_chunk_fwd_segmented_workspace_bytes", "sfda_chunk_fwd_auto_segments",
            "sfda_chunk_bwd", "sfda_chunk_bwd_workspace_bytes",
-           "sfda_chunk_bwd_factored_workspace_bytes", "sfda_chunk_solve_monitor",
+           "sfda_chunk_bwd_auto_workspace_bytes", "sfda_chunk_fwd_auto_factored",
+           "sfda_chunk_solve_monitor",
            "sfda_step", "sfda_status_string", "sfda_abi_version")
 
 _lib = None
@@ -92,8 +93,10 @@ def load_library(path: str = LIB_PATH):
     lib.sfda_chunk_bwd.restype = i
     lib.sfda_chunk_bwd_workspace_bytes.argtypes = [i] * 6
     lib.sfda_chunk_bwd_workspace_bytes.restype = ctypes.c_size_t
-    lib.sfda_chunk_bwd_factored_workspace_bytes.argtypes = [i] * 7
-    lib.sfda_chunk_bwd_factored_workspace_bytes.restype = ctypes.c_size_t
+    lib.sfda_chunk_fwd_auto_factored.argtypes = [i] * 7
+    lib.sfda_chunk_fwd_auto_factored.restype = i
+    lib.sfda_chunk_bwd_auto_workspace_bytes.argtypes = [i] * 7
+    lib.sfda_chunk_bwd_auto_workspace_bytes.restype = ctypes.c_size_t
     lib.sfda_step.argtypes = [vp] * 8 + [i] * 4 + [i, i, vp]
     lib.sfda_step.restype = i
     lib.sfda_status_string.argtypes = [i]
@@ -217,7 +220,8 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
         nfac = 0
         # (a slice the library refuses goes to sfda_chunk_fwd_sliced, which says so; a workspace
         # the caller sized for segments keeps them)
-        if in_code == SFDA_F32 and workspace is None and (slice is None or (8 <= slice <= 64 and slice % 8 == 0)):
+        if in_code == SFDA_F32 and workspace is None and (slice is None or (8 <= slice <= 64 and slice % 8 == 0)) and \
+                lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, in_code, 0):
             nfac = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 0)
         if nfac:
             ws = _workspace(nfac, q.device, stream)
@@ -338,8 +342,8 @@ def chunk_fwd_decoupled(q, k, r, v, alpha, theta, eta, beta, S0=None, C: int = 3
                 o=(o, (B, H, T, n, 2)), S_T=(S_T, (B, H, m, n, 2))))
     args = [_ptr(q), _ptr(k), _ptr(r), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(eta), _ptr(beta), _ptr(S0),
             _ptr(o), _ptr(S_T), B, H, T, m, n, C, in_code, _dtype_code(o)]
-    nws = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 1)
-    if nws:
+    if lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, in_code, 1):
+        nws = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 1)
         ws = _workspace(nws, q.device, stream)
         st = lib.sfda_chunk_fwd_decoupled_factored(*args, _ptr(ws), nws, _stream(stream))
     else:
@@ -355,8 +359,8 @@ def chunk_bwd(q, k, v, alpha, theta, beta, S0, dO, dS_T=None, C: int = 64, *,
     dO = dL/do [B,H,T,n,2] (o's dtype) and dS_T = dL/dS_T [B,H,m,n,2] float32 or None.
     Inputs as chunk_fwd.  Returns dq, dk, dv, dalpha, dtheta, dbeta in the inputs' dtype and
     dS0 (float32, or None without want_dS0); complex gradients are dL/dRe + i dL/dIm.
-    `workspace`: a uint8 device tensor of at least bwd_workspace_bytes(...) bytes, allocated
-    here when not given (at sfda_chunk_bwd_factored_workspace_bytes, where the call is fastest)."""
+    `workspace`: a uint8 device tensor of at least bwd_workspace_bytes(...) bytes (fastest at
+    bwd_auto_workspace_bytes(...), which is allocated here when none is given)."""
     import torch
     lib = load_library()
     B, H, T, m, _ = _dims(q, v, 5)
@@ -374,8 +378,7 @@ def chunk_bwd(q, k, v, alpha, theta, beta, S0, dO, dS_T=None, C: int = 64, *,
              dalpha=torch.empty_like(alpha), dtheta=torch.empty_like(theta), dbeta=torch.empty_like(beta),
              dS0=torch.empty((B, H, m, n, 2), dtype=torch.float32, device=q.device) if want_dS0 else None)
     if workspace is None:
-        nws = max(lib.sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C),
-                  lib.sfda_chunk_bwd_factored_workspace_bytes(B, H, T, m, n, C, in_code))
+        nws = lib.sfda_chunk_bwd_auto_workspace_bytes(B, H, T, m, n, C, in_code)
         workspace = _workspace(max(nws, 1), q.device, stream)
     _check(dict(q=(q, (B, H, T, m, 2)), workspace=(workspace, tuple(workspace.shape))))
     st = lib.sfda_chunk_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(beta), _ptr(S0),
@@ -390,6 +393,13 @@ def chunk_bwd(q, k, v, alpha, theta, beta, S0, dO, dS_T=None, C: int = 64, *,
 
 def bwd_workspace_bytes(B: int, H: int, T: int, m: int, n: int, C: int) -> int:
     return int(load_library().sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C))
+
+
+def bwd_auto_workspace_bytes(B: int, H: int, T: int, m: int, n: int, C: int, dtype: str = "f32") -> int:
+    """The workspace at which chunk_bwd is fastest (sfda_chunk_bwd_auto_workspace_bytes); dtype:
+    the inputs' ("f32" or "bf16")."""
+    code = {"f32": SFDA_F32, "bf16": SFDA_BF16}[dtype]
+    return int(load_library().sfda_chunk_bwd_auto_workspace_bytes(B, H, T, m, n, C, code))
 
 
 def chunk_solve_monitor(k, alpha, theta, beta, stream=None) -> Tuple:

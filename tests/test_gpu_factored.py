@@ -120,7 +120,7 @@ def test_bad_gate_gives_nan_from_its_block_on(lib, field, bad):
 
 @pytest.mark.parametrize("dtype,out", [("f32", "f32"), ("f32", "bf16"), ("bf16", "bf16"), ("bf16", "f32")])
 @pytest.mark.parametrize("B,H,T,m,n", [
-    (2, 4, 1, 64, 64), (1, 2, 16, 16, 8), (2, 5, 17, 17, 9), (1, 3, 63, 33, 33), (1, 8, 64, 48, 32),
+    (2, 4, 1, 64, 64), (1, 2, 49, 16, 8), (2, 5, 48, 17, 9), (1, 3, 63, 33, 33), (1, 8, 64, 48, 32),
     (3, 3, 65, 64, 65), (1, 9, 129, 5, 7), (1, 2, 200, 47, 1), (1, 1, 130, 3, 40), (2, 1, 96, 62, 96),
 ])
 def test_backward_edges(lib, B, H, T, m, n, dtype, out):
@@ -138,11 +138,11 @@ def test_backward_edges(lib, B, H, T, m, n, dtype, out):
     dO_t, dS_t = to_device(I.to_storage(dO, out), out), to_device(I.to_storage(dS, "f32"), "f32")
     ref = BW.recurrence_backward(x.q, x.k, x.v, x.alpha, x.theta, x.beta, x.S0, dO, dS)
     code = sfda.SFDA_F32 if dtype == "f32" else sfda.SFDA_BF16
-    full = lib.sfda_chunk_bwd_factored_workspace_bytes(B, H, T, m, n, 64, code)
+    full = lib.sfda_chunk_bwd_auto_workspace_bytes(B, H, T, m, n, 64, code)
     least = sfda.bwd_workspace_bytes(B, H, T, m, n, 64)
-    assert full > least
+    assert full >= least > 0                           # (equal: in place alone, or alone on prepared operands)
     tol = 2e-2 if "bf16" in (dtype, out) else 1e-4
-    for size in (full, least):
+    for size in {full, least}:
         say("backward", (B, H, T, m, n), dtype, out, size)
         g = sfda.chunk_bwd(d["q"], d["k"], d["v"], d["alpha"], d["theta"], d["beta"], d["S0"], dO_t, dS_t,
                            workspace=torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda"))
