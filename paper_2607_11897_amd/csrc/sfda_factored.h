@@ -85,9 +85,10 @@ struct BwdLayout {
 };
 
 // What the backward's scans leave for the gradient kernel, per head:
-//   states: S entering and dL/dS leaving every grad_blocks() blocks, fp32, as right operands over
-//     the value columns: [channel block][column block of 16][lane (c, g)][4] complex, channel c,
-//     columns 4g .. 4g + 3;
+//   states: S entering and dL/dS leaving every grad_blocks() blocks, fp32.  bf16 operands: as
+//     right operands over the value columns, [channel block][column block of 16][lane (c, g)][4]
+//     complex, channel c, columns 4g .. 4g + 3 (the scan turns them through LDS); fp32: [channel][column]
+//     (its scan writes 8 columns of a channel at a time: half lines, quarter lines in the other order);
 //   rows: Delta and G_F of every block.  bf16 operands: as they enter the products, pairs in
 //     column fragments [column block][lane (c, g)][4], column c, tokens 4g .. 4g + 3 (rounding
 //     them here is the rounding every use of them makes); fp32: [token][column].

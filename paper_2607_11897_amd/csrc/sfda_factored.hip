@@ -1122,10 +1122,11 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
     }
     constexpr int GB = grad_blocks(false);
     const bool in_rec = live && (j >> 4) < A.grad.ncb;
-    const u32 so_rec = in_rec ? static_cast<u32>((wave * A.grad.ncb + (j >> 4)) * 2048 + (4 * g + 16 * ((j & 15) >> 2)) * 32 + (j & 3) * 8 + qp * 4) : OOR;
+    const int row_rec = A.grad.ncb * 128;
+    const u32 so_rec = in_rec ? static_cast<u32>((wave * 16 + 4 * g) * row_rec + j * 8 + qp * 4) : OOR;
     auto put_state = [&](rsrc_t rs) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[r]), rs, so_rec + r * 32, 0, 0);
+        for (int r = 0; r < 4; ++r) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[r]), rs, so_rec, r * row_rec, 0);
     };
     // row 4g + wave of a block's rows
     const u32 roff = (j >> 4) < A.grad.ncb ? static_cast<u32>((((4 * g + wave) * A.grad.ncb * 16 + j) * 2 + qp) * 4) : OOR;
@@ -1309,7 +1310,10 @@ template <typename TO>
 __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nfwd)
 {
     constexpr int P = PREC_BF16;
+    constexpr int GB = grad_blocks(true);
+    static_assert(GB % 2 == 0, "the states to record wait in LDS for one block");
     __shared__ f32x4 red[2][4][2][64];                 // [parity][state wave][re, im][lane]
+    __shared__ __align__(16) char st_out[4][2][16 * 144];     // states to record [state wave][half's block]: 16 channels x 16 columns, padded rows
     const bool adj = blockIdx.x >= nfwd;
     long bh;
     int sl;
@@ -1373,18 +1377,12 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
                     S[kb].im[r] = x.y;
                 }
         }
-        constexpr int GB = grad_blocks(true);
-        const bool in_rec = sl * 2 + cw < A.grad.ncb;
-        u32 so_rec[2];                                       // records: channel 4g + r, column c of its block
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-            so_rec[kb] = in_rec && (kb ? live1 : live0) ? static_cast<u32>(((2 * h + kb) * A.grad.ncb + sl * 2 + cw) * 2048 + (4 * g + 16 * (c >> 2)) * 32 + (c & 3) * 8) : OOR;
-        auto put_state = [&](rsrc_t rs) __attribute__((always_inline)) {
+        auto put_state = [&]() __attribute__((always_inline)) {     // for the row waves to record
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(S[kb].re[r]), __float_as_uint(S[kb].im[r])}, rs, so_rec[kb] + r * 32, 0, 0);
+                    *reinterpret_cast<float2*>(st_out[wave][kb] + (4 * g + r) * 144 + c * 8) = make_float2(S[kb].re[r], S[kb].im[r]);
         };
         // a: the operand of the first product (-W; adjoint: conj(K Q)); k: of the second (K Q;
         // adjoint: -W^*); z, rows: the term known beforehand (T conj(V); adjoint: Z^* G_R)
@@ -1419,7 +1417,7 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
         auto walk = [&](auto adj_c) __attribute__((always_inline)) {
             constexpr bool ADJ = decltype(adj_c)::value;
             auto block = [&](int b, int ch, Pre& p, const Step& next) __attribute__((always_inline)) {
-                if (b % GB == (ADJ ? GB - 1 : 0)) put_state(wk.state(A, ADJ ? A.G_rec : A.S_rec, ch / GB));
+                if (b % GB == (ADJ ? GB - 1 : 0)) put_state();
                 const Right<P> ub = conj_right(p.u);
                 CAcc d;
                 czero(d);
@@ -1481,6 +1479,7 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
         // ================================================ row waves: blocks of parity h
         const char* const rowrec = adj ? A.F_rows : A.D_rows;
         const u32 rec_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 1024) + l16 : OOR;
+        const u32 st_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 2048 + lane * 32) : OOR;
         struct Pre { Frag<P> ns, an, u; float b[4]; };
         Pre pre[2];
         const uint16_t* const gb = static_cast<const uint16_t*>(A.beta);
@@ -1507,8 +1506,20 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
                 __syncthreads();
                 // (the walks meet parity b & 1 = i & 1 forwards and 1 - (i & 1) backwards)
                 const int par = adj ? 1 - (i & 1) : i & 1;
-                if (par != h) continue;
                 const int ch = st * NB + (adj ? NB - 1 - i : i);
+                if (par != h) {
+                    // the state of a run's start (adjoint: end) to the records, by whole lines
+                    if (i % GB != 0) continue;
+                    const rsrc_t rs = wk.state(A, adj ? A.G_rec : A.S_rec, ch / GB);
+#pragma unroll
+                    for (int kb = 0; kb < 4; ++kb) {
+                        const char* p = st_out[2 * cw + (kb >> 1)][kb & 1] + c * 144 + g * 32;
+#pragma unroll
+                        for (int e = 0; e < 2; ++e)
+                            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(p + e * 16), rs, st_off + e * 16, kb * A.grad.ncb * 2048, 0);
+                    }
+                    continue;
+                }
                 CAcc d;
                 d.re = red[par][2 * cw][0][lane] + red[par][2 * cw + 1][0][lane];
                 d.im = red[par][2 * cw][1][lane] + red[par][2 * cw + 1][1][lane];

@@ -308,15 +308,15 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
     };
     // S and G of one column block
     const long st0 = (bh * A.lay.recs + rec) * A.lay.state;
-    const u32 st_off = live ? static_cast<u32>(w * ncb * 2048 + lane * 32) : OOR;
+    const u32 st_off = !live ? OOR : static_cast<u32>(P == PREC_F32 ? ch * ncb * 128 + g * 32 : w * ncb * 2048 + lane * 32);
     // (fp32 scans run 8 columns a workgroup: past the last of them the record holds nothing)
     const int n_rec = P == PREC_F32 ? (n + 7) / 8 * 8 : ncb * 16;
     struct Pair { f32x4 a, b; };
     auto load_state = [&](const char* p, int cb, Pair& x) __attribute__((always_inline)) {
         const rsrc_t r = rsrc(p + st0, A.lay.state);
         const u32 o = cb * 16 + 4 * g < n_rec ? st_off : OOR;
-        x.a = ldv4(r, o, cb * 2048);
-        x.b = ldv4(r, o + 16, cb * 2048);
+        x.a = ldv4(r, o, cb * (P == PREC_F32 ? 128 : 2048));
+        x.b = ldv4(r, o + 16, cb * (P == PREC_F32 ? 128 : 2048));
     };
     auto cacc = [](const Pair& x) {
         CAcc z;
