@@ -196,9 +196,10 @@ size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n
 /*
  * sfda_chunk_fwd_auto_factored -- 1 where the factored forward (decoupled: the write-decoupled one)
  * is the faster one on the current device, 0 where the one-launch entry point is: short sequences,
- * many heads in float32, and bfloat16 inputs without decoupling.
+ * many heads (bfloat16 without decoupling: more than 64), and, in bfloat16, long sequences that
+ * sfda_chunk_fwd_auto_segments splits.
  */
-int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, sfda_dtype_t in_dtype,
+int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype,
                                  int decoupled);
 
 sfda_status_t sfda_chunk_fwd_factored(const void* q, const void* k, const void* v,

@@ -330,11 +330,22 @@ size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n
     return sfda::factored_bytes(BH, T, m, n, in_dtype == SFDA_BF16, decoupled != 0, FACTORED_CAP);
 }
 
-int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, sfda_dtype_t in_dtype, int decoupled)
+int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype, int decoupled)
 {
     if (sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_dtype, decoupled) == 0) return 0;
-    if (in_dtype == SFDA_BF16 && !decoupled) return 0;     // sfda_chunk_fwd's bfloat16 kernel is the faster one
-    return factored_faster(static_cast<long>(B) * H, T, m, n, in_dtype == SFDA_BF16, decoupled != 0) ? 1 : 0;
+    const long BH = static_cast<long>(B) * H;
+    if (in_dtype == SFDA_BF16 && !decoupled) {
+        // against sfda_chunk_fwd's bfloat16 kernel, whose chain is 0.9 us a block where the scan on
+        // prepared operands takes 0.5, and whose segments overtake both on long sequences.  us, in
+        // place or in segments / factored, m n 64: 12 heads T 192 20/19, T 256 24/22, T 1536 100/73,
+        // T 2560 119/105, T 4096 132/159; 32 heads T 256 24/24, T 1536 100/75; 48 heads T 384 32/35,
+        // T 768 55/50, T 3072 193/168; 64 heads T 384 32/34, T 768 55/50, T 1536 101/90, T 2048
+        // 130/131; 96 heads T 1024 71/73; n 96: 48 heads T 768 56/50, 64 heads T 768 56/50, T 2048 132/136
+        const bool few = BH <= 32 ? T >= 256 : BH <= 48 ? T >= 640 : BH <= 64 && T >= 640 && T <= 1536;
+        if (!few || BH * ((n + 31L) / 32) > 144) return 0;
+        return T <= 2560 || sfda_chunk_fwd_auto_segments(B, H, T, m, n, C, in_dtype) == 1 ? 1 : 0;
+    }
+    return factored_faster(BH, T, m, n, in_dtype == SFDA_BF16, decoupled != 0) ? 1 : 0;
 }
 
 // the checks of both factored entry points past sfda_chunk_fwd's, then the launches

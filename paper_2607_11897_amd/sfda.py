@@ -93,7 +93,7 @@ def load_library(path: str = LIB_PATH):
     lib.sfda_chunk_bwd.restype = i
     lib.sfda_chunk_bwd_workspace_bytes.argtypes = [i] * 6
     lib.sfda_chunk_bwd_workspace_bytes.restype = ctypes.c_size_t
-    lib.sfda_chunk_fwd_auto_factored.argtypes = [i] * 7
+    lib.sfda_chunk_fwd_auto_factored.argtypes = [i] * 8
     lib.sfda_chunk_fwd_auto_factored.restype = i
     lib.sfda_chunk_bwd_auto_workspace_bytes.argtypes = [i] * 7
     lib.sfda_chunk_bwd_auto_workspace_bytes.restype = ctypes.c_size_t
@@ -199,11 +199,11 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
     slice: value columns per workgroup (sfda_chunk_fwd_sliced); segments: G parallel
     segments per head (sfda_chunk_fwd_segmented; `workspace` a uint8 device tensor of at
     least segmented_workspace_bytes(...) bytes, allocated here when not given), None for one
-    scan per head (sfda_chunk_fwd), or "auto" (the default).  "auto" runs float32 inputs through
-    sfda_chunk_fwd_factored (whatever the slice: no column's arithmetic depends on it) and
-    bfloat16 ones, without a slice, with the count sfda_chunk_fwd_auto_segments suggests:
-    segments when the heads alone would leave most compute units idle.  Workspaces not given
-    come from torch's allocator."""
+    scan per head (sfda_chunk_fwd), or "auto" (the default).  "auto" runs sfda_chunk_fwd_factored
+    where sfda_chunk_fwd_auto_factored says so (whatever the slice: no column's arithmetic depends
+    on it), else, without a slice, the count sfda_chunk_fwd_auto_segments suggests: segments when
+    the heads alone would leave most compute units idle.  Workspaces not given come from torch's
+    allocator."""
     import torch
     lib = load_library()
     B, H, T, m, _ = _dims(q, v, 5)
@@ -232,8 +232,8 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
         nfac = 0
         # (a slice the library refuses goes to sfda_chunk_fwd_sliced, which says so; a workspace
         # the caller sized for segments keeps them)
-        if in_code == SFDA_F32 and workspace is None and (slice is None or (8 <= slice <= 64 and slice % 8 == 0)) and \
-                lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, in_code, 0):
+        if workspace is None and (slice is None or (8 <= slice <= 64 and slice % 8 == 0)) and \
+                lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, C, in_code, 0):
             nfac = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 0)
         if nfac:
             ws = _workspace(nfac, q.device, stream)
@@ -357,7 +357,7 @@ def chunk_fwd_decoupled(q, k, r, v, alpha, theta, eta, beta, S0=None, C: int = 3
                 o=(o, (B, H, T, n, 2)), S_T=(S_T, (B, H, m, n, 2))))
     args = [_ptr(q), _ptr(k), _ptr(r), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(eta), _ptr(beta), _ptr(S0),
             _ptr(o), _ptr(S_T), B, H, T, m, n, C, in_code, _dtype_code(o)]
-    if lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, in_code, 1):
+    if lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, C, in_code, 1):
         nws = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 1)
         ws = _workspace(nws, q.device, stream)
         st = lib.sfda_chunk_fwd_decoupled_factored(*args, _ptr(ws), nws, _stream(stream))

@@ -154,3 +154,34 @@ def test_backward_edges(lib, B, H, T, m, n, dtype, out):
             errs[name] = rel_err(got, ref[name])
         say({k: f"{e:.2e}" for k, e in errs.items()})
         assert max(errs.values()) <= tol, errs
+
+
+@pytest.mark.parametrize("dtype,B,H,T,m,n,decoupled,want", [
+    ("f32", 1, 4, 48, 64, 64, 0, 0), ("f32", 1, 4, 49, 64, 64, 0, 1), ("f32", 1, 4, 33, 64, 64, 1, 1),
+    ("f32", 1, 96, 96, 64, 64, 0, 0), ("f32", 1, 96, 97, 64, 64, 0, 1), ("f32", 4, 64, 512, 64, 64, 0, 0),
+    ("f32", 4, 64, 512, 16, 64, 0, 1), ("bf16", 1, 32, 255, 64, 64, 0, 0), ("bf16", 1, 32, 256, 64, 64, 0, 1),
+    ("bf16", 1, 48, 639, 64, 64, 0, 0), ("bf16", 1, 64, 1537, 64, 64, 0, 0), ("bf16", 1, 65, 1024, 64, 64, 0, 0),
+    ("bf16", 1, 12, 4096, 64, 64, 0, 0), ("bf16", 1, 12, 4095, 64, 64, 0, 1), ("bf16", 1, 48, 1024, 64, 97, 0, 0),
+    ("bf16", 8, 16, 48, 64, 64, 1, 0), ("bf16", 8, 16, 49, 64, 64, 1, 1),
+])
+def test_rule_and_both_paths(lib, dtype, B, H, T, m, n, decoupled, want):
+    """The rule at its edges; where it takes a bfloat16 or float32 forward to prepared operands, the
+    default's result is the factored entry's, bit for bit, and the in-place one's to rounding (twice
+    the bar against the oracle: each within it)."""
+    import torch
+    from paper_2607_11897_amd import sfda
+    code = sfda.SFDA_F32 if dtype == "f32" else sfda.SFDA_BF16
+    assert lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, 64, code, decoupled) == want
+    if decoupled or not want or B * H * T > 32 * 1024:
+        return
+    x = I.make_chunk_inputs(I.Workload("rule", B, H, T, m, n, 64, dtype, I.LAWS_MAIN, 990 + T, 1e-4))
+    say("rule", (B, H, T, m, n), dtype)
+    d = upload(x)
+    args = (d["q"], d["k"], d["v"], d["alpha"], d["theta"], d["beta"], d["S0"])
+    o, S = sfda.chunk_fwd(*args)
+    o1, S1 = sfda.chunk_fwd(*args, segments=None)
+    of, Sf = factored(lib, x)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_complex(o), of) and np.array_equal(to_complex(S), Sf)
+    tol = 2 * (1e-4 if dtype == "f32" else 2e-2)
+    assert rel_err(of, to_complex(o1)) <= tol and rel_err(Sf, to_complex(S1)) <= tol
