@@ -568,7 +568,9 @@ static size_t bwd_factored_need(int B, int H, int T, int m, int n, int C, sfda_d
     if (need == 0 || !dtype_ok(in_dtype) || !sfda::bwd_factored_fits(BH, T, n) ||
         !bwd_factored_faster(BH, T, m, n, in_dtype == SFDA_BF16))
         return 0;
-    return std::max(need, sfda::bwd_factored_bytes(BH, T, m, n, in_dtype == SFDA_BF16));
+    // (with few value columns the operand records are many times the states: not past 16 GiB)
+    const size_t bytes = sfda::bwd_factored_bytes(BH, T, m, n, in_dtype == SFDA_BF16);
+    return bytes <= std::max(need, size_t(16) << 30) ? std::max(need, bytes) : 0;
 }
 
 size_t sfda_chunk_bwd_auto_workspace_bytes(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype)

@@ -190,6 +190,15 @@ def _workspace(nbytes: int, device, stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
+def _try_workspace(nbytes: int, device, stream):
+    """_workspace, or None where the device's memory is full (the paths that need less run then)."""
+    import torch
+    try:
+        return _workspace(nbytes, device, stream)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=None,
               out_dtype=None, want_state: bool = True, slice: Optional[int] = None,
               segments="auto", workspace=None, stream=None) -> Tuple:
@@ -235,8 +244,8 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
         if workspace is None and (slice is None or (8 <= slice <= 64 and slice % 8 == 0)) and \
                 lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, C, in_code, 0):
             nfac = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 0)
-        if nfac:
-            ws = _workspace(nfac, q.device, stream)
+        ws = _try_workspace(nfac, q.device, stream) if nfac else None
+        if ws is not None:
             st = lib.sfda_chunk_fwd_factored(*args, in_code, _dtype_code(o), _ptr(ws), nfac, _stream(stream))
             if st != 0:
                 raise SfdaError(st, "sfda_chunk_fwd_factored")
@@ -357,9 +366,11 @@ def chunk_fwd_decoupled(q, k, r, v, alpha, theta, eta, beta, S0=None, C: int = 3
                 o=(o, (B, H, T, n, 2)), S_T=(S_T, (B, H, m, n, 2))))
     args = [_ptr(q), _ptr(k), _ptr(r), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(eta), _ptr(beta), _ptr(S0),
             _ptr(o), _ptr(S_T), B, H, T, m, n, C, in_code, _dtype_code(o)]
+    ws = None
     if lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, C, in_code, 1):
         nws = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 1)
-        ws = _workspace(nws, q.device, stream)
+        ws = _try_workspace(nws, q.device, stream)
+    if ws is not None:
         st = lib.sfda_chunk_fwd_decoupled_factored(*args, _ptr(ws), nws, _stream(stream))
     else:
         st = lib.sfda_chunk_fwd_decoupled(*args, _stream(stream))
@@ -394,7 +405,10 @@ def chunk_bwd(q, k, v, alpha, theta, beta, S0, dO, dS_T=None, C: int = 64, *,
              dS0=torch.empty((B, H, m, n, 2), dtype=torch.float32, device=q.device) if want_dS0 else None)
     if workspace is None:
         nws = lib.sfda_chunk_bwd_auto_workspace_bytes(B, H, T, m, n, C, in_code)
-        workspace = _workspace(max(nws, 1), q.device, stream)
+        workspace = _try_workspace(max(nws, 1), q.device, stream)
+        if workspace is None:
+            nws = lib.sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C)
+            workspace = _workspace(max(nws, 1), q.device, stream)
     _check(dict(q=(q, (B, H, T, m, 2)), workspace=(workspace, tuple(workspace.shape))))
     st = lib.sfda_chunk_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(beta), _ptr(S0),
                             _ptr(dO), _ptr(dS_T), _ptr(g["dq"]), _ptr(g["dk"]), _ptr(g["dv"]),
