@@ -26,9 +26,9 @@
 // elementwise stage finds G_Qg, G_Kg, G_Ki, q, k and g on one lane.  Only the rows (Delta, G_F, G_R:
 // shared by the channel blocks) and the four 16 x 16 products pass through LDS.
 //
-// Bound by vector issue: about 1400 instructions per wave and block around 54 matrix instructions
+// Bound by vector issue: about 1350 instructions per wave and block around 54 matrix instructions
 // (bf16), two waves per SIMD; fp32 by the matrix instructions (332 of 32 cycles).  B8 H16 T4096 bf16
-// 670 us, B4 H8 T2048 float32 172 us, B2 H6 T509 bf16 11 us, where the pass over the 16-token chunks'
+// 600-660 us from box to box, B4 H8 T2048 float32 172 us, B2 H6 T509 bf16 11 us, where the pass over the 16-token chunks'
 // records (staging S and G themselves through LDS) takes 1190, 241 and 19 us.
 #include <type_traits>
 
@@ -84,6 +84,18 @@ template <typename T> __device__ __forceinline__ float ld_real_at(rsrc_t r, u32 
     if constexpr (sizeof(T) == 4) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, s, 0));
     else return __uint_as_float(static_cast<u32>(__builtin_amdgcn_raw_buffer_load_b16(r, off, s, 0)) << 16);
 }
+// four complex elements as loaded, converted where they are used
+template <typename T> struct Raw4;
+template <> struct Raw4<float> {
+    float2 x[4];
+    __device__ __forceinline__ void load(int r, rsrc_t rs, u32 off, int s) { x[r] = ldv2(rs, off, s); }
+    __device__ __forceinline__ float2 get(int r) const { return x[r]; }
+};
+template <> struct Raw4<uint16_t> {
+    u32 w[4];
+    __device__ __forceinline__ void load(int r, rsrc_t rs, u32 off, int s) { w[r] = __builtin_amdgcn_raw_buffer_load_b32(rs, off, s, 0); }
+    __device__ __forceinline__ float2 get(int r) const { return make_float2(bf_lo(w[r]), bf_hi(w[r])); }
+};
 // a gradient's element in the inputs' type
 template <typename T> __device__ __forceinline__ void st_cplx(rsrc_t r, u32 off, int s, float2 x) {
     if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(x.x), __float_as_uint(x.y)}, r, off, s, 0);
@@ -218,7 +230,9 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
     }
 
     // ---- the rows' tiles: tile kind * NBK + b, kind 0 Delta, 1 G_F (with V, for dbeta), 2 G_R
-    struct Tile { Frag<P> f; float2 x[4], v[4]; };
+    // (bf16 rows stay the pairs they are: G_R's conjugate flips a sign bit)
+    constexpr bool RAW_O = P == PREC_BF16 && sizeof(TOUT) == 2;
+    struct Tile { Frag<P> f; float2 x[4]; Raw4<TIN> v; };
     auto tile_of = [&](int u, int& kind, int& b) __attribute__((always_inline)) {
         kind = NBK == 4 ? u : (w + 4 * u) / NBK;
         b = NBK == 4 ? w : (w + 4 * u) % NBK;
@@ -241,13 +255,17 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
                 for (int r = 0; r < 4; ++r)
                     x.x[r] = ldv2(rr, j < n ? static_cast<u32>((4 * g + r) * ncb * 16 + j) * 8 : OOR, b * A.lay.rows);
             }
+        } else if constexpr (RAW_O) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                x.f.w[r] = __builtin_amdgcn_raw_buffer_load_b32(r_o, j < n ? o_n * 2u : OOR, (b * 16 + r) * n * 4, 0);
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r) x.x[r] = ld_cplx<TOUT>(r_o, j < n ? o_n * static_cast<u32>(sizeof(TOUT)) : OOR, (b * 16 + r) * n * 2 * static_cast<int>(sizeof(TOUT)));
         }
         if (kind == 1) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) x.v[r] = ld_cplx<TIN>(r_v, j < n ? o_n * EI : OOR, (b * 16 + r) * n * 2 * EI);
+            for (int r = 0; r < 4; ++r) x.v.load(r, r_v, j < n ? o_n * EI : OOR, (b * 16 + r) * n * 2 * EI);
         }
     };
     float vd[TU][4];                                     // Re(conj(G_F) conj(V)), this lane's columns
@@ -257,7 +275,9 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
         for (int r = 0; r < 4; ++r) vd[u][r] = 0.f;
     auto put_tile = [&](int kind, int b, const Tile& x, GradTiles<P, NBK>& t, float (&acc)[4]) __attribute__((always_inline)) {
         Frag<P> f = x.f;
-        if (kind == 2) {
+        if (kind == 2 && RAW_O) {
+            if constexpr (RAW_O) f.w ^= 0x80000000u;
+        } else if (kind == 2) {
             float2 y[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) y[r] = conj(x.x[r]);
@@ -269,7 +289,8 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float2 y = frag_get<P>(f, r);
-                acc[r] = __builtin_fmaf(y.x, x.v[r].x, __builtin_fmaf(-y.y, x.v[r].y, acc[r]));
+                const float2 v = x.v.get(r);
+                acc[r] = __builtin_fmaf(y.x, v.x, __builtin_fmaf(-y.y, v.y, acc[r]));
             }
         }
         const int i = kind * NBK + b;
