@@ -160,7 +160,7 @@ def test_backward_edges(lib, B, H, T, m, n, dtype, out):
     ("f32", 1, 4, 48, 64, 64, 0, 0), ("f32", 1, 4, 49, 64, 64, 0, 1), ("f32", 1, 4, 33, 64, 64, 1, 1),
     ("f32", 1, 96, 96, 64, 64, 0, 0), ("f32", 1, 96, 97, 64, 64, 0, 1), ("f32", 4, 64, 512, 64, 64, 0, 0),
     ("f32", 4, 64, 512, 16, 64, 0, 1), ("bf16", 1, 32, 255, 64, 64, 0, 0), ("bf16", 1, 32, 256, 64, 64, 0, 1),
-    ("bf16", 1, 48, 639, 64, 64, 0, 0), ("bf16", 1, 64, 1537, 64, 64, 0, 0), ("bf16", 1, 65, 1024, 64, 64, 0, 0),
+    ("bf16", 1, 48, 639, 64, 64, 0, 0), ("bf16", 1, 64, 1537, 64, 64, 0, 0), ("bf16", 1, 64, 1537, 64, 32, 0, 1), ("bf16", 1, 64, 1537, 48, 64, 0, 0), ("bf16", 1, 65, 1024, 64, 64, 0, 0),
     ("bf16", 1, 12, 4096, 64, 64, 0, 0), ("bf16", 1, 12, 4095, 64, 64, 0, 1), ("bf16", 1, 48, 1024, 64, 97, 0, 0),
     ("bf16", 8, 16, 48, 64, 64, 1, 0), ("bf16", 8, 16, 49, 64, 64, 1, 1),
 ])
