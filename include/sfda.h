@@ -196,7 +196,7 @@ size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n
 /*
  * sfda_chunk_fwd_auto_factored -- 1 where the factored forward (decoupled: the write-decoupled one)
  * is the faster one on the current device, 0 where the one-launch entry point is: short sequences,
- * many heads (bfloat16 without decoupling: more than 64), and, in bfloat16, long sequences that
+ * many heads (bfloat16 without decoupling: more than 64), and long sequences of few heads that
  * sfda_chunk_fwd_auto_segments splits.
  */
 int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype,
@@ -227,13 +227,16 @@ sfda_status_t sfda_chunk_fwd_decoupled_factored(const void* q, const void* k, co
  * the stretch's transitions, B its write from the zero state) composed along the segments
  * (Lemma A.2, the boundary-state scan of Thm 6.1 at segment granularity): chunk passes give
  * every segment's P_g (final state from S0 = I with v = 0) and B_g (final state from
- * S0 = 0), a fold gives S_in[g + 1] = P_g S_in[g] + B_g and S_T = S_in[G], and a third pass
- * writes o from the exact incoming states: three times the scan work of sfda_chunk_fwd, spread
- * over G times as many workgroups; results agree with it to rounding.  With float32 inputs
- * the call runs the factored forward (sfda_chunk_fwd_factored, bitwise its result) in the same
- * workspace instead, a piece of the sequence at a time, which spreads each head's work
- * without repeating it; where the workspace does not hold one 64-token step of that, it runs
- * sfda_chunk_fwd.
+ * S0 = 0), and a fold gives S_in[g + 1] = P_g S_in[g] + B_g and S_T = S_in[G].  With
+ * float32 inputs and outputs the same two passes also give the readouts X_t = P_t^* q_t and
+ * the zero-state outputs o0_t, and a join writes o_t = o0_t + S_in^* X_t (the same law token
+ * by token); otherwise a third pass writes o from the exact incoming states.  With float32
+ * inputs and n <= 64 the first two passes run as one scan per segment (one copy of the chunk
+ * factors, twice the columns).  Two to three times the scan work of sfda_chunk_fwd, spread over
+ * G times as many workgroups; results agree with it to rounding.  With float32 inputs the call
+ * runs the factored forward (sfda_chunk_fwd_factored, bitwise its result) in the same workspace
+ * instead, a piece of the sequence at a time, where that is the faster one: G == 1, or segments
+ * that are many blocks each or too few beside the fold's chain.
  *   Arguments and errors as sfda_chunk_fwd, plus:
  *   G >= 1 with T a multiple of G * C (SFDA_ERR_SHAPE otherwise; T == 0 is as
  *   sfda_chunk_fwd).
@@ -242,7 +245,7 @@ sfda_status_t sfda_chunk_fwd_decoupled_factored(const void* q, const void* k, co
  *               NULL), 16-byte aligned, not overlapping any other argument
  *               (SFDA_ERR_ALIAS); no initial contents needed.  Its size is that of, per
  *               segment, P_g (m x m), B_g and the incoming state (m x n), and with float32
- *               inputs m more per token, complex float32 (0 for sizes or a dtype out of range).
+ *               inputs X_t (m) per token, complex float32 (0 for sizes or a dtype out of range).
  *   S_T == S0 (in place) is allowed.
  */
 size_t sfda_chunk_fwd_segmented_workspace_bytes(int B, int H, int T, int m, int n, int G,
@@ -254,9 +257,9 @@ size_t sfda_chunk_fwd_segmented_workspace_bytes(int B, int H, int T, int m, int 
  * for which the segments' workgroups (B * H * G * ceil(n / 64)) still fit the compute units
  * once each, T is a multiple of G * C and every segment keeps at least 256 tokens; 1 (use
  * sfda_chunk_fwd) when that G is below 4 for float32 inputs or below 8 for bfloat16 ones.
- * With bfloat16 inputs the segmented scan does three times the scan work of sfda_chunk_fwd spread
- * over G times the workgroups, so it pays only when few heads would leave most compute units
- * idle.  Sizes or a dtype out of range, or no device, give 1.
+ * The segmented scan does two (float32) or three (bfloat16) times the scan work of
+ * sfda_chunk_fwd spread over G times the workgroups, so it pays only when few heads would leave
+ * most compute units idle.  Sizes or a dtype out of range, or no device, give 1.
  * Launches nothing and allocates nothing.
  */
 int sfda_chunk_fwd_auto_segments(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype);

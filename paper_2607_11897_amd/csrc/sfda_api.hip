@@ -116,6 +116,28 @@ bool factored_faster(long BH, int T, int m, int n, bool bf16, bool dec)
     if (T <= (dec ? 80 : 96) && BH * cols >= 3 * cus) return false;
     return !fills_rounds(BH, m, n, cus);
 }
+// The float32 forward over G segments against the one on prepared operands, estimated in us (MI355X):
+// the segments' chain costs 8.5 .. 14.5 us a 16-token block with the columns of both sets (past 64
+// value columns two launches, 13.5 .. 16), on a G-th of the blocks, and the fold 1.0 .. 2.9 us a
+// segment; the prepared operands' chain 0.72 us a block whatever the sizes, and each piece of the
+// sequence its launches.  Measured, segments / prepared operands, m n 64: 1 head T 4096 (G 16)
+// 268/212, T 16384 (G 64) 410/744, T 65536 (G 256) 967/2886; 8 heads T 16384 (G 32) 618/782; 16
+// heads T 65536 (G 16) 3778/3147; 32 heads T 2048 (G 8) 282/153; m n 16: 4 heads T 2048 (G 8)
+// 146/113, T 4096 (G 16) 158/203, T 65536 (G 64) 653/2890, 16 heads T 65536 (G 16) 2210/2917;
+// m 4 n 16: 1 head T 65536 (G 256) 459/2857, in pieces of one step T 4096 (G 16) 153/516.  A bfloat16
+// o takes a third pass in place of the join (another 5.5 .. 8 us a block).
+double segments_us(long BH, int T, int m, int n, int G, bool out_bf16, long cus)
+{
+    const long rounds = (BH * G * ((n + 63L) / 64) + cus - 1) / cus;
+    double block = n <= 64 ? 2.6 + 2.95 * ((m + 31) / 32 + (n + 31) / 32) : m <= 32 ? 13.5 : 16.;
+    if (out_bf16) block += n <= 32 ? 5.5 : 8.;
+    return rounds * block * T / (16. * G) + G * (0.9 + 0.031 * m);
+}
+double prepared_us(int T, const sfda::FactoredPlan& p)
+{
+    const long steps = (T + 63L) / 64, pieces = (steps + p.piece - 1) / p.piece;
+    return 20. + 0.72 * T / 16 + (pieces - 1) * (p.beside ? 4. : 10.);
+}
 // and the backward on prepared operands (three launches; two in place): float32 T 16 34/35, T 32
 // 42/35, 64 heads m n 64 T 32 46/53, T 48 56/53, 96 heads T 80 83/97, T 96 108/97, 128 heads T 96
 // 111/117, T 128 138/119, 256 heads T 256 511/530; bfloat16 T 32 30/33, T 48 34/34,
@@ -348,7 +370,15 @@ int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, int C, sfda_
         if (!few || BH * slices > 144) return 0;
         return T <= 2560 || sfda_chunk_fwd_auto_segments(B, H, T, m, n, C, in_dtype) == 1 ? 1 : 0;
     }
-    return factored_faster(BH, T, m, n, in_dtype == SFDA_BF16, decoupled != 0) ? 1 : 0;
+    if (!factored_faster(BH, T, m, n, in_dtype == SFDA_BF16, decoupled != 0)) return 0;
+    if (!decoupled) {
+        const long cus = device_cus();
+        const int G = sfda_chunk_fwd_auto_segments(B, H, T, m, n, C, in_dtype);
+        if (G > 1 && segments_us(BH, T, m, n, G, false, cus) < prepared_us(T, sfda::factored_plan(BH, T, m, n, false, false,
+                sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_dtype, 0), cus)))
+            return 0;
+    }
+    return 1;
 }
 
 // the checks of both factored entry points past sfda_chunk_fwd's, then the launches
@@ -489,37 +519,62 @@ static sfda_status_t segmented_impl(const void* q, const void* k, const void* v,
 
     const hipStream_t st = static_cast<hipStream_t>(stream);
     sfda::ChunkLaunch L;
-    L.q = q; L.k = k; L.v = v; L.alpha = alpha; L.theta = theta; L.beta = beta;
-    L.m = m; L.n = n; L.C = C;
+    L.q = q; L.k = k; L.alpha = alpha; L.theta = theta; L.beta = beta;
+    L.m = m; L.C = C;
     L.in_bf16 = in_dtype == SFDA_BF16;
     L.out_bf16 = out_dtype == SFDA_BF16;
     if (in_dtype == SFDA_F32) {
-        // the factored forward needs no segments: the workspace holds its operand records, one
-        // piece of the sequence at a time.  Where not even one step's records fit (a few
-        // hundred tokens, few columns) one scan per head takes less time than two launches.
-        L.B = B; L.H = H; L.T = T; L.S0 = S0; L.S_T = S_T; L.o = o;
-        L.slice = auto_slice(BH, n);
-        const bool fits = factored_fits(BH, n) && sfda::factored_bytes(BH, T, m, n, false, false, 0) <= need;
-        const hipError_t e = fits ? sfda::launch_factored(L, workspace, need, device_cus(), st) : sfda::launch_chunk(L, st);
-        return e == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
+        // the workspace holds the operand records of a piece of the sequence: where that is the
+        // faster one, the factored forward, which needs no segments
+        const long cus = device_cus() > 0 ? device_cus() : 256;
+        const sfda::FactoredPlan p = sfda::factored_plan(BH, T, m, n, false, false, need, cus);
+        const bool fits = factored_fits(BH, n) && p.piece > 0;
+        if (G == 1 || (fits && prepared_us(T, p) <= segments_us(BH, T, m, n, G, L.out_bf16, cus))) {
+            L.v = v; L.B = B; L.H = H; L.T = T; L.n = n; L.S0 = S0; L.S_T = S_T; L.o = o;
+            L.slice = auto_slice(BH, n);
+            const hipError_t e = fits ? sfda::launch_factored(L, workspace, need, device_cus(), st) : sfda::launch_chunk(L, st);
+            return e == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
+        }
     }
     const long segs = BH * G;
     float* P = static_cast<float*>(workspace);                      // [segs][m][m]
     float* Bs = P + segs * m * m * 2;                               // [segs][m][n]
     float* Sin = Bs + segs * static_cast<long>(m) * n * 2;          // [segs][m][n]
+    float* X = Sin + segs * static_cast<long>(m) * n * 2;           // [segs][T / G][m], float32 inputs
     // [B, H, T, .] with T = G * Ts is [B*H*G, Ts, .]: each segment runs as a head
-    L.B = static_cast<int>(segs); L.H = 1; L.T = T / G;
-    // P_g: S0 = I, v = 0, in place on the identity
-    if (sfda::launch_identity(P, segs, m, st) != hipSuccess) return SFDA_ERR_HIP;
-    L.v = nullptr; L.S0 = P; L.S_T = P; L.o = nullptr;
-    L.n = m; L.slice = ((m + 7) / 8) * 8;
-    if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
-    // B_g
-    L.v = v; L.S0 = nullptr; L.S_T = Bs;
-    L.n = n; L.slice = slice_n;
-    if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
-    // incoming states and S_T, then the outputs from the exact incoming states
+    const int Ts = T / G;
+    // float32 inputs and outputs: the outputs come from the zero-state pass and a join
+    // (o0 + S_in^* X), cheaper than a third pass of the latency-bound float32 scan; bfloat16
+    // inputs: a third pass of the pipelined kernel from the incoming states (cheaper than
+    // writing X in float32 and the join); a bfloat16 o of float32 inputs: a third pass too
+    // (the join would round it twice)
+    const bool join = in_dtype == SFDA_F32 && !L.out_bf16;
+    L.B = static_cast<int>(segs); L.H = 1; L.T = Ts;
+    if (in_dtype == SFDA_F32 && n <= 64) {
+        // P_g and B_g in one scan per segment (one copy of the chunk factors): the transfer
+        // columns from I_m with X_t = P_t^* q_t, the value columns from zero with o0 into o
+        L.v = v; L.S0 = nullptr; L.S_T = Bs; L.o = join ? o : nullptr;
+        L.n = n; L.slice = slice_n; L.xo = join ? X : nullptr; L.pend = P;
+        if (sfda::launch_chunk_segment(L, st) != hipSuccess) return SFDA_ERR_HIP;
+    } else {
+        // P_g (and with the join X_t = P_t^* q_t, the m-column float32 output): S0 = I,
+        // v = 0, in place on the identity
+        if (sfda::launch_identity(P, segs, m, st) != hipSuccess) return SFDA_ERR_HIP;
+        L.v = nullptr; L.S0 = P; L.S_T = P; L.o = join ? X : nullptr; L.out_bf16 = false;
+        L.n = m; L.slice = ((m + 7) / 8) * 8;
+        if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
+        // B_g (and with the join the zero-state outputs o0, into o)
+        L.v = v; L.S0 = nullptr; L.S_T = Bs; L.o = join ? o : nullptr; L.out_bf16 = out_dtype == SFDA_BF16;
+        L.n = n; L.slice = slice_n;
+        if (sfda::launch_chunk(L, st) != hipSuccess) return SFDA_ERR_HIP;
+    }
+    // incoming states and S_T
     if (sfda::launch_fold(P, Bs, Sin, S0, S_T, BH, G, m, n, st) != hipSuccess) return SFDA_ERR_HIP;
+    if (join) {
+        // o = o0 + S_in^* X (the affine law of each segment, token by token)
+        return sfda::launch_join(X, Sin, static_cast<float*>(o), segs, Ts, m, n, st) == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
+    }
+    // outputs from the exact incoming states
     L.S0 = Sin; L.S_T = nullptr; L.o = o;
     return sfda::launch_chunk(L, st) == hipSuccess ? SFDA_OK : SFDA_ERR_HIP;
 }

@@ -1589,6 +1589,28 @@ size_t factored_bytes(long heads, int T, int m, int n, bool in_bf16, bool dec, s
     return static_cast<size_t>(piece) * one + (piece < steps ? static_cast<size_t>(heads) * m * n * 8 : 0);
 }
 
+FactoredPlan factored_plan(long heads, int T, int m, int n, bool in_bf16, bool dec, size_t bytes, long cus)
+{
+    using namespace fac;
+    const bool bf = bf16_operands(in_bf16, m);
+    const long steps = (static_cast<long>(T) + CP - 1) / CP, one = fac_step_bytes(heads, m, bf, dec);
+    const long carry_bytes = heads * m * static_cast<long>(n) * 8;
+    const bool whole = static_cast<size_t>(steps) * one <= bytes;
+    FactoredPlan p{whole ? steps : (static_cast<long>(bytes) - carry_bytes) / one, false};
+    if (p.piece < 1) return FactoredPlan{0, false};
+    const long most = 0x7FFFFFFFL / heads;              // workgroups of a launch
+    if (p.piece > most) p.piece = most;
+    // float32 scans on at most half of the compute units: each piece's scan with the next one's
+    // preparation beside it, the records in two halves of the workspace (H16 T65536: 3.86 ms
+    // one after the other)
+    const int cols = bf ? BCOLS : FCOLS;
+    if (!dec && !in_bf16 && 2 * scan_grid(heads, (n + cols - 1) / cols) <= cus && steps >= 8) {
+        const long half = whole ? (steps + 3) / 4 : p.piece / 2;
+        if (half >= 1 && static_cast<size_t>(2 * half * one + carry_bytes) <= bytes) p = FactoredPlan{half, true};
+    }
+    return p;
+}
+
 hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus, hipStream_t st)
 {
     using namespace fac;
@@ -1597,11 +1619,10 @@ hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus
     const int steps = (L.T + CP - 1) / CP;
     const long one = fac_step_bytes(heads, L.m, bf, dec);
     const long carry_bytes = heads * L.m * static_cast<long>(L.n) * 8;
-    const bool whole = static_cast<size_t>(steps) * one <= bytes;
-    long piece = whole ? steps : (static_cast<long>(bytes) - carry_bytes) / one;
+    const FactoredPlan plan = factored_plan(heads, L.T, L.m, L.n, L.in_bf16, dec, bytes, cus);
+    const long piece = plan.piece;
+    const bool beside = plan.beside;
     if (piece < 1) return hipErrorInvalidValue;
-    const long most = 0x7FFFFFFFL / heads;              // workgroups of a launch
-    if (piece > most) piece = most;
     // the state between pieces: S_T where the caller wants it, else the end of the workspace
     float* carry = L.S_T ? L.S_T : reinterpret_cast<float*>(static_cast<char*>(ws) + bytes - carry_bytes);
 
@@ -1609,18 +1630,7 @@ hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus
     const int cols = bf ? BCOLS : FCOLS;
     sa.n_slices = (L.n + cols - 1) / cols;
     PrepArgs pa{L.q, L.k, L.alpha, L.theta, L.beta, L.r, L.wbeta, static_cast<char*>(ws), L.T, L.m, 0, 0, sa.lay, BwdLayout(L.m, bf)};
-    // float32 scans on at most half of the compute units: each piece's scan with the next one's
-    // preparation beside it, the records in two halves of the workspace (H16 T65536: 3.86 ms
-    // one after the other)
     const long nscan = scan_grid(heads, sa.n_slices);
-    bool beside = false;
-    if (!dec && !L.in_bf16 && 2 * nscan <= cus && steps >= 8) {
-        const long half = whole ? (steps + 3) / 4 : piece / 2;
-        if (half >= 1 && static_cast<size_t>(2 * half * one + carry_bytes) <= bytes) {
-            beside = true;
-            piece = half;
-        }
-    }
     for (int s = 0, half = 0; s < steps; s += static_cast<int>(piece), half ^= beside) {
         const int here = steps - s < piece ? steps - s : static_cast<int>(piece);
         const int after = steps - s - here < piece ? steps - s - here : static_cast<int>(piece);

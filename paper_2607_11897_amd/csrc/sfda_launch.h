@@ -39,6 +39,11 @@ struct ChunkLaunch {
     // strengths wbeta; beta holds the erase strengths
     const void* r = nullptr;
     const void* wbeta = nullptr;
+    // segment forward (launch_chunk_segment): beside the value columns (from S0 = 0 when
+    // S0 is null) the m columns of the homogeneous transfer from I_m, with outputs
+    // X_t = P_t^* q_t [heads][T][m] and the last transfer [heads][m][m] (complex fp32)
+    float* xo = nullptr;
+    float* pend = nullptr;
 };
 
 // per-chunk gradient pass of the backward (one workgroup per head and chunk)
@@ -68,12 +73,17 @@ hipError_t launch_step(const StepLaunch& L, hipStream_t st);
 hipError_t launch_chunk(const ChunkLaunch& L, hipStream_t st);
 hipError_t launch_chunk_bf16(const ChunkLaunch& L, hipStream_t st);   // bf16 inputs
 hipError_t launch_chunk_decoupled(const ChunkLaunch& L, hipStream_t st);   // C = 16 or 32
+hipError_t launch_chunk_segment(const ChunkLaunch& L, hipStream_t st);
 // the factored forward (sfda_factored.h; write-decoupled when L.r is set): operand records of
 // as many 64-token steps at a time as `bytes` of workspace hold, then a scan over them.
 // factored_bytes: the workspace that holds `cap` bytes of records (at least one step's, at
 // most the whole sequence's), with the state carried between pieces
 size_t factored_bytes(long heads, int T, int m, int n, bool in_bf16, bool dec, size_t cap);
-hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus, hipStream_t st);   // cus: compute units
+// how a workspace of `bytes` cuts the sequence: 64-token steps per piece (0: it holds none), and
+// whether each piece's scan runs beside the next one's preparation; cus: compute units
+struct FactoredPlan { long piece; bool beside; };
+FactoredPlan factored_plan(long heads, int T, int m, int n, bool in_bf16, bool dec, size_t bytes, long cus);
+hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus, hipStream_t st);
 // the backward on operand records (sfda_factored.h): preparation, both scans, gradient kernel;
 // F, A as launch_bwd_scans without the records, G without them too; ws of bwd_factored_bytes
 bool bwd_factored_fits(long heads, int T, int n);
@@ -87,8 +97,11 @@ hipError_t launch_bwd_scans(const ChunkLaunch& F, const ChunkLaunch& A, hipStrea
 hipError_t launch_chunk_grad(const GradLaunch& L, hipStream_t st);
 // per 16-token block: the triangular solve's residual and ||D_beta L'||_F ([B, H, ceil(T / 16)])
 hipError_t launch_solve_monitor(const ChunkLaunch& L, float* residual, float* lnorm, hipStream_t st);
-// segment-parallel scan: identity fill and the fold of the segments' affine maps
+// segment-parallel scan: identity fill, the fold of the segments' affine maps and the join of
+// the outputs (o += S_in^* X)
 hipError_t launch_identity(float* P, long count, int m, hipStream_t st);
+hipError_t launch_join(const float* X, const float* Sin, float* o, long segs, int Ts, int m, int n,
+                       hipStream_t st);
 hipError_t launch_fold(const float* P, const float* Bs, float* Sin, const float* S0, float* S_T,
                        long heads, int G, int m, int n, hipStream_t st);
 

@@ -79,9 +79,7 @@ def test_segmented_f32(B, H, T, m, n, C, G):
 
 @pytest.mark.parametrize("m,n,G", [(64, 40, 4), (21, 64, 2)])
 def test_segmented_f32_in_bf16_out(m, n, G):
-    """float32 inputs, bfloat16 output: the segment scans store o0 in bfloat16 and the join
-    adds S_in^* X in float32 before rounding once more; o within the bf16 bar, S_T (float32)
-    within 1e-4."""
+    """float32 inputs, bfloat16 output: o within the bf16 bar, S_T (float32) within 1e-4."""
     import torch
     from paper_2607_11897_amd import sfda
     x = make(2, 1, 256, m, n, 16, seed=17)
@@ -219,3 +217,80 @@ def test_default_picks_segments_for_few_heads():
     eo, es = rel_err(to_complex(o1), o_ref), rel_err(to_complex(S1), S_ref)
     say("default segments err(o)", eo, "err(S_T)", es)
     assert eo <= 1e-4 and es <= 1e-4
+
+
+def _segments_and_factored(x, C, G, out_dtype=None, in_place=False):
+    """chunk_fwd over G segments, and the factored forward's result (C entry)."""
+    import ctypes
+    import torch
+    from paper_2607_11897_amd import sfda
+    lib = sfda.load_library()
+    d = upload(x)
+    args = (d["q"], d["k"], d["v"], d["alpha"], d["theta"], d["beta"])
+    B, H, T, m, n = x.shape
+    od = torch.bfloat16 if out_dtype == "bf16" else torch.float32
+    need = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, 0, 0)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    of = torch.full((B, H, T, n, 2), float("nan"), device="cuda", dtype=od)
+    Sf = torch.full((B, H, m, n, 2), float("nan"), device="cuda")
+    p = lambda t: None if t is None else ctypes.c_void_p(t.data_ptr())
+    assert lib.sfda_chunk_fwd_factored(*map(p, args), p(d["S0"]), p(of), p(Sf), B, H, T, m, n, C, 0, int(od == torch.bfloat16),
+                                       p(ws), need, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    o = torch.full_like(of, float("nan"))
+    o, S = sfda.chunk_fwd(*args, d["S0"], C=C, segments=G, o=o, out_dtype=od, S_T=d["S0"] if in_place else None)
+    torch.cuda.synchronize()
+    return o, S, of, Sf
+
+
+STRONG = I.Laws(alpha=("uniform", 0.02, 0.1), theta=("uniform", -3.14159, 3.14159), beta=("uniform", 0.0, 1.0),
+                s0_scale=0.1)
+
+
+@pytest.mark.parametrize("B,H,T,m,n,C,G,out,laws", [
+    (1, 1, 4096, 16, 16, 64, 16, "f32", I.LAWS_MAIN),
+    (1, 2, 1024, 5, 3, 16, 8, "f32", I.LAWS_MAIN),          # ragged channels and columns
+    (2, 1, 8192, 33, 33, 64, 32, "f32", I.LAWS_MAIN),
+    (1, 1, 8192, 64, 64, 64, 32, "f32", I.LAWS_LONG),
+    (1, 1, 8192, 17, 72, 64, 32, "f32", I.LAWS_MAIN),       # past 64 columns: two passes
+    (1, 1, 4096, 12, 24, 16, 16, "f32", STRONG),            # transfers below the float range
+    (1, 2, 8192, 20, 9, 64, 32, "bf16", I.LAWS_MAIN),       # bfloat16 o: a third pass, rounded once
+    (1, 1, 8192, 8, 80, 64, 32, "bf16", I.LAWS_MAIN),
+])
+def test_few_heads_long_sequences_run_segments(B, H, T, m, n, C, G, out, laws):
+    """float32 where G segments are faster than one scan on prepared operands: other bits than the
+    factored forward's, both within the bar of the oracle, and of each other (float32: each within
+    2e-6 relative 2-norm at these lengths; bfloat16 o: one rounding each, 2^-8 of the value)."""
+    import torch
+    x = I.make_chunk_inputs(I.Workload("seg_long", B, H, T, m, n, C, "f32", laws, 31, 1e-4))
+    say((B, H, T, m, n), "C", C, "G", G, out)
+    o, S, of, Sf = _segments_and_factored(x, C, G, out, in_place=True)
+    assert not torch.equal(S, Sf)                           # (the factored forward would give these bits)
+    rel = lambda a, b: float((a.double() - b.double()).norm() / b.double().norm())
+    say("o", rel(o, of), "S", rel(S, Sf))
+    assert rel(o, of) <= (4e-6 if out == "f32" else 2 ** -8) and rel(S, Sf) <= 4e-6
+    o_ref, S_ref = run_oracle(x)
+    assert rel_err(to_complex(o), o_ref) <= (1e-4 if out == "f32" else 2 ** -8) and rel_err(to_complex(S), S_ref) <= 1e-4
+
+
+def test_default_float32_long_few_heads():
+    """The default takes segments where they are faster, and the prepared operands elsewhere."""
+    import torch
+    from paper_2607_11897_amd import sfda
+    lib = sfda.load_library()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if cus == 256:
+        for heads, T, m, n, want in ((1, 65536, 64, 64, 0), (1, 16384, 64, 64, 0), (1, 4096, 64, 64, 1), (16, 65536, 64, 64, 1),
+                                     (4, 4096, 16, 16, 0), (4, 2048, 16, 16, 1), (16, 65536, 16, 16, 0), (32, 16384, 64, 64, 1)):
+            assert lib.sfda_chunk_fwd_auto_factored(1, heads, T, m, n, 64, 0, 0) == want, (heads, T, m, n)
+    x = I.make_chunk_inputs(I.Workload("seg_default", 1, 1, 16384, 8, 8, 64, "f32", I.LAWS_LONG, 33, 1e-4))
+    d = upload(x)
+    args = (d["q"], d["k"], d["v"], d["alpha"], d["theta"], d["beta"], d["S0"])
+    G = sfda.auto_segments(1, 1, 16384, 8, 8)
+    say("default, segments", G)
+    assert G > 1
+    o1, S1 = sfda.chunk_fwd(*args)
+    o2, S2 = sfda.chunk_fwd(*args, segments=G)
+    torch.cuda.synchronize()
+    assert torch.equal(o1, o2) and torch.equal(S1, S2)
+    o_ref, S_ref = run_oracle(x)
+    assert rel_err(to_complex(o1), o_ref) <= 1e-4 and rel_err(to_complex(S1), S_ref) <= 1e-4
