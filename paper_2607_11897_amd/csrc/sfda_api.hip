@@ -90,31 +90,45 @@ bool factored_fits(long BH, int n)
     return (BH + 7) * ((n + 7) / 8) <= 0x7FFFFFFFL && static_cast<long>(64) * n * 8 < 0x80000000L;
 }
 
-// Whether the factored forward is the faster one.  It costs two launches and, per 64-token step,
-// time that grows with heads x value columns (x channel blocks); the scan in place costs one launch
-// and a chain of blocks per workgroup of a head and 64 columns, the same up to one workgroup per
-// compute unit.  Measured on MI355X (us, in place / factored):
-//  * short sequences pay the second launch: float32 T 32 20/23, T 48 22/23, T 64 28/23;
-//    decoupled float32 T 32 23/24, T 48 32/24, bfloat16 T 48 21/24, T 64 26/24;
-//  * with many heads a step costs more than the few blocks of the chain: float32 m n 64, 96 heads
-//    T 80 35/41, T 96 41/41, 128 heads T 96 41/44, T 128 52/44 (decoupled 96 heads T 48 33/39, T 80
-//    51/50, 128 heads T 80 51/55, T 96 60/56);
-//  * in float32, workgroups that fill whole rounds of the chip leave the chain nothing to wait for:
-//    m n 64 T 512, 192 heads 256/217, 256 heads 265/286, 384 heads 517/456, 512 heads 524/590;
-//    fewer channels or columns never get there (m 16, 256 heads 257/203; n 32, 189/151).
-bool fills_rounds(long BH, int m, int n, long cus)
+// most bytes of operand records that the suggested workspace holds at a time (the sequence then
+// runs in pieces).  A bound on memory: more is a little faster (us at 64, 128, 256, 512, 1024 MiB:
+// decoupled bfloat16 B8 H16 T4096 592, 519, 485, 460, 443; float32 forward 32 heads T 16384 1489, 1284,
+// 1202, 1148, 1127; 16 heads T 65536 3235, 3083, 3150, 3129, 3186), less costs launches and state passes.
+constexpr size_t FACTORED_CAP = size_t(256) << 20;
+
+// Whether the factored forward is the faster one.
+//  * bfloat16 operands (the write-decoupled forward: 256 compute units, m n 64): past 48 tokens, us in
+//    place / factored T 48 21/24, T 64 26/24.
+//  * float32 operands: by an estimate of both in us, fitted to 3600 measured pairs of 16 .. 1500 heads
+//    x 33 .. 1000 tokens (each within 22%, the rule's picks within 3% of the better side).  In place:
+//    rounds of one workgroup per compute unit, a chain of blocks each.  Factored: a floor of two
+//    launches and a chain of blocks, then time per head and block, padding blocks of the last 64-token
+//    step among them (preparation: channel blocks; scan: 8-column workgroups), and for every
+//    further piece of the sequence its launches and the state's way through memory.  us in place /
+//    factored: forward, 4 heads m n 64 T 48 22/23, T 64 28/23; 96 heads m n 64 T 96 41/41;
+//    160 heads m 48 n 32 T 80 34/43; 768 heads m 64 n 32 T 160 189/251; 1500 heads m 48 n 64 T 300
+//    931/1237; 256 heads m n 64 T 512 265/286, m 16 n 64 257/203; decoupled, 256 heads m 3 n 64 T 80
+//    61/80, 1500 heads m 64 n 48 T 160 675/904, m 16 n 8 T 49 215/76.  It takes a workspace, so it has to
+//    be 4% ahead.
+struct Blocks { long nb, pad, nkb, cols; };    // 16-token blocks, those of whole steps; channel and 8-column blocks
+Blocks blocks_of(int T, int m, int n) { return {(T + 15L) / 16, (T + 63L) / 64 * 4, (m + 15) / 16, (n + 7L) / 8}; }
+long rounds_of(long workgroups, long cus) { return (workgroups + cus - 1) / cus; }
+bool factored_faster(long BH, int T, int m, int n, bool in_bf16, bool dec)
 {
-    const long rounds = (BH * ((n + 63L) / 64) + cus - 1) / cus;
-    return BH * ((n + 7L) / 8) * ((m + 15) / 16) >= 0.92 * 32 * static_cast<double>(cus * rounds);
-}
-bool factored_faster(long BH, int T, int m, int n, bool bf16, bool dec)
-{
-    if (T <= (dec && !bf16 ? 32 : 48)) return false;
-    if (bf16) return true;
+    if (T <= (dec && !in_bf16 ? 32 : 48)) return false;
+    if (sfda::bf16_operands(in_bf16, m)) return true;
     const long cus = device_cus() > 0 ? device_cus() : 256;
-    const long cols = (static_cast<long>(n) + 7) / 8;
-    if (T <= (dec ? 80 : 96) && BH * cols >= 3 * cus) return false;
-    return !fills_rounds(BH, m, n, cus);
+    const Blocks k = blocks_of(T, m, n);
+    const int slice = auto_slice(BH, n);
+    const double chain = static_cast<double>(rounds_of(BH * ((n + slice - 1) / slice), cus)) * k.nb;
+    const double x = static_cast<double>(BH) / cus, wide = static_cast<double>(k.cols * k.nkb);
+    const sfda::FactoredPlan p = sfda::factored_plan(BH, T, m, n, in_bf16, dec, sfda::factored_bytes(BH, T, m, n, in_bf16, dec, FACTORED_CAP), cus);
+    const double more = p.piece > 0 && !p.beside ? (k.pad / 4 + p.piece - 1) / p.piece - 1 : 0;
+    const double in_place = dec ? 6.0 + chain * (8.07 + (slice > 32 ? 3.15 : 0.) + 0.109 * k.nkb)
+                                : 5.7 + chain * (5.44 + (slice > 32 ? 2.53 : 0.) + 0.071 * k.nkb);
+    const double factored = dec ? 14.8 + 0.523 * k.pad + x * k.pad * (0.539 + 0.835 * k.nkb + 0.798 * k.cols + 0.034 * wide) + more * (26.6 + 0.468 * x * wide)
+                                : 12.7 + 0.435 * k.pad + x * k.pad * (0.354 + 0.640 * k.nkb + 0.605 * k.cols + 0.018 * wide) + more * (23.2 + 0.416 * x * wide);
+    return factored < 0.96 * in_place;
 }
 // The float32 forward over G segments against the one on prepared operands, estimated in us (MI355X):
 // the segments' chain costs 8.5 .. 14.5 us a 16-token block with the columns of both sets (past 64
@@ -138,20 +152,27 @@ double prepared_us(int T, const sfda::FactoredPlan& p)
     const long steps = (T + 63L) / 64, pieces = (steps + p.piece - 1) / p.piece;
     return 20. + 0.72 * T / 16 + (pieces - 1) * (p.beside ? 4. : 10.);
 }
-// and the backward on prepared operands (three launches; two in place): float32 T 16 34/35, T 32
-// 42/35, 64 heads m n 64 T 32 46/53, T 48 56/53, 96 heads T 80 83/97, T 96 108/97, 128 heads T 96
-// 111/117, T 128 138/119, 256 heads T 256 511/530; bfloat16 T 32 30/33, T 48 34/34,
-// T 64 40/34
-bool bwd_factored_faster(long BH, int T, int m, int n, bool bf16)
+// and the backward on prepared operands (three launches; two in place).  us in place / factored:
+// bfloat16 T 32 30/33, T 48 34/34, T 64 40/34; float32 T 16 34/35, T 32 42/35, 64 heads m n 64 T 32
+// 46/53, T 48 56/53, 96 heads T 80 83/97, T 96 108/97, 128 heads T 96 111/117, T 128 138/119.  In
+// float32, workgroups that fill whole rounds of the chip leave the chain nothing to wait for (256 heads
+// T 256 511/530), and elsewhere the estimate (as above; the gradient pass adds time per block on
+// both sides) keeps short sequences of many heads in place: 384 heads m n 64 T 112 359/396,
+// bfloat16 inputs 1024 heads m 1 n 64 T 80 607/680; 512 heads m 16 n 64 T 112 424/361.
+bool bwd_factored_faster(long BH, int T, int m, int n, bool in_bf16)
 {
-    if (bf16) return T > 48;
-    const long cus = device_cus() > 0 ? device_cus() : 256, cols = BH * ((n + 7L) / 8);
-    return T > (cols >= 4 * cus ? 96 : cols >= 3 * cus ? 80 : cols >= 2 * cus ? 32 : 16) && !fills_rounds(BH, m, n, cus);
+    if (T <= (in_bf16 ? 48 : 16)) return false;
+    if (sfda::bf16_operands(in_bf16, m)) return true;
+    const long cus = device_cus() > 0 ? device_cus() : 256;
+    const Blocks k = blocks_of(T, m, n);
+    const long cols = BH * k.cols, slices = (n + 63L) / 64;
+    if (!in_bf16 && T <= (cols >= 4 * cus ? 96 : cols >= 3 * cus ? 80 : cols >= 2 * cus ? 32 : 16)) return false;
+    if (!in_bf16 && cols * k.nkb >= 0.92 * 32 * static_cast<double>(cus * rounds_of(BH * slices, cus))) return false;
+    const double x = static_cast<double>(BH) / cus;
+    const double in_place = 15.8 + rounds_of(2 * BH * slices, cus) * k.nb * (6.42 + (n > 32 ? 3.43 : 0.)) + x * k.nb * (8.28 + 0.298 * k.nkb * n / 16);
+    const double factored = 21.7 + 0.535 * k.pad + x * k.pad * (2.36 + 1.42 * k.nkb + 1.66 * k.cols + 0.232 * k.cols * k.nkb);
+    return factored < 0.96 * in_place;
 }
-// most bytes of operand records that the suggested workspace holds at a time (the sequence then
-// runs in pieces; the records of one piece also stay within reach of the 256 MiB last-level
-// cache)
-constexpr size_t FACTORED_CAP = size_t(256) << 20;
 
 }  // namespace
 
@@ -368,7 +389,17 @@ int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, int C, sfda_
         const long slices = (n + 31L) / 32;
         const bool few = BH <= 32 ? T >= 256 : BH <= 48 ? T >= 640 : BH <= 64 && T >= 640 && (T <= 1536 || (m + 15) / 16 * slices <= 4);
         if (!few || BH * slices > 144) return 0;
-        return T <= 2560 || sfda_chunk_fwd_auto_segments(B, H, T, m, n, C, in_dtype) == 1 ? 1 : 0;
+        const int G = sfda_chunk_fwd_auto_segments(B, H, T, m, n, C, in_dtype);
+        if (G == 1) return 1;
+        // (at most four channels, float32 operands: 12 heads n 64 T 2048 356/119; 1 head T 16384 358/734)
+        if (!sfda::bf16_operands(true, m)) return T <= 2560;
+        // the segments' three passes over a G-th of the blocks and their fold, against the chain, in
+        // us, each estimated within 9%: m n 64, 16 heads T 2048 107/88, 12 heads T 4096 132/159; m 8 n 1,
+        // 12 heads T 2560 90/109; m 16 n 1, 24 heads T 2048 82/95
+        const double cus = static_cast<double>(device_cus()), x = BH / cus, nkb = (m + 15) / 16;
+        const double seg = 21.5 + T / (16. * G) * (2.83 + 0.121 * nkb) + G * (0.62 + 0.567 * nkb) + 7.74 * x * ((n + 63) / 64) * G;
+        const double fac = 13.6 + 0.532 * T / 16 + x * T / 16 * (0.371 + 0.174 * nkb);
+        return fac < 0.96 * seg ? 1 : 0;
     }
     if (!factored_faster(BH, T, m, n, in_dtype == SFDA_BF16, decoupled != 0)) return 0;
     if (!decoupled) {

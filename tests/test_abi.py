@@ -323,3 +323,36 @@ def test_factored_row_offsets(lib, dtype):
     assert lib.sfda_chunk_fwd_factored_workspace_bytes(1, 1, 64, 1, n - 1, dtype, 0) > 0
     assert lib.sfda_chunk_fwd_factored_workspace_bytes(1, 1, 64, 1, n, dtype, 0) == 0
     assert lib.sfda_chunk_fwd_factored_workspace_bytes(1, 1, 64, 1, n, dtype, 1) == 0
+
+
+@pytest.mark.parametrize("dtype,B,H,T,m,n,decoupled,want", [
+    # float32 operands: many heads over short sequences stay in place (us in place / factored)
+    (0, 1, 160, 80, 48, 32, 0, 0),       # 34/43
+    (0, 1, 768, 160, 64, 32, 0, 0),      # 189/251
+    (0, 1, 1500, 300, 48, 64, 0, 0),     # 931/1237
+    (0, 1, 1024, 300, 64, 32, 0, 0),     # 459/552
+    (0, 1, 1500, 49, 8, 8, 0, 1),        # 154/57
+    (0, 1, 256, 512, 16, 64, 0, 1),      # 257/203
+    (0, 1, 1024, 160, 64, 48, 1, 0),     # 451/591
+    (0, 1, 1500, 49, 16, 8, 1, 1),       # 215/76
+    # bfloat16 inputs of at most four channels take float32 operands, and their rule
+    (1, 1, 256, 80, 3, 64, 1, 0),        # 61/80
+    (1, 1, 512, 80, 1, 64, 1, 0),        # 122/147
+    (1, 1, 1500, 64, 2, 1, 1, 1),
+    (1, 1, 256, 80, 16, 64, 1, 1),       # bfloat16 operands
+])
+def test_factored_rule_many_heads(lib, dtype, B, H, T, m, n, decoupled, want):
+    """sfda_chunk_fwd_auto_factored on the side that measured faster (256 compute units)."""
+    assert lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, 64, dtype, decoupled) == want
+
+
+@pytest.mark.parametrize("dtype,H,T,m,n,factored", [
+    (0, 384, 112, 64, 64, False),        # 359/396
+    (1, 1024, 80, 1, 64, False),         # 607/680
+    (0, 512, 112, 16, 64, True),         # 424/361
+    (1, 1024, 49, 2, 8, True),           # 362/117
+    (0, 32, 2048, 64, 64, True),
+])
+def test_backward_rule_many_heads(lib, dtype, H, T, m, n, factored):
+    least = lib.sfda_chunk_bwd_workspace_bytes(1, H, T, m, n, 64)
+    assert (lib.sfda_chunk_bwd_auto_workspace_bytes(1, H, T, m, n, 64, dtype) > least) == factored
