@@ -409,7 +409,8 @@ def chunk_bwd(q, k, v, alpha, theta, beta, S0, dO, dS_T=None, C: int = 64, *,
         if workspace is None:
             nws = lib.sfda_chunk_bwd_workspace_bytes(B, H, T, m, n, C)
             workspace = _workspace(max(nws, 1), q.device, stream)
-    _check(dict(q=(q, (B, H, T, m, 2)), workspace=(workspace, tuple(workspace.shape))))
+    else:
+        _check(dict(q=(q, (B, H, T, m, 2)), workspace=(workspace, tuple(workspace.shape))))
     st = lib.sfda_chunk_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(theta), _ptr(beta), _ptr(S0),
                             _ptr(dO), _ptr(dS_T), _ptr(g["dq"]), _ptr(g["dk"]), _ptr(g["dv"]),
                             _ptr(g["dalpha"]), _ptr(g["dtheta"]), _ptr(g["dbeta"]), _ptr(g["dS0"]),
