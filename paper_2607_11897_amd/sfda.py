@@ -208,11 +208,10 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
     slice: value columns per workgroup (sfda_chunk_fwd_sliced); segments: G parallel
     segments per head (sfda_chunk_fwd_segmented; `workspace` a uint8 device tensor of at
     least segmented_workspace_bytes(...) bytes, allocated here when not given), None for one
-    scan per head (sfda_chunk_fwd), or "auto" (the default).  "auto" runs sfda_chunk_fwd_factored
-    where sfda_chunk_fwd_auto_factored says so (whatever the slice: no column's arithmetic depends
-    on it), else, without a slice, the count sfda_chunk_fwd_auto_segments suggests: segments when
-    the heads alone would leave most compute units idle.  Workspaces not given come from torch's
-    allocator."""
+    scan per head (sfda_chunk_fwd), or "auto" (the default, without a slice): sfda_chunk_fwd_factored
+    where sfda_chunk_fwd_auto_factored says so, else the count sfda_chunk_fwd_auto_segments
+    suggests: segments when the heads alone would leave most compute units idle.  Workspaces not
+    given come from torch's allocator."""
     import torch
     lib = load_library()
     B, H, T, m, _ = _dims(q, v, 5)
@@ -239,10 +238,8 @@ def chunk_fwd(q, k, v, alpha, theta, beta, S0=None, C: int = 64, *, o=None, S_T=
             raise ValueError(f"segments must be an int, None or 'auto', not {segments!r}")
         segments = None
         nfac = 0
-        # (a slice the library refuses goes to sfda_chunk_fwd_sliced, which says so; a workspace
-        # the caller sized for segments keeps them)
-        if workspace is None and (slice is None or (8 <= slice <= 64 and slice % 8 == 0)) and \
-                lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, C, in_code, 0):
+        # (a slice asks for sfda_chunk_fwd_sliced; a workspace the caller sized for segments keeps them)
+        if workspace is None and slice is None and lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, C, in_code, 0):
             nfac = lib.sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_code, 0)
         ws = _try_workspace(nfac, q.device, stream) if nfac else None
         if ws is not None:

@@ -306,6 +306,38 @@ def test_bf16_odd_shapes(m, n):
     check(small(T=70, m=m, n=n, B=2, H=1, dtype="bf16"), 16, 2e-2, label=f"bf16 m{m}n{n}")
 
 
+@pytest.mark.parametrize("slice", [8, 24, 64])
+@pytest.mark.parametrize("dtype,T", [("f32", 150), ("bf16", 300)])
+def test_slice_asks_for_the_sliced_scan(dtype, T, slice):
+    """chunk_fwd with a slice runs sfda_chunk_fwd_sliced, with no workspace, also where the default
+    runs on prepared operands: the C entry's bits, and nothing allocated but o and S_T."""
+    import ctypes
+    import torch
+    from paper_2607_11897_amd import sfda
+    lib = sfda.load_library()
+    x = small(T=T, B=1, H=2, n=72, dtype=dtype)
+    B, H, _, m, n = x.shape
+    code = sfda.SFDA_F32 if dtype == "f32" else sfda.SFDA_BF16
+    assert lib.sfda_chunk_fwd_auto_factored(B, H, T, m, n, 64, code, 0) == 1
+    say("sliced", dtype, slice)
+    d = upload(x)
+    args = [d[k] for k in ("q", "k", "v", "alpha", "theta", "beta", "S0")]
+    o1, S1 = torch.empty((B, H, T, n, 2), dtype=d["q"].dtype, device="cuda"), torch.empty((B, H, m, n, 2), device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert lib.sfda_chunk_fwd_sliced(*map(p, args), p(o1), p(S1), B, H, T, m, n, 64, slice, code, code,
+                                     ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    o, S = torch.empty_like(o1), torch.empty_like(S1)
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    sfda.chunk_fwd(*args, slice=slice, o=o, S_T=S)
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    torch.cuda.synchronize()
+    assert torch.equal(o, o1) and torch.equal(S, S1)
+    o_ref, S_ref = run_oracle(x)
+    tol = 1e-4 if dtype == "f32" else 2e-2
+    assert rel_err(to_complex(o), o_ref) <= tol and rel_err(to_complex(S), S_ref) <= tol
+
+
 @pytest.mark.parametrize("slice", [8, 16, 24, 32, 40, 64])
 def test_bf16_slices(slice):
     check(small(T=130, n=64, dtype="bf16"), 64, 2e-2, slice=slice, label=f"bf16 slice{slice}")
@@ -317,7 +349,7 @@ def test_slices_bitwise_equal(dtype):
     sfda_chunk_fwd picks by itself (32 columns when heads are few) changes no bit."""
     x = small(T=150, B=1, H=2, n=64, dtype=dtype)
     say("slices bitwise", dtype)
-    o0, S0 = run_chunk(x, 64)
+    o0, S0 = run_chunk(x, 64, segments=None)             # sfda_chunk_fwd
     for sl in (64, 32, 16):
         o, S = run_chunk(x, 64, slice=sl)
         assert np.array_equal(o, o0) and np.array_equal(S, S0), sl
