@@ -196,8 +196,9 @@ size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n
 /*
  * sfda_chunk_fwd_auto_factored -- 1 where the factored forward (decoupled: the write-decoupled one)
  * is the faster one on the current device, 0 where the one-launch entry point is: short sequences,
- * many heads (bfloat16 without decoupling: more than 64), and long sequences of few heads that
- * sfda_chunk_fwd_auto_segments splits.
+ * many heads (bfloat16 without decoupling: more than 64), long sequences of few heads that
+ * sfda_chunk_fwd_auto_segments splits, and so many heads that one 64-token step of them does not
+ * fit 256 MiB (up to 118 KiB a head, decoupled 150 KiB).
  */
 int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype,
                                  int decoupled);
@@ -330,6 +331,7 @@ size_t sfda_chunk_bwd_workspace_bytes(int B, int H, int T, int m, int n, int C);
  * current device, at least sfda_chunk_bwd_workspace_bytes (0 where that is): with more, where the
  * sequence is not short, the call prepares its scans' operands for all blocks in parallel (as
  * sfda_chunk_fwd_factored does; the same gradients up to rounding) and records fewer states.
+ * At most twice sfda_chunk_bwd_workspace_bytes or 1280 MiB more than it, whichever is more.
  */
 size_t sfda_chunk_bwd_auto_workspace_bytes(int B, int H, int T, int m, int n, int C,
                                            sfda_dtype_t in_dtype);

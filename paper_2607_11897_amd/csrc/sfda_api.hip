@@ -95,6 +95,9 @@ bool factored_fits(long BH, int n)
 // decoupled bfloat16 B8 H16 T4096 592, 519, 485, 460, 443; float32 forward 32 heads T 16384 1489, 1284,
 // 1202, 1148, 1127; 16 heads T 65536 3235, 3083, 3150, 3129, 3186), less costs launches and state passes.
 constexpr size_t FACTORED_CAP = size_t(256) << 20;
+// and what the backward's suggested workspace may take past the smaller one where it is more than
+// twice that: a training step has to fit beside it
+constexpr size_t BWD_EXTRA = size_t(1280) << 20;
 
 // Whether the factored forward is the faster one.
 //  * bfloat16 operands (the write-decoupled forward: 256 compute units, m n 64): past 48 tokens, us in
@@ -377,6 +380,8 @@ int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, int C, sfda_
 {
     if (sfda_chunk_fwd_factored_workspace_bytes(B, H, T, m, n, in_dtype, decoupled) == 0) return 0;
     const long BH = static_cast<long>(B) * H;
+    // (the workspace holds a step of every head: not past the bound on it)
+    if (sfda::factored_bytes(BH, 64, m, n, in_dtype == SFDA_BF16, decoupled != 0, 0) > FACTORED_CAP) return 0;
     if (in_dtype == SFDA_BF16 && !decoupled) {
         // against sfda_chunk_fwd's bfloat16 kernel, whose chain is 0.9 us a block where the scan on
         // prepared operands takes 0.5, and whose segments overtake both on long sequences.  us, in
@@ -657,9 +662,10 @@ static size_t bwd_factored_need(int B, int H, int T, int m, int n, int C, sfda_d
     if (need == 0 || !dtype_ok(in_dtype) || !sfda::bwd_factored_fits(BH, T, n) ||
         !bwd_factored_faster(BH, T, m, n, in_dtype == SFDA_BF16))
         return 0;
-    // (with few value columns the operand records are many times the states: not past 16 GiB)
+    // (with few value columns the operand records are many times the states: m 64 in float32, 1.6
+    // times the smaller workspace at n 64, 6.7 times at n 8, 53 times at n 1)
     const size_t bytes = sfda::bwd_factored_bytes(BH, T, m, n, in_dtype == SFDA_BF16);
-    return bytes <= std::max(need, size_t(16) << 30) ? std::max(need, bytes) : 0;
+    return bytes <= std::max(2 * need, need + BWD_EXTRA) ? std::max(need, bytes) : 0;
 }
 
 size_t sfda_chunk_bwd_auto_workspace_bytes(int B, int H, int T, int m, int n, int C, sfda_dtype_t in_dtype)

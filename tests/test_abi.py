@@ -356,3 +356,23 @@ def test_factored_rule_many_heads(lib, dtype, B, H, T, m, n, decoupled, want):
 def test_backward_rule_many_heads(lib, dtype, H, T, m, n, factored):
     least = lib.sfda_chunk_bwd_workspace_bytes(1, H, T, m, n, 64)
     assert (lib.sfda_chunk_bwd_auto_workspace_bytes(1, H, T, m, n, 64, dtype) > least) == factored
+
+
+def test_workspaces_are_bounded(lib):
+    """The forward is not sent to a workspace past its 256 MiB of records because one step of every
+    head needs more, and the backward's suggested workspace stays within twice the smaller one or
+    1280 MiB more than it."""
+    for heads, want in ((3000, 1), (16384, 0)):          # 76800 bytes a head
+        assert lib.sfda_chunk_fwd_auto_factored(1, heads, 1024, 64, 64, 64, 1, 1) == want
+    assert lib.sfda_chunk_fwd_auto_factored(1, 16384, 1024, 8, 8, 64, 0, 0) == 0
+    taken = 0
+    for dtype in (0, 1):
+        for heads in (1, 16, 128, 1024):
+            for T in (64, 1024, 4096, 32768):
+                for m in (1, 16, 64):
+                    for n in (1, 8, 17, 64, 96):
+                        least = lib.sfda_chunk_bwd_workspace_bytes(1, heads, T, m, n, 64)
+                        full = lib.sfda_chunk_bwd_auto_workspace_bytes(1, heads, T, m, n, 64, dtype)
+                        assert least <= full <= max(2 * least, least + (1280 << 20)), (dtype, heads, T, m, n)
+                        taken += full > least
+    assert taken > 100
