@@ -89,9 +89,9 @@ struct BwdLayout {
 //     right operands over the value columns, [channel block][column block of 16][lane (c, g)][4]
 //     complex, channel c, columns 4g .. 4g + 3 (the scan turns them through LDS); fp32: [channel][column]
 //     (its scan writes 8 columns of a channel at a time: half lines, quarter lines in the other order);
-//   rows: Delta and G_F of every block.  bf16 operands: as they enter the products, pairs in
-//     column fragments [column block][lane (c, g)][4], column c, tokens 4g .. 4g + 3 (rounding
-//     them here is the rounding every use of them makes); fp32: [token][column].
+//   rows: Delta and G_F of every block, fp32.  bf16 operands: in the accumulator's order
+//     [column block][lane (c, g)][4] complex, column c, tokens 4g .. 4g + 3 (a lane's 32 bytes are
+//     one line's quarter both ways); fp32: [token][column].
 // The gradient kernel walks from a run's ends to its blocks, three matrix products per block.  In
 // fp32 (32 cycles an instruction, and the SIMD issues nothing beside it) that costs more than
 // recording every block.  bf16, B8 H16 T4096 m n 64: runs of 1, 2, 4 blocks: scans 1150, 795, 615 us
@@ -107,7 +107,7 @@ struct GradLayout {
         blocks = (static_cast<long>(T) + CP - 1) / CP * NB;
         recs = static_cast<int>(blocks / grad_blocks(bf16));
         state = nkb * ncb * 2048;
-        rows = ncb * (bf16 ? 1024 : 2048);
+        rows = ncb * 2048;
     }
     __host__ __device__ size_t bytes(long heads) const {
         return static_cast<size_t>(heads) * 2 * (static_cast<size_t>(recs) * state + static_cast<size_t>(blocks) * rows);

@@ -1478,7 +1478,7 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
     } else {
         // ================================================ row waves: blocks of parity h
         const char* const rowrec = adj ? A.F_rows : A.D_rows;
-        const u32 rec_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 1024) + l16 : OOR;
+        const u32 rec_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 2048 + lane * 32) : OOR;
         const u32 st_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 2048 + lane * 32) : OOR;
         struct Pre { Frag<P> ns, an, u; float b[4]; };
         Pre pre[2];
@@ -1533,8 +1533,12 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
                         __builtin_amdgcn_raw_buffer_store_b32(pack_bf16(p.b[r] * d.re[r], -p.b[r] * d.im[r]), rv, off4[r], 0, 0);
                     fetch(st - 1, ch - st * NB, p);
                 }
-                const Frag<P> rows = frag_acc<P>(d);
-                __builtin_amdgcn_raw_buffer_store_b128(rows.w, wk.block_rows(A, rowrec, ch), rec_off, 0, 0);
+                const rsrc_t rr = wk.block_rows(A, rowrec, ch);
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(d.re[2 * e]), __float_as_uint(d.im[2 * e]),
+                                                                 __float_as_uint(d.re[2 * e + 1]), __float_as_uint(d.im[2 * e + 1])},
+                                                           rr, rec_off + e * 16, 0, 0);
             }
         }
     }

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
     // ---- the rows' tiles: tile kind * NBK + b, kind 0 Delta, 1 G_F (with V, for dbeta), 2 G_R
     // (bf16 rows stay the pairs they are: G_R's conjugate flips a sign bit)
     constexpr bool RAW_O = P == PREC_BF16 && sizeof(TOUT) == 2;
-    struct Tile { Frag<P> f; float2 x[4]; Raw4<TIN> v; };
+    struct Tile { float2 x[4]; Raw4<TIN> v; };      // (a pair that stays as loaded: in x[].x)
     auto tile_of = [&](int u, int& kind, int& b) __attribute__((always_inline)) {
         kind = NBK == 4 ? u : (w + 4 * u) / NBK;
         b = NBK == 4 ? w : (w + 4 * u) % NBK;
@@ -249,7 +249,12 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
         if (kind < 2) {
             const rsrc_t rr = kind ? r_f : r_d;
             if constexpr (P == PREC_BF16) {
-                x.f.w = __builtin_amdgcn_raw_buffer_load_b128(rr, lane * 16, b * A.lay.rows + cb * 1024, 0);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const f32x4 y = ldv4(rr, lane * 32 + e * 16, b * A.lay.rows + cb * 2048);
+                    x.x[2 * e] = make_float2(y[0], y[1]);
+                    x.x[2 * e + 1] = make_float2(y[2], y[3]);
+                }
             } else {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
@@ -258,7 +263,7 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
         } else if constexpr (RAW_O) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                x.f.w[r] = __builtin_amdgcn_raw_buffer_load_b32(r_o, j < n ? o_n * 2u : OOR, (b * 16 + r) * n * 4, 0);
+                x.x[r] = make_float2(__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r_o, j < n ? o_n * 2u : OOR, (b * 16 + r) * n * 4, 0)), 0.f);
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r) x.x[r] = ld_cplx<TOUT>(r_o, j < n ? o_n * static_cast<u32>(sizeof(TOUT)) : OOR, (b * 16 + r) * n * 2 * static_cast<int>(sizeof(TOUT)));
@@ -274,21 +279,24 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
 #pragma unroll
         for (int r = 0; r < 4; ++r) vd[u][r] = 0.f;
     auto put_tile = [&](int kind, int b, const Tile& x, GradTiles<P, NBK>& t, float (&acc)[4]) __attribute__((always_inline)) {
-        Frag<P> f = x.f;
+        Frag<P> f;
         if (kind == 2 && RAW_O) {
-            if constexpr (RAW_O) f.w ^= 0x80000000u;
+            if constexpr (RAW_O) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) f.w[r] = __float_as_uint(x.x[r].x) ^ 0x80000000u;
+            }
         } else if (kind == 2) {
             float2 y[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) y[r] = conj(x.x[r]);
             f = frag4<P>(y);
-        } else if (P == PREC_F32) {
+        } else {
             f = frag4<P>(x.x);
         }
         if (kind == 1) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float2 y = frag_get<P>(f, r);
+                const float2 y = x.x[r];
                 const float2 v = x.v.get(r);
                 acc[r] = __builtin_fmaf(y.x, v.x, __builtin_fmaf(-y.y, v.y, acc[r]));
             }
@@ -603,8 +611,7 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
             for (int r = 0; r < 4; ++r) {
                 const int s = row_m(b, r);
                 const float da = sl[r] + ol;
-                if constexpr (EI == 2) st_real<TIN>(r_da, o_m, s, da * __builtin_amdgcn_rcpf(x.a[r]));
-                else st_real<TIN>(r_da, o_m, s, da / x.a[r]);
+                st_real<TIN>(r_da, o_m, s, da / x.a[r]);
                 st_real<TIN>(r_dt, o_m, s, sp[r] + op);
             }
 #pragma unroll

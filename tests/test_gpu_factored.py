@@ -156,6 +156,30 @@ def test_backward_edges(lib, B, H, T, m, n, dtype, out):
         assert max(errs.values()) <= tol, errs
 
 
+def test_backward_rows_keep_32_bits(lib):
+    """bfloat16 inputs: G_F is recorded in 32 bits.  One key channel, alpha 1, theta 0, beta 0 and
+    no state: G_F of a token is dS_T plus the last token's dL/do, here 1 + 2^-10 and 1 in two columns
+    whose v are 1 and -1, every product exact; dbeta = 2^-10 in the last block, 0 from rows rounded
+    to bfloat16."""
+    import torch
+    from paper_2607_11897_amd import sfda
+    T, m, n = 64, 16, 16
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    q = torch.zeros(1, 1, T, m, 2, **bf)
+    q[..., 0, 0] = 1
+    v, dO = torch.zeros(1, 1, T, n, 2, **bf), torch.zeros(1, 1, T, n, 2, **bf)
+    v[..., 0, 0], v[..., 1, 0], dO[0, 0, -1, 0, 0] = 1, -1, 2.0 ** -10
+    dS = torch.zeros(1, 1, m, n, 2, device="cuda")
+    dS[0, 0, 0, :2, 0] = 1
+    least = sfda.bwd_workspace_bytes(1, 1, T, m, n, 64)
+    assert sfda.bwd_auto_workspace_bytes(1, 1, T, m, n, 64, "bf16") > least
+    say("rows in 32 bits")
+    g = sfda.chunk_bwd(q, q.clone(), v, torch.ones(1, 1, T, m, **bf), torch.zeros(1, 1, T, m, **bf),
+                       torch.zeros(1, 1, T, **bf), None, dO, dS)
+    torch.cuda.synchronize()
+    assert torch.equal(g["dbeta"][0, 0, -16:].float().cpu(), torch.full((16,), 2.0 ** -10))
+
+
 @pytest.mark.parametrize("dtype,B,H,T,m,n,decoupled,want", [
     ("f32", 1, 4, 48, 64, 64, 0, 0), ("f32", 1, 4, 49, 64, 64, 0, 1), ("f32", 1, 4, 33, 64, 64, 1, 1),
     ("f32", 1, 96, 96, 64, 64, 0, 0), ("f32", 1, 96, 97, 64, 64, 0, 1), ("f32", 4, 64, 512, 64, 64, 0, 0),
