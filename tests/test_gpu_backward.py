@@ -40,14 +40,21 @@ def as_np(t, complex_):
     return to_complex(t) if complex_ else t.float().cpu().numpy().astype(np.float64)
 
 
-def run_bwd(x, dO, dS, C, out_dtype):
+def run_bwd(x, dO, dS, C, out_dtype, in_place=False):
+    """in_place: with the smaller workspace, which leaves the scans in place where the other has room
+    for prepared operands."""
     import torch
     from paper_2607_11897_amd import sfda
+    ws = None
+    if in_place:
+        least = sfda.bwd_workspace_bytes(*x.shape, C)
+        assert sfda.bwd_auto_workspace_bytes(*x.shape, C, x.dtype) > least
+        ws = torch.full((least,), 0xFF, dtype=torch.uint8, device="cuda")
     d = upload(x)
     dO_t = to_device(I.to_storage(dO, out_dtype), out_dtype)
     dS_t = None if dS is None else to_device(I.to_storage(dS, "f32"), "f32")
     g = sfda.chunk_bwd(d["q"], d["k"], d["v"], d["alpha"], d["theta"], d["beta"], d["S0"], dO_t,
-                       dS_t, C=C)
+                       dS_t, C=C, workspace=ws)
     torch.cuda.synchronize()
     return {kk: as_np(g[kk], kk in ("dq", "dk", "dv", "dS0")) for kk in NAMES}
 
@@ -206,3 +213,36 @@ def test_bwd_full_size_sampled_heads(name, heads):
         ref = oracle_bwd(x.head(b, h), dO[b:b + 1, h:h + 1], dS[b:b + 1, h:h + 1])
         gh = {kk: got[kk][b:b + 1, h:h + 1] for kk in NAMES}
         check(gh, ref, w.tol, f"{name} head {(b, h)}")
+
+
+THETA = I.Laws(alpha=("uniform", 0.9, 1.0), theta=("uniform", -50.0, 50.0), beta=("uniform", 0.0, 1.0), s0_scale=0.1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,T,m,n,law", [
+    (1, 2, 229, 64, 24, "strong"), (1, 2, 229, 64, 24, "mixed"), (1, 2, 229, 64, 24, "theta"),
+    (2, 3, 300, 33, 24, "main"), (1, 2, 70, 64, 80, "main"), (1, 2, 97, 5, 3, "zero"),
+])
+def test_bwd_in_place(dtype, B, H, T, m, n, law):
+    """The scans in place and their gradient pass (the smaller workspace) past the few chunks that
+    reach them by default: strong and mixed decay, large phases, ragged sizes, the zero state."""
+    laws = {"strong": STRONG, "mixed": MIXED, "theta": THETA, "main": I.LAWS_MAIN,
+            "zero": I.Laws(I.LAWS_MAIN.alpha, I.LAWS_MAIN.theta, I.LAWS_MAIN.beta, None)}[law]
+    x = I.make_chunk_inputs(I.Workload("bwd", B, H, T, m, n, 64, dtype, laws, 430 + T, 1e-4))
+    dO, dS = I.make_cotangents(B, H, T, m, n, dtype, seed=530 + T)
+    say("in place", dtype, (B, H, T, m, n), law)
+    got = run_bwd(x, dO, dS, 64, dtype, in_place=True)
+    check(got, oracle_bwd(x, dO, dS), 1e-4 if dtype == "f32" else 2e-2, f"in place {dtype} {law}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_bwd_in_place_decay_outside_range_returns_nan(dtype):
+    """As test_bwd_decay_outside_range_returns_nan, with the smaller workspace."""
+    x = make(1, 2, 200, 64, 24, dtype, seed=33)
+    x.alpha[..., 144:160, 7] = I.round_to_storage(np.full(16, 0.001), dtype)
+    dO, dS = I.make_cotangents(1, 2, 200, 64, 24, dtype, seed=34)
+    say("in place", dtype, "backward out of range")
+    got = run_bwd(x, dO, dS, 64, dtype, in_place=True)
+    ref = oracle_bwd(x, dO, dS)
+    assert np.all(np.isnan(got["dS0"])) and np.all(np.isnan(got["dv"][:, :, :160]))
+    assert rel_err(got["dv"][:, :, 160:], ref["dv"][:, :, 160:]) <= (1e-4 if dtype == "f32" else 2e-2)

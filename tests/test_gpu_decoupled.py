@@ -40,6 +40,26 @@ def run_dec(x, C, S0=True):
     return to_complex(o), to_complex(S)
 
 
+def run_dec_in_place(x, C, S0=True):
+    """The one-launch entry sfda_chunk_fwd_decoupled (the binding sends most calls past it)."""
+    import ctypes
+    import torch
+    from paper_2607_11897_amd import sfda
+    lib = sfda.load_library()
+    st = x.storage()
+    d = [to_device(st[k], x.dtype) for k in ("q", "k", "r", "v", "alpha", "theta", "eta", "beta")]
+    d.append(to_device(st["S0"], "f32") if (S0 and st["S0"] is not None) else None)
+    B, H, T, m, n = x.q.shape[:4] + x.v.shape[3:4]
+    code = sfda.SFDA_F32 if x.dtype == "f32" else sfda.SFDA_BF16
+    o = torch.full((B, H, T, n, 2), float("nan"), dtype=d[0].dtype, device="cuda")
+    S = torch.full((B, H, m, n, 2), float("nan"), device="cuda")
+    p = lambda t: None if t is None else ctypes.c_void_p(t.data_ptr())
+    assert lib.sfda_chunk_fwd_decoupled(*map(p, d), p(o), p(S), B, H, T, m, n, C, code, code,
+                                        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    return to_complex(o), to_complex(S)
+
+
 def oracle_dec(x, S0=True):
     from oracle import decoupled as D
     return D.decoupled_recurrence(x.q, x.k, x.r, x.v, x.alpha, x.theta, x.eta, x.beta,
@@ -135,3 +155,36 @@ def test_decoupled_bf16_b8h16_t4k_full_sampled_heads():
         eo, es = rel_err(o[b, h], o_ref[0, 0]), rel_err(S[b, h], S_ref[0, 0])
         say((b, h), "err(o)", eo, "err(S_T)", es)
         assert eo <= 2e-2 and es <= 2e-2
+
+
+IN_PLACE_LAWS = {
+    "main": I.LAWS_MAIN,
+    "strong": I.Laws(alpha=("uniform", 0.02, 0.1), theta=("uniform", -3.14159, 3.14159), beta=("uniform", 0.0, 1.0), s0_scale=0.1),
+    "theta": I.Laws(alpha=("uniform", 0.9, 1.0), theta=("uniform", -50.0, 50.0), beta=("uniform", 0.0, 1.0), s0_scale=0.1),
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,T,m,n,law,S0", [
+    (1, 2, 100, 64, 64, "main", True),
+    (2, 1, 300, 33, 24, "main", True),
+    (1, 2, 130, 64, 80, "main", True),        # two column slices
+    (1, 1, 97, 5, 3, "main", True),
+    (1, 9, 129, 17, 72, "main", False),
+    (1, 2, 229, 64, 64, "strong", True),
+    (1, 2, 229, 48, 40, "theta", True),
+])
+def test_decoupled_in_place(dtype, B, H, T, m, n, law, S0):
+    """The scan in place over several chunks of its two alternating LDS sets: against the oracle, and
+    the factored form's result (each within the bar, so twice the bar apart)."""
+    x = I.make_decoupled_inputs(B, H, T, m, n, dtype, seed=650 + T, laws=IN_PLACE_LAWS[law])
+    say("in place", dtype, (B, H, T, m, n), law, S0)
+    o, S = run_dec_in_place(x, 32, S0)
+    o_ref, S_ref = oracle_dec(x, S0)
+    eo, es = rel_err(o, o_ref), rel_err(S, S_ref)
+    say("err(o)", eo, "err(S_T)", es)
+    tol = 1e-4 if dtype == "f32" else 2e-2
+    assert np.all(np.isfinite(o)) and np.all(np.isfinite(S))
+    assert eo <= tol and es <= tol
+    of, Sf = run_dec(x, 32, S0)
+    assert rel_err(o, of) <= 2 * tol and rel_err(S, Sf) <= 2 * tol
