@@ -640,6 +640,7 @@ __device__ __forceinline__ void scan_f32(ScanF32Smem& sm, const ScanArgs& A, uns
     long bh;
     int sl;
     if (!scan_place(wg, A.n_slices, A.heads, bh, sl)) return;
+    poison_area(red, 256);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4, qp = lane & 1;
@@ -735,6 +736,8 @@ __device__ __forceinline__ void scan_f32(ScanF32Smem& sm, const ScanArgs& A, uns
         fetch_w(next, b, p);
         red[b & 1][0][wave][lane] = pw;
         __syncthreads();
+        poison_slot(red[(b & 1) ^ 1][0][wave][lane]);
+        poison_slot(red[b & 1][1][wave][lane]);
         f32x4 d[4];
 #pragma unroll
         for (int w2 = 0; w2 < 4; ++w2) d[w2] = red[b & 1][0][w2][lane];
@@ -832,6 +835,8 @@ __global__ __launch_bounds__(512, 1) void scan_bf16_kernel(ScanArgs A)
     long bh;
     int sl;
     if (!scan_place(blockIdx.x, A.n_slices, A.heads, bh, sl)) return;
+    poison_area(red, 512);
+    poison_area(ent, 512);
     const int lane = threadIdx.x & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3;
     const int c = lane & 15, g = lane >> 4, h = wave & 1, cw = wave >> 1;
@@ -919,6 +924,12 @@ __global__ __launch_bounds__(512, 1) void scan_bf16_kernel(ScanArgs A)
             red[b & 1][wave][1][lane] = d.im;
             fetch_w(next, b, p);
             __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                poison_slot(red[(b & 1) ^ 1][wave][e][lane]);
+                poison_slot(ent[(b & 1) ^ 1][cw][2 * h][e][lane]);
+                poison_slot(ent[(b & 1) ^ 1][cw][2 * h + 1][e][lane]);
+            }
             const f32x4 ore = red[b & 1][wave ^ 1][0][lane], oim = red[b & 1][wave ^ 1][1][lane];
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
@@ -1090,6 +1101,7 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
     long bh;
     int sl;
     if (!scan_place(wg, A.n_slices, A.heads, bh, sl)) return;
+    poison_area(red, 256);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4, qp = lane & 1;
@@ -1182,6 +1194,7 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
                 fetch_w(next, b, p);
                 red[b & 1][0][wave][lane] = pw;
                 __syncthreads();
+                poison_slot(red[(b & 1) ^ 1][0][wave][lane]);
                 f32x4 d[4];
 #pragma unroll
                 for (int w2 = 0; w2 < 4; ++w2) d[w2] = red[b & 1][0][w2][lane];
@@ -1261,6 +1274,8 @@ __device__ __forceinline__ void bwd_f32(BwdF32Smem& sm, const BwdArgs& A, unsign
             fetch_k(next, b, p);
             red[b & 1][0][wave][lane] = px;
             __syncthreads();
+            poison_slot(red[(b & 1) ^ 1][0][wave][lane]);
+            poison_slot(red[b & 1][1][wave][lane]);
             f32x4 d[4];
 #pragma unroll
             for (int w2 = 0; w2 < 4; ++w2) d[w2] = red[b & 1][0][w2][lane];
@@ -1318,6 +1333,8 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
     long bh;
     int sl;
     if (!scan_place(adj ? blockIdx.x - nfwd : blockIdx.x, A.n_slices, A.heads, bh, sl)) return;
+    poison_area(red, 512);
+    poison_area(st_out, 512);
     const int lane = threadIdx.x & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3;
     const int c = lane & 15, g = lane >> 4, h = wave & 1, cw = wave >> 1;
@@ -1428,6 +1445,13 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
                 red[b & 1][wave][1][lane] = d.im;
                 fetch_a(next, b, p);
                 __syncthreads();
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    poison_slot(red[(b & 1) ^ 1][wave][e][lane]);
+                    if (b % GB == (ADJ ? GB - 1 : 0)) continue;      // (read behind this barrier)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) poison_slot(*reinterpret_cast<float2*>(st_out[wave][e] + (4 * g + r) * 144 + c * 8));
+                }
                 const f32x4 ore = red[b & 1][wave ^ 1][0][lane], oim = red[b & 1][wave ^ 1][1][lane];
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) {             // S <- g S (adjoint: conj(g) S)

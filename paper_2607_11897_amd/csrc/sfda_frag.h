@@ -148,6 +148,23 @@ __device__ __forceinline__ f32x4 ldv4(rsrc_t r, u32 off, int s = 0) {
 __device__ __forceinline__ float2 ldv2(rsrc_t r, u32 off, int s = 0) {
     return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, s, 0));
 }
+// LDS-poison debug build: a kernel's whole exchange area at entry (every thread of the workgroup), and
+// this lane's slot of a parity once the barrier behind its last read is passed, so that a read of what
+// is not written yet, or of what another block left, gives NaN
+template <typename T> __device__ __forceinline__ void poison_area(T& area, int nthr) {
+#ifdef SFDA_LDS_POISON
+    lds_poison(&area, sizeof(area), threadIdx.x, nthr);
+    __syncthreads();
+#endif
+}
+template <typename T> __device__ __forceinline__ void poison_slot(T& slot) {
+#ifdef SFDA_LDS_POISON
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) reinterpret_cast<u32*>(&slot)[i] = 0xFFFFFFFFu;
+#endif
+}
+
 // keeps the loads before it in this order for every block, so that the wait counts stay exact
 #define LOAD_ORDER() __builtin_amdgcn_sched_barrier(0)
 
