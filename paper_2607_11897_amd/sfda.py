@@ -186,6 +186,8 @@ def _workspace(nbytes: int, device, stream):
     import torch
     if stream is None:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if not isinstance(stream, torch.cuda.Stream):       # any object with a cuda_stream handle
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
     with torch.cuda.stream(stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 

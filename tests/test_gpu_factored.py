@@ -156,6 +156,36 @@ def test_backward_edges(lib, B, H, T, m, n, dtype, out):
         assert max(errs.values()) <= tol, errs
 
 
+class _Handle:
+    """A stream of some other library: only its handle."""
+    def __init__(self, h):
+        self.cuda_stream = h
+
+
+@pytest.mark.parametrize("wrap", [lambda s: s, lambda s: _Handle(s.cuda_stream)])
+def test_streams_given_as_objects(lib, wrap):
+    """Whatever has a cuda_stream is taken as the stream, also where the call allocates a workspace
+    on it; the workspace then belongs to that stream."""
+    import torch
+    from paper_2607_11897_amd import sfda
+    x = I.make_chunk_inputs(I.Workload("stream", 1, 2, 130, 16, 8, 64, "f32", I.LAWS_MAIN, 960, 1e-4))
+    d = upload(x)
+    args = [d[k] for k in ("q", "k", "v", "alpha", "theta", "beta", "S0")]
+    o, S = sfda.chunk_fwd(*args)
+    g = sfda.chunk_bwd(*args, o, S)
+    dec = sfda.chunk_fwd_decoupled(args[0], args[1], args[1], *args[2:5], args[5], args[5], args[6])
+    torch.cuda.synchronize()
+    say("streams")
+    side = torch.cuda.Stream()
+    st = wrap(side)
+    o2, S2 = sfda.chunk_fwd(*args, stream=st)
+    g2 = sfda.chunk_bwd(*args, o, S, stream=st)
+    dec2 = sfda.chunk_fwd_decoupled(args[0], args[1], args[1], *args[2:5], args[5], args[5], args[6], stream=st)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(S, S2) and all(torch.equal(g[k], g2[k]) for k in g)
+    assert all(torch.equal(a, b) for a, b in zip(dec, dec2))
+
+
 def test_backward_rows_keep_32_bits(lib):
     """bfloat16 inputs: G_F is recorded in 32 bits.  One key channel, alpha 1, theta 0, beta 0 and
     no state: G_F of a token is dS_T plus the last token's dL/do, here 1 + 2^-10 and 1 in two columns
