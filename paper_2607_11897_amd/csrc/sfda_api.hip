@@ -83,11 +83,13 @@ int auto_slice(long BH, int n)
     return slice;
 }
 
-// the factored scans run one workgroup per head and 8 value columns, and address a 64-token
-// step's rows of v, o and dL/do (at most 8 bytes per element) with 32-bit byte offsets
-bool factored_fits(long BH, int n)
+// the factored scans run workgroups of 256 threads per head and 8 value columns (bfloat16 operands:
+// 512 per 32), in a launch of less than 2^32 threads, and address a 64-token step's rows of v, o and
+// dL/do (at most 8 bytes per element) with 32-bit byte offsets
+bool factored_fits(long BH, int m, int n, bool in_bf16)
 {
-    return (BH + 7) * ((n + 7) / 8) <= 0x7FFFFFFFL && static_cast<long>(64) * n * 8 < 0x80000000L;
+    const long threads = sfda::bf16_operands(in_bf16, m) ? 512 * ((n + 31L) / 32) : 256 * ((n + 7L) / 8);
+    return (BH + 7) * threads < (1L << 32) && static_cast<long>(64) * n * 8 < 0x80000000L;
 }
 
 // most bytes of operand records that the suggested workspace holds at a time (the sequence then
@@ -372,7 +374,7 @@ size_t sfda_chunk_fwd_factored_workspace_bytes(int B, int H, int T, int m, int n
         !dtype_ok(in_dtype))
         return 0;
     const long BH = static_cast<long>(B) * H;
-    if (!factored_fits(BH, n)) return 0;
+    if (!factored_fits(BH, m, n, in_dtype == SFDA_BF16)) return 0;
     return sfda::factored_bytes(BH, T, m, n, in_dtype == SFDA_BF16, decoupled != 0, FACTORED_CAP);
 }
 
@@ -422,7 +424,7 @@ static sfda_status_t factored_impl(const sfda::ChunkLaunch& L, sfda_dtype_t in_d
                                    void* workspace, size_t workspace_bytes, sfda_stream_t stream)
 {
     const long BH = static_cast<long>(L.B) * L.H;
-    if (!factored_fits(BH, L.n)) return SFDA_ERR_SHAPE;
+    if (!factored_fits(BH, L.m, L.n, L.in_bf16)) return SFDA_ERR_SHAPE;
     const size_t need = sfda_chunk_fwd_factored_workspace_bytes(L.B, L.H, L.T, L.m, L.n, in_dtype, L.r != nullptr);
     if (!workspace) return SFDA_ERR_NULL;
     if (!aligned16(workspace)) return SFDA_ERR_ALIGN;
@@ -564,7 +566,7 @@ static sfda_status_t segmented_impl(const void* q, const void* k, const void* v,
         // faster one, the factored forward, which needs no segments
         const long cus = device_cus() > 0 ? device_cus() : 256;
         const sfda::FactoredPlan p = sfda::factored_plan(BH, T, m, n, false, false, need, cus);
-        const bool fits = factored_fits(BH, n) && p.piece > 0;
+        const bool fits = factored_fits(BH, m, n, false) && p.piece > 0;
         if (G == 1 || (fits && prepared_us(T, p) <= segments_us(BH, T, m, n, G, L.out_bf16, cus))) {
             L.v = v; L.B = B; L.H = H; L.T = T; L.n = n; L.S0 = S0; L.S_T = S_T; L.o = o;
             L.slice = auto_slice(BH, n);

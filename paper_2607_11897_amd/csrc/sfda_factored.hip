@@ -1,5 +1,6 @@
 // The factored chunk evaluation (sfda_factored.h has the relations and the operand records):
 // the preparing kernel and the scans.
+#include <algorithm>
 #include <type_traits>
 
 #include "sfda_factored.h"
@@ -1626,7 +1627,7 @@ FactoredPlan factored_plan(long heads, int T, int m, int n, bool in_bf16, bool d
     const bool whole = static_cast<size_t>(steps) * one <= bytes;
     FactoredPlan p{whole ? steps : (static_cast<long>(bytes) - carry_bytes) / one, false};
     if (p.piece < 1) return FactoredPlan{0, false};
-    const long most = 0x7FFFFFFFL / heads;              // workgroups of a launch
+    const long most = ((1L << 32) / 256 - 1) / heads;   // workgroups of a launch (less than 2^32 threads)
     if (p.piece > most) p.piece = most;
     // float32 scans on at most half of the compute units: each piece's scan with the next one's
     // preparation beside it, the records in two halves of the workspace (H16 T65536: 3.86 ms
@@ -1691,10 +1692,12 @@ hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus
 
 // ------------------------------------------------------------------ backward
 
-// (n: a state record's bytes and a step's rows are 32-bit offsets)
+// (n: a state record's bytes and a step's rows are 32-bit offsets; the gradient kernel's and both scans'
+// launches, 256 threads per run of blocks, 256 per 8 or 512 per 32 columns, have less than 2^32 threads)
 bool bwd_factored_fits(long heads, int T, int n)
 {
-    return heads * (T / 16L + fac::NB) <= 0x7FFFFFFFL && n <= (1 << 20) && 2 * (heads + 7) * (((static_cast<long>(n) + 15) / 16) * 2) <= 0x7FFFFFFFL;
+    const long scans = std::max(256 * ((n + 7L) / 8), 512 * ((n + 31L) / 32));
+    return heads * (T / 16L + fac::NB) * 256 < (1L << 32) && n <= (1 << 20) && 2 * (heads + 7) * scans < (1L << 32);
 }
 
 size_t bwd_factored_bytes(long heads, int T, int m, int n, bool in_bf16)

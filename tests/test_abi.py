@@ -376,3 +376,17 @@ def test_workspaces_are_bounded(lib):
                         assert least <= full <= max(2 * least, least + (1280 << 20)), (dtype, heads, T, m, n)
                         taken += full > least
     assert taken > 100
+
+
+@pytest.mark.parametrize("dtype,n,heads", [(0, 64, 1 << 21), (0, 8, 1 << 24), (1, 8, 1 << 23), (1, 32, 1 << 23), (1, 64, 1 << 22)])
+def test_factored_launches_stay_below_two_to_32_threads(lib, dtype, n, heads):
+    """A launch has less than 2^32 threads (256 per head and 8 columns, bfloat16 operands 512 per 32
+    columns): past that the factored forward has no workspace and refuses the call, instead of
+    failing after its first launch."""
+    B = 1 << 10
+    f = lib.sfda_chunk_fwd_factored_workspace_bytes
+    assert f(B, heads // B - 1, 64, 8, n, dtype, 1) > 0              # (1024 heads below the line)
+    assert f(B, heads // B, 64, 8, n, dtype, 1) == 0
+    if dtype == 0:
+        q, k, v, a, t, b, o, w = [P[0] + (i << 50) for i in range(1, 9)]
+        assert lib.sfda_chunk_fwd_factored(q, k, v, a, t, b, None, o, None, B, heads // B, 64, 8, n, 64, 0, 0, w, 1 << 40, None) == 2
