@@ -609,7 +609,7 @@ struct Span {
     const char* fac;
     __device__ __forceinline__ Span(const ScanArgs& A, long bh) {
         tb = A.step0 * CP;
-        te = min(A.T, tb + A.nsteps * CP);
+        te = tb + min(A.T - tb, A.nsteps * CP);
         nsteps = (te - tb + CP - 1) / CP;
         base_tn = (bh * A.T + tb) * static_cast<long>(A.n);
         base_mn = bh * static_cast<long>(A.m) * A.n;
@@ -1645,7 +1645,7 @@ hipError_t launch_factored(const ChunkLaunch& L, void* ws, size_t bytes, int cus
     using namespace fac;
     const bool dec = L.r != nullptr, bf = bf16_operands(L.in_bf16, L.m);
     const long heads = static_cast<long>(L.B) * L.H;
-    const int steps = (L.T + CP - 1) / CP;
+    const int steps = static_cast<int>((static_cast<long>(L.T) + CP - 1) / CP);
     const long one = fac_step_bytes(heads, L.m, bf, dec);
     const long carry_bytes = heads * L.m * static_cast<long>(L.n) * 8;
     const FactoredPlan plan = factored_plan(heads, L.T, L.m, L.n, L.in_bf16, dec, bytes, cus);
@@ -1713,7 +1713,7 @@ hipError_t launch_bwd_factored(const ChunkLaunch& F, const ChunkLaunch& L, const
     using namespace fac;
     const bool bf = bf16_operands(F.in_bf16, F.m);
     const long heads = static_cast<long>(F.B) * F.H;
-    const int steps = (F.T + CP - 1) / CP;
+    const int steps = static_cast<int>((static_cast<long>(F.T) + CP - 1) / CP);
     const GradLayout gl(F.T, F.m, F.n, bf);
     char* const rec = static_cast<char*>(ws) + heads * gl.blocks * BwdLayout(F.m, bf).block;
     const size_t states = static_cast<size_t>(heads) * gl.recs * gl.state, rows = static_cast<size_t>(heads) * gl.blocks * gl.rows;

@@ -390,3 +390,14 @@ def test_factored_launches_stay_below_two_to_32_threads(lib, dtype, n, heads):
     if dtype == 0:
         q, k, v, a, t, b, o, w = [P[0] + (i << 50) for i in range(1, 9)]
         assert lib.sfda_chunk_fwd_factored(q, k, v, a, t, b, None, o, None, B, heads // B, 64, 8, n, 64, 0, 0, w, 1 << 40, None) == 2
+
+
+def test_factored_length_near_two_to_31(lib):
+    """T within 64 of 2^31: the count of 64-token steps does not overflow (the sanitizer run of this suite
+    reports it if it does).  Here, without a device, the first launch returns SFDA_ERR_HIP."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are not real: only where nothing can be launched")
+    T = (1 << 31) - 32
+    q, k, v, a, t, b, o, w = [P[0] + (i << 50) for i in range(1, 9)]
+    assert lib.sfda_chunk_fwd_factored(q, k, v, a, t, b, None, o, None, 1, 1, T, 1, 1, 16, 0, 0, w, 1 << 40, None) == 7
