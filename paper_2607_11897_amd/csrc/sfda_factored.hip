@@ -609,7 +609,7 @@ struct Span {
     const char* fac;
     __device__ __forceinline__ Span(const ScanArgs& A, long bh) {
         tb = A.step0 * CP;
-        te = tb + min(A.T - tb, A.nsteps * CP);
+        te = static_cast<int>(min(static_cast<unsigned>(A.T), static_cast<unsigned>(tb) + static_cast<unsigned>(A.nsteps) * CP));
         nsteps = (te - tb + CP - 1) / CP;
         base_tn = (bh * A.T + tb) * static_cast<long>(A.n);
         base_mn = bh * static_cast<long>(A.m) * A.n;
