@@ -24,7 +24,8 @@
 //   -W  [nkb]  rows tokens,   K channels of kb         Z  [nkb]  the same
 //   K Q [nkb]  rows channels of kb, K tokens            (R Q) D_beta [nkb]  (decoupled)
 //   X, Y       rows tokens, K tokens
-//   |D| [64] fp32; e^{i phi} of the step's whole phase [64] complex fp32 (block 3's is used)
+//   |D| [64] fp32; e^{i phi} of the step's whole phase [64] complex fp32 (in every block; the
+//   scans read block 0's)
 // Phases are relative to the step's first token; the scans rotate the state by the step's
 // phase after its last block.  Decay magnitudes are relative to the block, as in the bf16
 // kernel, and a block whose decay falls below 2^-126 has NaN operands.

@@ -234,8 +234,8 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
     constexpr bool RAW_O = P == PREC_BF16 && sizeof(TOUT) == 2;
     struct Tile { float2 x[4]; Raw4<TIN> v; };      // (a pair that stays as loaded: in x[].x)
     auto tile_of = [&](int u, int& kind, int& b) __attribute__((always_inline)) {
-        kind = NBK == 4 ? u : (w + 4 * u) / NBK;
-        b = NBK == 4 ? w : (w + 4 * u) % NBK;
+        kind = (w + 4 * u) / NBK;
+        b = (w + 4 * u) % NBK;
         return w + 4 * u < NT;
     };
     const long e_n = 2 * (bh * T + t0) * static_cast<long>(n);

@@ -28,7 +28,7 @@ def say(*a):
     print("[case]", *a, flush=True)
 
 
-def factored(lib, x, bytes_=None):
+def factored(lib, x):
     """sfda_chunk_fwd_factored through the C entry (every dtype), its workspace poisoned."""
     import torch
     from paper_2607_11897_amd import sfda
