@@ -620,6 +620,7 @@ def bwd_hash() -> str:
     h = hashlib.sha256()
     for p in ("paper_2607_11897_amd/csrc/sfda_factored.hip", "paper_2607_11897_amd/csrc/sfda_factored.h",
               "paper_2607_11897_amd/csrc/sfda_grad.hip", "paper_2607_11897_amd/csrc/sfda_frag.h",
+              "paper_2607_11897_amd/csrc/sfda_chunk.hip", "paper_2607_11897_amd/csrc/sfda_segments.hip",
               "paper_2607_11897_amd/csrc/sfda_chunk_common.h", "paper_2607_11897_amd/csrc/sfda_device.h"):
         with open(os.path.join(ROOT, p), "rb") as f:
             h.update(f.read())

@@ -368,9 +368,10 @@ const char* sfda_status_string(sfda_status_t s);
  * sfda_chunk_solve_monitor -- the conditioning watch that Prop. 6.4 asks for (its bound
  * ||M||_2 <= 1 / (1 - eta) holds when ||L||_2 <= eta < 1, which the gates do not enforce):
  * for every 16-token block of every head (the blocking of the chunk kernels), the
- * triangular solve that forms N = (I + D_beta L')^{-1} is repeated exactly as the float32
- * path's kernels do it (same load stage, Gram products and substitution; with bfloat16
- * inputs and m > 4 the Gram products take bfloat16 operands, as in the backward's scans), and
+ * triangular solve that forms N = (I + D_beta L')^{-1} is repeated exactly as the scans in
+ * place on float32 operands do it (same load stage, Gram products and substitution; with
+ * bfloat16 inputs and m > 4 the Gram products take bfloat16 operands, as in the backward's
+ * scans; the factored forms solve the same systems to rounding), and
  *   residual[b, h, blk] = max_ij |((I + D_beta L') N - I)_ij|   (on the L' it used)
  *   lnorm[b, h, blk]    = ||D_beta L'||_F   (an upper bound of the spectral norm)
  * are written, float32, [B, H, ceil(T / 16)].  L'[t, j] = k_t^* diag(g_t / g_j) k_j for j < t

@@ -390,7 +390,8 @@ int sfda_chunk_fwd_auto_factored(int B, int H, int T, int m, int n, int C, sfda_
         // place or in segments / factored, m n 64: 12 heads T 192 20/19, T 256 24/22, T 1536 100/73,
         // T 2560 119/105, T 4096 132/159; 32 heads T 256 24/24, T 1536 100/75; 48 heads T 384 32/35,
         // T 768 55/50, T 3072 193/168; 64 heads T 384 32/34, T 768 55/50, T 1536 101/90, T 2048
-        // 130/131; 96 heads T 1024 71/73; n 96: 48 heads T 768 56/50, 64 heads T 768 56/50, T 2048 132/136;
+        // 130/131; 96 heads T 1024 76/78, T 4096 257/326; 128 heads T 1024 73/100, T 4096 262/372 (records of
+        // 495 MB); 256 heads T 4096 351/750; 128 heads T 4096 m 32 n 32 252/301; n 96: 48 heads T 768 56/50, 64 heads T 768 56/50, T 2048 132/136;
         // with half the channels or columns the records are half as many: 64 heads T 2048, T 4096: m 16
         // n 64 130/98, 252/197, m 64 n 16 138/115, 271/249, m 36 n 29 136/107, 267/239
         const long slices = (n + 31L) / 32;

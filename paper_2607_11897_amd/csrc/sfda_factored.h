@@ -95,8 +95,9 @@ struct BwdLayout {
 //     one line's quarter both ways); fp32: [token][column].
 // The gradient kernel walks from a run's ends to its blocks, three matrix products per block.  In
 // fp32 (32 cycles an instruction, and the SIMD issues nothing beside it) that costs more than
-// recording every block.  bf16, B8 H16 T4096 m n 64: runs of 1, 2, 4 blocks: scans 1150, 795, 615 us
-// (what they write), gradients 720, 670, 1060-1570 (four blocks' sums do not fit the registers).
+// recording every block.  bf16, B8 H16 T4096 m n 64 (with rows of 16 bits): runs of 1, 2, 4 blocks:
+// scans 1150, 795, 615 us (what they write), gradients 720, 670, 1060-1570 (four blocks' sums do not
+// fit the registers).
 __host__ __device__ constexpr int grad_blocks(bool bf16) { return bf16 ? 2 : 1; }
 struct GradLayout {
     int nkb, ncb, recs;                  // recs: state records per head

@@ -26,10 +26,10 @@
 // elementwise stage finds G_Qg, G_Kg, G_Ki, q, k and g on one lane.  Only the rows (Delta, G_F, G_R:
 // shared by the channel blocks) and the four 16 x 16 products pass through LDS.
 //
-// Bound by vector issue: about 1350 instructions per wave and block around 54 matrix instructions
-// (bf16), two waves per SIMD; fp32 by the matrix instructions (332 of 32 cycles).  B8 H16 T4096 bf16
-// 600-660 us from box to box, B4 H8 T2048 float32 172 us, B2 H6 T509 bf16 11 us, where the pass over the 16-token chunks'
-// records (staging S and G themselves through LDS) takes 1190, 241 and 19 us.
+// Bound by memory (bf16): B8 H16 T4096 reads 2.62 GB and writes 0.40 in 600-620 us, 5 TB/s where a
+// device copy runs at 5.17; fp32 by the matrix instructions (332 of 32 cycles a block): B4 H8 T2048
+// 175-185 us; B2 H6 T509 bf16 11 us.  The pass over the 16-token chunks' records (staging S and G
+// themselves through LDS) takes 1190, 241 and 19 us.
 #include <type_traits>
 
 #include "sfda_factored.h"
