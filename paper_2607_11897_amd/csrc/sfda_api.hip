@@ -104,8 +104,8 @@ constexpr size_t BWD_EXTRA = size_t(1280) << 20;
 // Whether the factored forward is the faster one.
 //  * bfloat16 operands (the write-decoupled forward: 256 compute units, m n 64): past 48 tokens, us in
 //    place / factored T 48 21/24, T 64 26/24.
-//  * float32 operands: by an estimate of both in us, fitted to 3600 measured pairs of 16 .. 1500 heads
-//    x 33 .. 1000 tokens (each within 22%, the rule's picks within 3% of the better side).  In place:
+//  * float32 operands: by an estimate of both in us, fitted to 5100 measured pairs of 16 .. 6000 heads
+//    x 33 .. 1000 tokens (each within 27%, 4 of the rule's picks 3 to 8% behind the other side).  In place:
 //    rounds of one workgroup per compute unit, a chain of blocks each.  Factored: a floor of two
 //    launches and a chain of blocks, then time per head and block, padding blocks of the last 64-token
 //    step among them (preparation: channel blocks; scan: 8-column workgroups), and for every
@@ -114,7 +114,7 @@ constexpr size_t BWD_EXTRA = size_t(1280) << 20;
 //    160 heads m 48 n 32 T 80 34/43; 768 heads m 64 n 32 T 160 189/251; 1500 heads m 48 n 64 T 300
 //    931/1237; 256 heads m n 64 T 512 265/286, m 16 n 64 257/203; decoupled, 256 heads m 3 n 64 T 80
 //    61/80, 1500 heads m 64 n 48 T 160 675/904, m 16 n 8 T 49 215/76.  It takes a workspace, so it has to
-//    be 4% ahead.
+//    be 5% ahead.
 struct Blocks { long nb, pad, nkb, cols; };    // 16-token blocks, those of whole steps; channel and 8-column blocks
 Blocks blocks_of(int T, int m, int n) { return {(T + 15L) / 16, (T + 63L) / 64 * 4, (m + 15) / 16, (n + 7L) / 8}; }
 long rounds_of(long workgroups, long cus) { return (workgroups + cus - 1) / cus; }
@@ -129,11 +129,11 @@ bool factored_faster(long BH, int T, int m, int n, bool in_bf16, bool dec)
     const double x = static_cast<double>(BH) / cus, wide = static_cast<double>(k.cols * k.nkb);
     const sfda::FactoredPlan p = sfda::factored_plan(BH, T, m, n, in_bf16, dec, sfda::factored_bytes(BH, T, m, n, in_bf16, dec, FACTORED_CAP), cus);
     const double more = p.piece > 0 && !p.beside ? (k.pad / 4 + p.piece - 1) / p.piece - 1 : 0;
-    const double in_place = dec ? 6.0 + chain * (8.07 + (slice > 32 ? 3.15 : 0.) + 0.109 * k.nkb)
-                                : 5.7 + chain * (5.44 + (slice > 32 ? 2.53 : 0.) + 0.071 * k.nkb);
-    const double factored = dec ? 14.8 + 0.523 * k.pad + x * k.pad * (0.539 + 0.835 * k.nkb + 0.798 * k.cols + 0.034 * wide) + more * (26.6 + 0.468 * x * wide)
-                                : 12.7 + 0.435 * k.pad + x * k.pad * (0.354 + 0.640 * k.nkb + 0.605 * k.cols + 0.018 * wide) + more * (23.2 + 0.416 * x * wide);
-    return factored < 0.96 * in_place;
+    const double in_place = dec ? 5.4 + chain * (8.21 + (slice > 32 ? 3.15 : 0.) + 0.091 * k.nkb)
+                                : 5.2 + chain * (5.61 + (slice > 32 ? 2.53 : 0.) + 0.052 * k.nkb);
+    const double factored = dec ? 14.5 + 0.468 * k.pad + x * k.pad * (0.610 + 0.841 * k.nkb + 0.831 * k.cols + 0.030 * wide) + more * (21.6 + x * (1.52 * k.cols + 0.096 * wide))
+                                : 12.6 + 0.372 * k.pad + x * k.pad * (0.455 + 0.629 * k.nkb + 0.641 * k.cols + 0.013 * wide) + more * (16.7 + x * 1.59 * k.cols);
+    return factored < 0.95 * in_place;
 }
 // The float32 forward over G segments against the one on prepared operands, estimated in us (MI355X):
 // the segments' chain costs 8.5 .. 14.5 us a 16-token block with the columns of both sets (past 64
