@@ -159,24 +159,22 @@ double prepared_us(int T, const sfda::FactoredPlan& p)
 }
 // and the backward on prepared operands (three launches; two in place).  us in place / factored:
 // bfloat16 T 32 30/33, T 48 34/34, T 64 40/34; float32 T 16 34/35, T 32 42/35, 64 heads m n 64 T 32
-// 46/53, T 48 56/53, 96 heads T 80 83/97, T 96 108/97, 128 heads T 96 111/117, T 128 138/119.  In
-// float32, workgroups that fill whole rounds of the chip leave the chain nothing to wait for (256 heads
-// T 256 511/530), and elsewhere the estimate (as above; the gradient pass adds time per block on
-// both sides) keeps short sequences of many heads in place: 384 heads m n 64 T 112 359/396,
-// bfloat16 inputs 1024 heads m 1 n 64 T 80 607/680; 512 heads m 16 n 64 T 112 424/361.
+// 46/53, T 48 56/53, 57 heads m 58 n 32 T 80 64/54, 96 heads m n 64 T 80 83/97, T 96 108/97, 128 heads T 96
+// 111/117, T 128 138/119.  With float32 operands, workgroups that fill whole rounds of the chip (the
+// padding of the last 64-token step counted in) leave the chain nothing to wait for: 256 heads m n 64
+// T 256 511/530, 384 heads T 112 359/396, m 48 768 heads 672/699, 512 heads m 16 T 112 424/361;
+// bfloat16 inputs of few channels by their columns alone: 1024 heads m 1 n 64 T 80 607/680, T 96
+// 727/683, 768 heads n 96 T 80 769/717.
 bool bwd_factored_faster(long BH, int T, int m, int n, bool in_bf16)
 {
     if (T <= (in_bf16 ? 48 : 16)) return false;
     if (sfda::bf16_operands(in_bf16, m)) return true;
     const long cus = device_cus() > 0 ? device_cus() : 256;
     const Blocks k = blocks_of(T, m, n);
-    const long cols = BH * k.cols, slices = (n + 63L) / 64;
-    if (!in_bf16 && T <= (cols >= 4 * cus ? 96 : cols >= 3 * cus ? 80 : cols >= 2 * cus ? 32 : 16)) return false;
-    if (!in_bf16 && cols * k.nkb >= 0.92 * 32 * static_cast<double>(cus * rounds_of(BH * slices, cus))) return false;
-    const double x = static_cast<double>(BH) / cus;
-    const double in_place = 15.8 + rounds_of(2 * BH * slices, cus) * k.nb * (6.42 + (n > 32 ? 3.43 : 0.)) + x * k.nb * (8.28 + 0.298 * k.nkb * n / 16);
-    const double factored = 21.7 + 0.535 * k.pad + x * k.pad * (2.36 + 1.42 * k.nkb + 1.66 * k.cols + 0.232 * k.cols * k.nkb);
-    return factored < 0.96 * in_place;
+    const long cols = BH * k.cols;
+    const double filled = static_cast<double>(cols) * k.pad / (static_cast<double>(k.nb) * 8 * cus * rounds_of(BH * ((n + 63L) / 64), cus));
+    if (in_bf16) return filled < 1.4;
+    return T > (cols >= 4 * cus ? 96 : cols >= 3 * cus ? 80 : cols >= 2 * cus ? 32 : 16) && filled * k.nkb / 4 < 0.84;
 }
 
 }  // namespace

@@ -350,6 +350,9 @@ def test_factored_rule_many_heads(lib, dtype, B, H, T, m, n, decoupled, want):
     (0, 384, 112, 64, 64, False),        # 359/396
     (1, 1024, 80, 1, 64, False),         # 607/680
     (0, 512, 112, 16, 64, True),         # 424/361
+    (0, 57, 80, 58, 32, True),           # 64/54
+    (0, 96, 80, 64, 64, False),          # 83/97
+    (1, 1024, 96, 4, 64, True),          # 727/683
     (1, 1024, 49, 2, 8, True),           # 362/117
     (0, 32, 2048, 64, 64, True),
 ])
