@@ -236,8 +236,8 @@ sfda_status_t sfda_chunk_fwd_decoupled_factored(const void* q, const void* k, co
  * factors, twice the columns).  Two to three times the scan work of sfda_chunk_fwd, spread over
  * G times as many workgroups; results agree with it to rounding.  With float32 inputs the call
  * runs the factored forward (sfda_chunk_fwd_factored, bitwise its result) in the same workspace
- * instead, a piece of the sequence at a time, where that is the faster one: G == 1, or segments
- * that are many blocks each or too few beside the fold's chain.
+ * instead, a piece of the sequence at a time, where that is the faster one (G == 1, or a G that
+ * leaves each segment many blocks).
  *   Arguments and errors as sfda_chunk_fwd, plus:
  *   G >= 1 with T a multiple of G * C (SFDA_ERR_SHAPE otherwise; T == 0 is as
  *   sfda_chunk_fwd).

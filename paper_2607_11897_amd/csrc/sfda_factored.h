@@ -91,8 +91,8 @@ struct BwdLayout {
 //     complex, channel c, columns 4g .. 4g + 3 (the scan turns them through LDS); fp32: [channel][column]
 //     (its scan writes 8 columns of a channel at a time: half lines, quarter lines in the other order);
 //   rows: Delta and G_F of every block, fp32.  bf16 operands: in the accumulator's order
-//     [column block][lane (c, g)][4] complex, column c, tokens 4g .. 4g + 3 (a lane's 32 bytes are
-//     one line's quarter both ways); fp32: [token][column].
+//     [column block][half][lane (c, g)][2] complex, column c, tokens 4g + 2 half + {0, 1} (whole lines
+//     by an instruction); fp32: [token][column].
 // The gradient kernel walks from a run's ends to its blocks, three matrix products per block.  In
 // fp32 (32 cycles an instruction, and the SIMD issues nothing beside it) that costs more than
 // recording every block.  bf16, B8 H16 T4096 m n 64 (with rows of 16 bits): runs of 1, 2, 4 blocks:

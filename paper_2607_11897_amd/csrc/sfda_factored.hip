@@ -1504,7 +1504,7 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
     } else {
         // ================================================ row waves: blocks of parity h
         const char* const rowrec = adj ? A.F_rows : A.D_rows;
-        const u32 rec_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 2048 + lane * 32) : OOR;
+        const u32 rec_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 2048) + l16 : OOR;
         const u32 st_off = sl * 2 + cw < A.grad.ncb ? static_cast<u32>((sl * 2 + cw) * 2048 + lane * 32) : OOR;
         struct Pre { Frag<P> ns, an, u; float b[4]; };
         Pre pre[2];
@@ -1564,7 +1564,7 @@ __global__ __launch_bounds__(512, 1) void bwd_bf16_kernel(BwdArgs A, unsigned nf
                 for (int e = 0; e < 2; ++e)
                     __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(d.re[2 * e]), __float_as_uint(d.im[2 * e]),
                                                                  __float_as_uint(d.re[2 * e + 1]), __float_as_uint(d.im[2 * e + 1])},
-                                                           rr, rec_off + e * 16, 0, 0);
+                                                           rr, rec_off + e * 1024, 0, 0);
             }
         }
     }

@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256, 2) void grad_steps_kernel(GradArgs A)
             if constexpr (P == PREC_BF16) {
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    const f32x4 y = ldv4(rr, lane * 32 + e * 16, b * A.lay.rows + cb * 2048);
+                    const f32x4 y = ldv4(rr, lane * 16 + e * 1024, b * A.lay.rows + cb * 2048);
                     x.x[2 * e] = make_float2(y[0], y[1]);
                     x.x[2 * e + 1] = make_float2(y[2], y[3]);
                 }
