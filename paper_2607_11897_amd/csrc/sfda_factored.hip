@@ -1047,7 +1047,7 @@ __global__ __launch_bounds__(512, 1) void scan_bf16_kernel(ScanArgs A)
 // one launch (they read the same records and are independent).  fp32 is bound by the SIMDs' issue
 // (both scans' workgroups share them: 330 us for B4 H8 T2048, 128 blocks at 2.6 us), bf16 at many
 // heads by what it writes and reads (B8 H16 T4096: 1.07 GB of states, 0.54 GB of rows and 0.14 GB of
-// dv written, 1.08 GB read, 800 us: 3.5 TB/s, two rounds of workgroups in a chain of blocks; with rows
+// dv written, 1.08 GB read, 780 us: 3.6 TB/s, two rounds of workgroups in a chain of blocks; with rows
 // of 16 bits 740 us, then with the states of every block 1150 us, of every fourth 615 us, but see
 // grad_blocks).  The scans in place take 1112 and 1290 us.
 struct BwdArgs {
